@@ -1747,7 +1747,47 @@ __global__ __launch_bounds__(1024) void k_cluster_big(ClusterArgs<T> A, T* scrat
 // k-step kk, element (16 I + l%16, 16 K + 4 kk + l/16), is the conjugate of register kk of
 // block (K, I): both operands come straight from the registers, with no data movement.
 constexpr int kExpmLut = 8;   // children handled through the LDS index tables (more: generic path)
-constexpr int kF64Squarings = 4;   // float-message path: squarings kept in FP64 before the FP32 ones
+constexpr int kF64Squarings = 2;   // float-message path: squarings kept in FP64 before the FP32 ones
+
+// The degree-12 polynomial p of the scaled exponential, p(x) ~ e^x on |x| <= kMax (every matrix here
+// is Hermitian, so only its real spectrum counts): the least largest relative error |p e^-x - 1|
+// under p(0) = p'(0) = 1, so that the error vanishes with x like x^2.  With y = kappa x it takes
+// four products,
+//     a6 = (y3 + b2 y2 + b1 y)^2 + r3 y3 + r2 y2 + r1 y,   p = (a6 + s3 y3 + s2 y2 + s1 y + s0) a6
+//          + t2 y2 + t1 y + 1,    y2 = y y, y3 = y y2,
+// kappa chosen to make the leading coefficient one.  Double messages: error 1.2e-14 on |x| <= 0.9
+// (a degree-12 Taylor polynomial takes five products and has 2e-14 on |x| <= 1/2); float messages:
+// 3.9e-9 on |x| <= 2.4 (degree-8 Taylor: four products, 5.4e-9 on |x| <= 1/2).
+template <typename T>
+struct ExpPoly;
+template <>
+struct ExpPoly<double> {
+  static constexpr double kMax = 0.9, kappa = 0.18882898470408857303, b2 = 0.58464362112354427638,
+                          b1 = 0.6831284791247130648, r3 = -0.023881684476552449845, r2 = 1.9385928716127867965,
+                          r1 = 1.0589551634691213031, s3 = 3.4831354272642447593, s2 = 1.7307059423721896079,
+                          s1 = 4.8156775029998268864, s0 = 8.0579615953395820167, t2 = -11.579710521939010742,
+                          t1 = -3.2372228833013124739;
+};
+template <>
+struct ExpPoly<float> {
+  static constexpr double kMax = 2.4, kappa = 0.18744074848716354881, b2 = 0.6860333548991685841,
+                          b1 = 0.60433167933303673257, r3 = -0.050660677725442783478, r2 = 1.9738009571293383397,
+                          r1 = 1.3925347923639631316, s3 = 3.4378842818474047335, s2 = 1.9047025547120234848,
+                          s1 = 4.2055893558107449546, s0 = 8.0977661592032409989, t2 = -12.50518558919466365,
+                          t1 = -5.9414018746586668523;
+};
+
+// The number of squarings for a matrix of spectral radius at most nrm: the least s >= 0 with
+// nrm <= kMax 2^s, at most 200 (0 for a NaN norm), from the binary exponent of nrm / kMax.
+template <typename T>
+__device__ __forceinline__ int expm_squarings(double nrm) {
+  const double x = nrm * (1.0 / ExpPoly<T>::kMax);
+  if (!(x > 1.0)) return 0;
+  if (!(x <= 0x1p199)) return 200;
+  int e;
+  const double m = frexp(x, &e);   // x = m 2^e, 0.5 <= m < 1
+  return m == 0.5 ? e - 1 : e;
+}
 
 // pext and pdep over the site bits of a one-wave cluster (at most 5 sites), for every site mask,
 // built at compile time: pext[mask][i] packs the bits of i at the mask positions;
@@ -1914,6 +1954,20 @@ __device__ __forceinline__ double xtrace(const XMat<NB, CPLX>& M, int l) {
   return (readlane_d(v, 12) + readlane_d(v, 29)) + (readlane_d(v, 46) + readlane_d(v, 63));
 }
 
+// The same sum for a matrix in the FP32 layout (see XMat32), in double.
+template <int NB, bool CPLX>
+__device__ __forceinline__ double xtrace_f32(const XMat<NB, CPLX>& M, int l) {
+  double v = 0.0;
+#pragma unroll
+  for (int I = 0; I < NB; ++I)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (4 * (l >> 4) + r == (l & 15)) v += M.re[I][I][r];
+  v += dpp_mov<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v += dpp_mov<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  return (readlane_d(v, 0) + readlane_d(v, 20)) + (readlane_d(v, 40) + readlane_d(v, 60));
+}
+
 // FP32 estimate of the trace of an FP64-layout matrix, for the binary exponent of a rescaling
 // (the value only picks an exact power of two): the diagonal lanes as in xtrace, the sum in FP32.
 template <int NB, bool CPLX>
@@ -1978,8 +2032,8 @@ struct XDiag {
   }
 };
 
-// D = a I + b A + c A2 (+ d A3)
-template <int NB, bool CPLX, bool WITH3>
+// D = a I + b A + c A2 (+ d A3) (+ D)
+template <int NB, bool CPLX, bool WITH3, bool DIAG, bool ADD>
 __device__ __forceinline__ void xpoly(XMat<NB, CPLX>& D, double a, double b, double c, double d,
                                       const XMat<NB, CPLX>& A1, const XMat<NB, CPLX>& A2,
                                       const XMat<NB, CPLX>& A3, const XDiag<NB, CPLX>& dg) {
@@ -1989,12 +2043,14 @@ __device__ __forceinline__ void xpoly(XMat<NB, CPLX>& D, double a, double b, dou
     for (int J = 0; J < NB; ++J)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        double v = fma(c, A2.re[I][J][r], b * A1.re[I][J][r]);
+        double v = ADD ? fma(b, A1.re[I][J][r], D.re[I][J][r]) : b * A1.re[I][J][r];
+        v = fma(c, A2.re[I][J][r], v);
         if constexpr (WITH3) v = fma(d, A3.re[I][J][r], v);
-        if (I == J) v = dg.add(r, a, v);
+        if (DIAG && I == J) v = dg.add(r, a, v);
         D.re[I][J][r] = v;
         if constexpr (CPLX) {
-          double w = fma(c, A2.im[I][J][r], b * A1.im[I][J][r]);
+          double w = ADD ? fma(b, A1.im[I][J][r], D.im[I][J][r]) : b * A1.im[I][J][r];
+          w = fma(c, A2.im[I][J][r], w);
           if constexpr (WITH3) w = fma(d, A3.im[I][J][r], w);
           D.im[I][J][r] = w;
         }
@@ -2157,46 +2213,8 @@ __global__ __launch_bounds__(64) void k_cluster_expm(ClusterArgs<T> A) {
   for (int I = 0; I < NB; ++I)
 #pragma unroll
     for (int r = 0; r < 4; ++r) X.re[I][I][r] = dg.add(r, -mu, X.re[I][I][r]);
-  // The scale uses the induced 1-norm, an upper bound of the spectral radius: the largest column
-  // sum (theta is Hermitian, so it equals the largest row sum).  Column 16 J + l%16 of block
-  // column J is spread over the registers of the lanes l%16 + 16 g; two xor-shuffles complete it
-  // in every lane, a DPP row maximum then leaves the largest column sum in every lane.  (On these
-  // clusters it is at most the Frobenius norm, the other bound at hand, so that one is not
-  // formed; moduli of complex entries use the hardware square root, as nrm only chooses s.)
-  double rmax = 0.0;
-#pragma unroll
-  for (int J = 0; J < NB; ++J) {
-    double a = 0.0;
-#pragma unroll
-    for (int I = 0; I < NB; ++I)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if constexpr (CPLX) a += __builtin_amdgcn_sqrt(fma(X.re[I][J][r], X.re[I][J][r], X.im[I][J][r] * X.im[I][J][r]));
-        else a += fabs(X.re[I][J][r]);
-      }
-    a += __shfl_xor(a, 16, 64);
-    a += __shfl_xor(a, 32, 64);
-    rmax = fmax(rmax, a);
-  }
-  rmax = fmax(rmax, dpp_mov<0xB1>(rmax));    // quad_perm [1, 0, 3, 2]
-  rmax = fmax(rmax, dpp_mov<0x4E>(rmax));    // quad_perm [2, 3, 0, 1]
-  rmax = fmax(rmax, dpp_mov<0x141>(rmax));   // row_half_mirror
-  rmax = fmax(rmax, dpp_mov<0x140>(rmax));   // row_mirror
-  const double nrm = beta * rmax;
-  // s = the least s >= 0 with nrm <= 2^(s-1), at most 200 (0 for a NaN norm): from the binary
-  // exponent of nrm instead of a search
-  int s;
-  if (!(nrm > 0.5)) {
-    s = 0;
-  } else if (!(nrm <= 0x1p199)) {
-    s = 200;
-  } else {
-    int e;
-    const double m = frexp(nrm, &e);   // nrm = m 2^e, 0.5 <= m < 1
-    s = m == 0.5 ? e : e + 1;
-  }
-  s = __builtin_amdgcn_readfirstlane(s);   // every lane holds the same value; make it scalar
-  const double sc = -ldexp(beta, -s);
+  using EP = ExpPoly<T>;
+  const double sc = -EP::kappa * beta;
 #pragma unroll
   for (int I = 0; I < NB; ++I)
 #pragma unroll
@@ -2206,33 +2224,66 @@ __global__ __launch_bounds__(64) void k_cluster_expm(ClusterArgs<T> A) {
         X.re[I][J][r] *= sc;
         if constexpr (CPLX) X.im[I][J][r] *= sc;
       }
-  // ---- E0 = T_m(X): powers X^2, X^3 and a Horner recursion in X^3 ----
-  // m = 12 for double messages.  Float messages take m = 8 (one product fewer): for ||X|| <= 1/2
-  // the truncation is below 0.5^9 / 9! = 5.4e-9, a backward error on X under 0.2 u_32 relative,
-  // below what the FP32 squarings and the float rounding of the messages already put there.
-  constexpr double c0 = 1.0, c1 = 1.0, c2 = 1.0 / 2, c3 = 1.0 / 6, c4 = 1.0 / 24, c5 = 1.0 / 120,
-                   c6 = 1.0 / 720, c7 = 1.0 / 5040, c8 = 1.0 / 40320, c9 = 1.0 / 362880, c10 = 1.0 / 3628800,
-                   c11 = 1.0 / 39916800, c12 = 1.0 / 479001600;
-  constexpr bool kDeg8 = std::is_same<T, float>::value;
+  // The scale: the square root of the induced 1-norm of X^2, an upper bound of the spectral radius
+  // of X that is never above X's own 1-norm (||X^2||_1 <= ||X||_1^2) and costs nothing more, as the
+  // polynomial needs X^2 anyway; X and X^2 are then scaled by exact powers of two.  The 1-norm is the
+  // largest column sum (X^2 is Hermitian).  Column 16 J + l%16 of block column J is spread over the
+  // registers of the lanes l%16 + 16 g; two xor-shuffles complete it in every lane, a DPP row
+  // maximum then leaves the largest column sum in every lane.  (Moduli of complex entries and the
+  // root are the hardware square root's: the norm only chooses s.)
   xzero(P2);
   xmm(X, X, P2);
+  double rmax = 0.0;
+#pragma unroll
+  for (int J = 0; J < NB; ++J) {
+    double a = 0.0;
+#pragma unroll
+    for (int I = 0; I < NB; ++I)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if constexpr (CPLX) a += __builtin_amdgcn_sqrt(fma(P2.re[I][J][r], P2.re[I][J][r], P2.im[I][J][r] * P2.im[I][J][r]));
+        else a += fabs(P2.re[I][J][r]);
+      }
+    a += __shfl_xor(a, 16, 64);
+    a += __shfl_xor(a, 32, 64);
+    rmax = fmax(rmax, a);
+  }
+  rmax = fmax(rmax, dpp_mov<0xB1>(rmax));    // quad_perm [1, 0, 3, 2]
+  rmax = fmax(rmax, dpp_mov<0x4E>(rmax));    // quad_perm [2, 3, 0, 1]
+  rmax = fmax(rmax, dpp_mov<0x141>(rmax));   // row_half_mirror
+  rmax = fmax(rmax, dpp_mov<0x140>(rmax));   // row_mirror
+  // every lane holds the same value; make s scalar
+  const int s = __builtin_amdgcn_readfirstlane(expm_squarings<T>(__builtin_amdgcn_sqrt(rmax) * (1.0 / EP::kappa)));
+  {
+    const double f1 = ldexp(1.0, -s), f2 = ldexp(1.0, -2 * s);
+#pragma unroll
+    for (int I = 0; I < NB; ++I)
+#pragma unroll
+      for (int J = 0; J < NB; ++J)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          X.re[I][J][r] *= f1;
+          P2.re[I][J][r] *= f2;
+          if constexpr (CPLX) {
+            X.im[I][J][r] *= f1;
+            P2.im[I][J][r] *= f2;
+          }
+        }
+  }
+  // ---- E0 = p(X / kappa) (see ExpPoly) ----
   xzero(P3);
   xmm(X, P2, P3);
-  if constexpr (kDeg8) xpoly<NB, CPLX, false>(M, c6, c7, c8, 0.0, X, P2, P3, dg);    // B2
-  else xpoly<NB, CPLX, true>(M, c9, c10, c11, c12, X, P2, P3, dg);                  // B3
+  M = P3;
+  xpoly<NB, CPLX, false, false, true>(M, 0.0, EP::b1, EP::b2, 0.0, X, P2, P3, dg);
   {
     XMat<NB, CPLX> B;
-    if constexpr (!kDeg8) {
-      xpoly<NB, CPLX, false>(B, c6, c7, c8, 0.0, X, P2, P3, dg);   // B2 + X^3 B3
-      xmm(P3, M, B);
-      M = B;
-    }
-    xpoly<NB, CPLX, false>(B, c3, c4, c5, 0.0, X, P2, P3, dg);   // B1 + X^3 (...)
-    xmm(P3, M, B);
+    xpoly<NB, CPLX, true, false, false>(B, 0.0, EP::r1, EP::r2, EP::r3, X, P2, P3, dg);
+    xmm(M, M, B);   // a6
     M = B;
-    xpoly<NB, CPLX, false>(B, c0, c1, c2, 0.0, X, P2, P3, dg);   // B0 + X^3 (...)
-    xmm(P3, M, B);
-    M = B;
+    xpoly<NB, CPLX, true, true, true>(M, EP::s0, EP::s1, EP::s2, EP::s3, X, P2, P3, dg);
+    xpoly<NB, CPLX, false, true, false>(X, 1.0, EP::t1, EP::t2, 0.0, X, P2, P3, dg);
+    xmm(M, B, X);
+    M = X;
   }
   // ---- normalise and square s times ----
   // Every rescaling is by an exact power of two 2^-e_j, e_j the binary exponent of the trace
@@ -2262,13 +2313,12 @@ __global__ __launch_bounds__(64) void k_cluster_expm(ClusterArgs<T> A) {
           if constexpr (CPLX) M.im[I][J][r] *= sc0;
         }
   }
-  // Float messages: the squarings after the first kF64Squarings (up to and including the
-  // rescaling at j = 3) run on the FP32 matrix cores.  A relative rounding error e in Y_j acts on rho
-  // like an error of about 2^(s-j) e in X = beta (theta - mu), and 2^s is about 2 ||X||, so for
-  // j >= 4 the float squarings perturb X by at most about ||X|| u_32 / 8 times the product's error
-  // growth, the order of what the float rounding of the messages themselves puts on X
-  // (beta ||nu|| u_32).  The polynomial and the first squarings, where the error would be
-  // amplified most, stay in FP64.
+  // Float messages: the squarings after the first kF64Squarings run on the FP32 matrix cores.  A
+  // relative rounding error e in Y_j acts on rho like an error of about 2^(s-j) e in
+  // X = beta (theta - mu); ||X|| is between kMax/2 and kMax (2.4) times 2^s, so after two squarings
+  // the float ones perturb X by at most about ||X|| u_32 / 5 times the product's error growth, the
+  // order of what the float rounding of the messages themselves puts on X (beta ||nu|| u_32).  The
+  // polynomial and the first squarings, where the error would be amplified most, stay in FP64.
   int n64 = s;
   if constexpr (std::is_same<T, float>::value) n64 = s < kF64Squarings ? s : kF64Squarings;
   auto post = [&](XMat<NB, CPLX>& Y, int j) {
@@ -2301,29 +2351,18 @@ __global__ __launch_bounds__(64) void k_cluster_expm(ClusterArgs<T> A) {
     }
   }
   if (n64 < s) {
-    // to the FP32 layout through LDS, squarings n64 .. s-1, and back
+    // Squarings n64 .. s-1.  The first takes its operands straight from the FP64 registers: there
+    // lane group g, register kk holds row 4 kk + g, which serves as well as row 4 g + kk as the k
+    // index of a step, since both operands use the same one; its result is in the FP32 layout.
     XMat32<NB, CPLX> Ya, Yb;
-    __syncthreads();
 #pragma unroll
     for (int I = 0; I < NB; ++I)
 #pragma unroll
       for (int J = 0; J < NB; ++J)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int o = (16 * I + 4 * r + (l >> 4)) * LD + 16 * J + (l & 15);
-          sar[o] = (T)M.re[I][J][r];
-          if constexpr (CPLX) sai[o] = (T)M.im[I][J][r];
-        }
-    __syncthreads();
-#pragma unroll
-    for (int I = 0; I < NB; ++I)
-#pragma unroll
-      for (int J = 0; J < NB; ++J)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int o = (16 * I + 4 * (l >> 4) + r) * LD + 16 * J + (l & 15);
-          Ya.re[I][J][r] = (float)sar[o];
-          if constexpr (CPLX) Ya.im[I][J][r] = (float)sai[o];
+          Ya.re[I][J][r] = (float)M.re[I][J][r];
+          if constexpr (CPLX) Ya.im[I][J][r] = (float)M.im[I][J][r];
         }
     auto post32 = [&](XMat32<NB, CPLX>& Y, int j) {
       if ((j & 3) == 3) {
@@ -2370,33 +2409,23 @@ __global__ __launch_bounds__(64) void k_cluster_expm(ClusterArgs<T> A) {
         Ya = Yb;
       }
     }
-    __syncthreads();
 #pragma unroll
     for (int I = 0; I < NB; ++I)
 #pragma unroll
       for (int J = 0; J < NB; ++J)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int o = (16 * I + 4 * (l >> 4) + r) * LD + 16 * J + (l & 15);
-          sar[o] = (T)Ya.re[I][J][r];
-          if constexpr (CPLX) sai[o] = (T)Ya.im[I][J][r];
-        }
-    __syncthreads();
-#pragma unroll
-    for (int I = 0; I < NB; ++I)
-#pragma unroll
-      for (int J = 0; J < NB; ++J)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int o = (16 * I + 4 * r + (l >> 4)) * LD + 16 * J + (l & 15);
-          M.re[I][J][r] = (double)sar[o];
-          if constexpr (CPLX) M.im[I][J][r] = (double)sai[o];
+          M.re[I][J][r] = (double)Ya.re[I][J][r];
+          if constexpr (CPLX) M.im[I][J][r] = (double)Ya.im[I][J][r];
         }
   }
+  // row of register r of a diagonal block: the FP64 layout, or the FP32 one after float squarings
+  const bool tail32 = n64 < s;
+  const auto row = [&](int r) { return tail32 ? 4 * (l >> 4) + r : 4 * r + (l >> 4); };
   double L;
   {
     E = ldexp(E, s - 1 - jr);   // the exponent after the last squaring
-    const double tf = xtrace(M, l);
+    const double tf = tail32 ? xtrace_f32(M, l) : xtrace(M, l);
     double kf;
     const double lm = log_split(tf, kf);
     L = fma(E + kf, 0.69314718055994530942, lm);   // E + kf is exact
@@ -2428,7 +2457,7 @@ __global__ __launch_bounds__(64) void k_cluster_expm(ClusterArgs<T> A) {
     for (int J = 0; J < NB; ++J)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int o = (16 * I + 4 * r + (l >> 4)) * LD + 16 * J + (l & 15);
+        const int o = (16 * I + row(r)) * LD + 16 * J + (l & 15);
         sar[o] = (T)M.re[I][J][r];
         if constexpr (CPLX) sai[o] = (T)M.im[I][J][r];
       }
@@ -2446,7 +2475,7 @@ __global__ __launch_bounds__(64) void k_cluster_expm(ClusterArgs<T> A) {
       for (int J = 0; J < NB; ++J)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int i = 16 * I + 4 * r + (l >> 4), j = 16 * J + (l & 15);
+          const int i = 16 * I + row(r), j = 16 * J + (l & 15);
           if (i > j) continue;
           const int kr = tri_index(i, j, DE);
           const T vr = (T)M.re[I][J][r];
@@ -2775,7 +2804,7 @@ __global__ __launch_bounds__(256) void k_cluster_expm_wg(ClusterArgs<T> A, doubl
     // and X^3, which the polynomial no longer needs; see k_cluster_expm)
     double t = block_sum(trp, red);
     double L = log(t);
-    const int n64 = std::is_same<T, float>::value ? (s < kF64Squarings ? s : kF64Squarings) : s;
+    const int n64 = std::is_same<T, float>::value ? (s < 4 ? s : 4) : s;
     for (int j = 0; j < n64; ++j) {
       trp = gmm<CPLX, DE>(Mr, Mi, Mr, Mi, Br, Bi, 1.0 / (t * t), zero, tid);
       __syncthreads();
