@@ -2514,328 +2514,502 @@ __global__ __launch_bounds__(64) void k_cluster_expm(ClusterArgs<T> A) {
   }
 }
 
-// Workgroup variant for De = 32 (complex), 64, 128, 256: five matrices (X, X^2, X^3 and two Horner / squaring
-// buffers) in a per-workgroup FP64 slab, row-major, real plane then imaginary plane; four
-// waves, each computing 32 x 32 output tiles (2 x 2 blocks of the 16 x 16 MFMA; 16 x 16 below De = 128).  The A operand
-// of block (I, K) is read as the conjugate of block (K, I), which keeps both operand reads as
-// rows of 16 consecutive doubles.
-struct GInit {
-  double a, b, c;             // C = a I + b X + c P + scale * (A B)
-  const double* xr; const double* xi;
-  const double* pr; const double* pi;
+// Workgroup variant for De = 32, 64, 128, 256: five matrices in a per-workgroup slab, row-major, real
+// plane then imaginary plane.  Only the 16 x 16 blocks on and above the diagonal of a product are
+// computed (every product here is a polynomial in one Hermitian matrix), an off-diagonal block is
+// also written conjugate-transposed.  The A operand of block (I, K) is read as the conjugate of
+// block (K, I), so both operands of a k-step come from the same rows of the matrix: KS whole rows
+// at a time go to LDS (global_load_lds, two buffers, one barrier per step), where every wave reads
+// the fragments of its blocks.  A staged row thus serves all blocks of the pass; reading fragments
+// from the slab instead (32 x 32 tiles per wave, no LDS) moved 10 MB per 256 x 256 product through
+// the last-level cache and HBM, which at 5 TB/s was the bound (MFMA 40 % busy), now 4 MB.
+//
+// A complex product takes three real ones (R1 R2, N1 N2, (R1 + N1)(R2 + N2)) instead of four.
+//
+// Blocks of a product and the waves that compute them: `passes` sweeps over the rows, in each of
+// which a wave holds the accumulators of `nblk` blocks (ab[b], bb[b] index its A and B fragments).
+template <int DE>
+struct WgPlan;
+template <>
+struct WgPlan<256> {   // 36 tiles of 2 x 2 blocks: three per wave, three waves per SIMD
+  static constexpr int waves = 12, passes = 3, na = 2, nb = 2, nblk = 4, ks = 16;
+  static constexpr int ab[4] = {0, 0, 1, 1}, bb[4] = {0, 1, 0, 1};
+};
+template <>
+struct WgPlan<128> {   // 36 blocks, three per wave: rows in runs of three, the rest as two and one
+  static constexpr int waves = 12, passes = 1, na = 2, nb = 3, nblk = 3, ks = 32;
+  static constexpr int ab[3] = {0, 0, 1}, bb[3] = {0, 1, 2};
+};
+template <>
+struct WgPlan<64> {    // 10 blocks, two per wave
+  static constexpr int waves = 5, passes = 1, na = 2, nb = 2, nblk = 2, ks = 16;
+  static constexpr int ab[2] = {0, 1}, bb[2] = {0, 1};
+};
+template <>
+struct WgPlan<32> {    // 3 blocks, one per wave
+  static constexpr int waves = 3, passes = 1, na = 1, nb = 1, nblk = 1, ks = 8;
+  static constexpr int ab[1] = {0}, bb[1] = {0};
+};
+// A rows then B columns (in blocks) of every (pass, wave)
+struct WgBlocks {
+  unsigned char t256[36][4], t128[12][5], t64[5][4], t32[3][2];
+};
+constexpr WgBlocks make_wg_blocks() {
+  WgBlocks w{};
+  int t = 0;
+  for (int i = 0; i < 8; ++i)
+    for (int j = i; j < 8; ++j, ++t) {
+      w.t256[t][0] = (unsigned char)(2 * i);
+      w.t256[t][1] = (unsigned char)(2 * i + 1);
+      w.t256[t][2] = (unsigned char)(2 * j);
+      w.t256[t][3] = (unsigned char)(2 * j + 1);
+    }
+  constexpr unsigned char g128[12][5] = {{0, 0, 0, 1, 2}, {0, 0, 3, 4, 5}, {1, 1, 1, 2, 3}, {1, 1, 4, 5, 6},
+                                         {2, 2, 2, 3, 4}, {2, 2, 5, 6, 7}, {3, 3, 3, 4, 5}, {4, 4, 4, 5, 6},
+                                         {5, 5, 5, 6, 7}, {0, 1, 6, 7, 7}, {3, 4, 6, 7, 7}, {6, 7, 6, 7, 7}};
+  constexpr unsigned char g64[5][4] = {{0, 0, 0, 1}, {0, 0, 2, 3}, {1, 1, 1, 2}, {1, 3, 3, 3}, {2, 2, 2, 3}};
+  constexpr unsigned char g32[3][2] = {{0, 0}, {0, 1}, {1, 1}};
+  for (int i = 0; i < 12; ++i)
+    for (int k = 0; k < 5; ++k) w.t128[i][k] = g128[i][k];
+  for (int i = 0; i < 5; ++i)
+    for (int k = 0; k < 4; ++k) w.t64[i][k] = g64[i][k];
+  for (int i = 0; i < 3; ++i)
+    for (int k = 0; k < 2; ++k) w.t32[i][k] = g32[i][k];
+  return w;
+}
+static __constant__ WgBlocks kWgBlocks = make_wg_blocks();
+template <int DE>
+__device__ __forceinline__ int wg_block(int t, int k) {
+  if constexpr (DE == 256) return kWgBlocks.t256[t][k];
+  else if constexpr (DE == 128) return kWgBlocks.t128[t][k];
+  else if constexpr (DE == 64) return kWgBlocks.t64[t][k];
+  else return kWgBlocks.t32[t][k];
+}
+template <bool CPLX, int DE>
+constexpr int wg_stage_bytes() { return WgPlan<DE>::ks * DE * (CPLX ? 2 : 1) * (int)sizeof(double); }
+
+template <typename S>
+struct WgMfma;
+template <>
+struct WgMfma<double> {
+  typedef mfma_f64x4 acc;
+  static __device__ __forceinline__ acc mma(double a, double b, acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int l, int r) { return 4 * r + (l >> 4); }
+};
+template <>
+struct WgMfma<float> {
+  typedef mfma_f32x4 acc;
+  static __device__ __forceinline__ acc mma(float a, float b, acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int l, int r) { return 4 * (l >> 4) + r; }
 };
 
-template <bool CPLX, int DE>
-__device__ double gmm(const double* xr, const double* xi, const double* yr, const double* yi, double* cr_,
-                      double* ci_, double scale, const GInit& in, int tid) {
-  constexpr int TB = DE >= 128 ? 2 : 1;   // output tile of TB x TB blocks per wave
-  constexpr int NB = DE / 16, NT = NB / TB;
-  const int wave = tid / 64, l = tid % 64;
-  const int lr = l >> 4, lc = l & 15;
-  double tr = 0.0;
-  // C is Hermitian (every product here is a polynomial in one matrix): only the tiles on and
-  // above the diagonal are computed, an off-diagonal tile is also written conjugate-transposed
-  for (int t = wave; t < NT * (NT + 1) / 2; t += 4) {
-    int TI = 0, TJ = t;
-    while (TJ >= NT - TI) {
-      TJ -= NT - TI;
-      ++TI;
-    }
-    TJ += TI;
-    mfma_f64x4 accr[TB][TB], acci[TB][TB];
-#pragma unroll
-    for (int ii = 0; ii < TB; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < TB; ++jj) {
-        accr[ii][jj] = mfma_f64x4{0.0, 0.0, 0.0, 0.0};
-        acci[ii][jj] = mfma_f64x4{0.0, 0.0, 0.0, 0.0};
-      }
-    // operand fragments of one K step (four k-sub-steps); with 16 x 16 tiles they are loaded one
-    // step ahead of the products that use them, so the L2 latency overlaps the matrix-core work
-    constexpr int NP = CPLX ? 2 : 1;
-    double fa[2][4][TB][NP], fb[2][4][TB][NP];
-    auto load_step = [&](int K, double (&ga)[4][TB][NP], double (&gb)[4][TB][NP]) {
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const int64_t row = (int64_t)(16 * K + 4 * kk + lr) * DE;
-#pragma unroll
-        for (int q = 0; q < TB; ++q) {
-          const int ca = 16 * (TB * TI + q) + lc, cb = 16 * (TB * TJ + q) + lc;
-          ga[kk][q][0] = xr[row + ca];
-          gb[kk][q][0] = yr[row + cb];
-          if constexpr (CPLX) {
-            ga[kk][q][1] = xi[row + ca];
-            gb[kk][q][1] = yi[row + cb];
-          }
-        }
-      }
-    };
-    auto mma_step = [&](const double (&ga)[4][TB][NP], const double (&gb)[4][TB][NP]) {
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-        for (int ii = 0; ii < TB; ++ii)
-#pragma unroll
-          for (int jj = 0; jj < TB; ++jj) {
-            accr[ii][jj] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[kk][ii][0], gb[kk][jj][0], accr[ii][jj], 0, 0, 0);
-            if constexpr (CPLX) {
-              accr[ii][jj] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[kk][ii][1], gb[kk][jj][1], accr[ii][jj], 0, 0, 0);
-              acci[ii][jj] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[kk][ii][0], gb[kk][jj][1], acci[ii][jj], 0, 0, 0);
-              acci[ii][jj] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ga[kk][ii][1], gb[kk][jj][0], acci[ii][jj], 0, 0, 0);
-            }
-          }
-    };
-    if constexpr (TB == 1) {   // 16 x 16 tiles: latency-bound, registers to spare
-      load_step(0, fa[0], fb[0]);
-#pragma unroll 1
-      for (int K = 0; K < NB; K += 2) {
-        if (K + 1 < NB) load_step(K + 1, fa[1], fb[1]);
-        mma_step(fa[0], fb[0]);
-        if (K + 1 < NB) {
-          if (K + 2 < NB) load_step(K + 2, fa[0], fb[0]);
-          mma_step(fa[1], fb[1]);
-        }
-      }
-    } else {
-      // 32 x 32 tiles: one K step at a time.  Its 32 loads in flight together hide the latency
-      // better than a ring of k-sub-step fragments loaded two or three k-sub-steps ahead (30 %
-      // slower at D = 128 and 256), and a second K-step buffer costs the second wave per SIMD.
-#pragma unroll 1
-      for (int K = 0; K < NB; ++K) {
-        load_step(K, fa[0], fb[0]);
-        mma_step(fa[0], fb[0]);
-      }
-    }
-#pragma unroll
-    for (int ii = 0; ii < TB; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < TB; ++jj)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = 16 * (TB * TI + ii) + 4 * r + lr, j = 16 * (TB * TJ + jj) + lc;
-          const int64_t o = (int64_t)i * DE + j;
-          double vr = scale * accr[ii][jj][r];
-          if (in.b != 0.0) vr = fma(in.b, in.xr[o], vr);
-          if (in.c != 0.0) vr = fma(in.c, in.pr[o], vr);
-          if (i == j) {
-            vr += in.a;
-            tr += vr;
-          }
-          cr_[o] = vr;
-          const int64_t ot = (int64_t)j * DE + i;
-          if (TI != TJ) cr_[ot] = vr;
-          if constexpr (CPLX) {
-            double vi = scale * acci[ii][jj][r];
-            if (in.b != 0.0) vi = fma(in.b, in.xi[o], vi);
-            if (in.c != 0.0) vi = fma(in.c, in.pi[o], vi);
-            ci_[o] = (i == j) ? 0.0 : vi;
-            if (TI != TJ) ci_[ot] = -vi;
-          }
-        }
-  }
-  return tr;
+// Bank swizzle of a staged row k: the four rows that one fragment read touches would start on the
+// same bank; row k holds its blocks of 16 elements permuted by block ^ wg_swizzle(k), which depends
+// on the low bits of k only (those of l / 16 for a reading lane).
+template <typename S, int DE>
+__device__ __forceinline__ int wg_swizzle(int k) {
+  return sizeof(S) == 8 ? (k & 1) : (DE >= 64 ? (k & 3) : ((k >> 1) & 1));
 }
 
-// C = scale (Y Y) for Hermitian Y in FP32 (the float-message path's later squarings): gmm's tiling
-// and operand reads on FP32 slabs with v_mfma_f32_16x16x4_f32, whose operands are laid out like
-// the FP64 instruction's and whose result register r of lane l holds row 4 (l/16) + r.  Returns
-// this thread's share of the trace.
-template <bool CPLX, int DE>
-__device__ double gsq32(const float* yr, const float* yi, float* cr_, float* ci_, float scale, int tid) {
-  constexpr int TB = DE >= 128 ? 2 : 1;
-  constexpr int NB = DE / 16, NT = NB / TB;
-  constexpr int NP = CPLX ? 2 : 1;
-  const int wave = tid / 64, l = tid % 64;
-  const int lr = l >> 4, lc = l & 15;
-  double tr = 0.0;
-  for (int t = wave; t < NT * (NT + 1) / 2; t += 4) {
-    int TI = 0, TJ = t;
-    while (TJ >= NT - TI) {
-      TJ -= NT - TI;
-      ++TI;
-    }
-    TJ += TI;
-    mfma_f32x4 accr[TB][TB], acci[TB][TB];
-#pragma unroll
-    for (int ii = 0; ii < TB; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < TB; ++jj) {
-        accr[ii][jj] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
-        acci[ii][jj] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-#pragma unroll 1
-    for (int K = 0; K < NB; ++K) {
-      float ga[4][TB][NP], gb[4][TB][NP];
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const int64_t row = (int64_t)(16 * K + 4 * kk + lr) * DE;
-#pragma unroll
-        for (int q = 0; q < TB; ++q) {
-          const int ca = 16 * (TB * TI + q) + lc, cb = 16 * (TB * TJ + q) + lc;
-          ga[kk][q][0] = yr[row + ca];
-          gb[kk][q][0] = yr[row + cb];
-          if constexpr (CPLX) {
-            ga[kk][q][1] = yi[row + ca];
-            gb[kk][q][1] = yi[row + cb];
-          }
-        }
-      }
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-        for (int ii = 0; ii < TB; ++ii)
-#pragma unroll
-          for (int jj = 0; jj < TB; ++jj) {
-            accr[ii][jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[kk][ii][0], gb[kk][jj][0], accr[ii][jj], 0, 0, 0);
-            if constexpr (CPLX) {
-              accr[ii][jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[kk][ii][1], gb[kk][jj][1], accr[ii][jj], 0, 0, 0);
-              acci[ii][jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[kk][ii][0], gb[kk][jj][1], acci[ii][jj], 0, 0, 0);
-              acci[ii][jj] = __builtin_amdgcn_mfma_f32_16x16x4f32(-ga[kk][ii][1], gb[kk][jj][0], acci[ii][jj], 0, 0, 0);
-            }
-          }
-    }
-#pragma unroll
-    for (int ii = 0; ii < TB; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < TB; ++jj)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int i = 16 * (TB * TI + ii) + 4 * lr + r, j = 16 * (TB * TJ + jj) + lc;
-          const int64_t o = (int64_t)i * DE + j;
-          const float vr = scale * accr[ii][jj][r];
-          if (i == j) tr += vr;
-          cr_[o] = vr;
-          const int64_t ot = (int64_t)j * DE + i;
-          if (TI != TJ) cr_[ot] = vr;
-          if constexpr (CPLX) {
-            const float vi = scale * acci[ii][jj][r];
-            ci_[o] = (i == j) ? 0.f : vi;
-            if (TI != TJ) ci_[ot] = -vi;
-          }
-        }
+// Sizes of a stage: KS rows of every plane of X (and of Y unless SAME).  A float stage holds twice
+// the rows of a double one, two matrices' stage half of them.
+template <typename S, bool CPLX, int DE, bool SAME>
+struct WgStage {
+  using P = WgPlan<DE>;
+  static constexpr int NPL = CPLX ? 2 : 1;
+  static constexpr int KS0 = P::ks * (int)(sizeof(double) / sizeof(S)) / (SAME ? 1 : 2);
+  static constexpr int KS = KS0 < DE ? KS0 : DE;
+  static constexpr int NK = DE / KS;
+  static constexpr int NROW = KS * NPL * (SAME ? 1 : 2);
+  static constexpr int CPR = DE * (int)sizeof(S) / 16;   // 16-byte chunks per row
+  static constexpr int NINS = NROW * CPR / 64;           // wave loads per stage
+  static_assert(NINS * 64 == NROW * CPR && KS % 4 == 0 && NK * KS == DE, "whole wave loads and stages");
+  static_assert(NROW * DE * (int)sizeof(S) <= wg_stage_bytes<CPLX, DE>(), "stage fits its buffer");
+};
+
+// Rows k0 .. k0 + KS - 1 to the buffer, by LDS-direct loads spread over the waves.
+template <typename S, bool CPLX, int DE, bool SAME>
+__device__ __forceinline__ void wg_fill(const S* X, const S* Y, int k0, unsigned char* buf, int wave, int l) {
+  using G = WgStage<S, CPLX, DE, SAME>;
+  constexpr int64_t DD = (int64_t)DE * DE;
+#pragma unroll 2
+  for (int q = wave; q < G::NINS; q += G::P::waves) {
+    const int ch = q * 64 + l;
+    const int row = ch / G::CPR, cp = ch % G::CPR;
+    const int k = row % G::KS, pl = row / G::KS;                           // pl: matrix * NPL + plane
+    const int cg = cp ^ (wg_swizzle<S, DE>(k) * (int)sizeof(S));          // sizeof(S) chunks per block
+    const S* src = (SAME || pl < G::NPL ? X : Y - G::NPL * DD) + pl * DD + (int64_t)(k0 + k) * DE +
+                   cg * (16 / (int)sizeof(S));
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)(buf + q * 1024), 16, 0, 0);
   }
-  return tr;
+}
+
+// Accumulators of a wave's blocks
+template <typename S, bool CPLX, int DE>
+struct WgAcc {
+  static constexpr int N = WgPlan<DE>::nblk;
+  typename WgMfma<S>::acc p1[N], p2[CPLX ? N : 1], p3[CPLX ? N : 1];
+};
+
+// One stage: the next one's loads are issued into `nxt` (k0 >= 0), then the products of the rows in
+// `st` are accumulated.  The two are different buffers: `restrict` tells the compiler so, which
+// would otherwise wait for the loads before the first read.
+template <typename S, bool CPLX, int DE, bool SAME>
+__device__ __forceinline__ void wg_step(const S* __restrict__ st, unsigned char* __restrict__ nxt, const S* X, const S* Y,
+                                        int k0, int wave, int l, const int (&oa)[WgPlan<DE>::na],
+                                        const int (&ob)[WgPlan<DE>::nb], WgAcc<S, CPLX, DE>& acc) {
+  using P = WgPlan<DE>;
+  using F = WgMfma<S>;
+  using G = WgStage<S, CPLX, DE, SAME>;
+  if (k0 >= 0) wg_fill<S, CPLX, DE, SAME>(X, Y, k0, nxt, wave, l);
+#pragma unroll 4
+  for (int kk = 0; kk < G::KS / 4; ++kk) {
+    S ar[P::na], an[P::na], br[P::nb], bn[P::nb];
+#pragma unroll
+    for (int q = 0; q < P::na; ++q) {
+      ar[q] = st[oa[q] + kk * 4 * DE];
+      if constexpr (CPLX) an[q] = st[oa[q] + kk * 4 * DE + G::KS * DE];
+    }
+#pragma unroll
+    for (int q = 0; q < P::nb; ++q) {
+      br[q] = st[ob[q] + kk * 4 * DE];
+      if constexpr (CPLX) bn[q] = st[ob[q] + kk * 4 * DE + G::KS * DE];
+    }
+#pragma unroll
+    for (int b = 0; b < P::nblk; ++b) {
+      acc.p1[b] = F::mma(ar[P::ab[b]], br[P::bb[b]], acc.p1[b]);
+      if constexpr (CPLX) {
+        // the A operands are transposes: N^T = -N, (R - N)^T = R + N
+        acc.p2[b] = F::mma(an[P::ab[b]], bn[P::bb[b]], acc.p2[b]);   // -N1 N2
+        acc.p3[b] = F::mma(ar[P::ab[b]] - an[P::ab[b]], br[P::bb[b]] + bn[P::bb[b]], acc.p3[b]);
+      }
+    }
+  }
+}
+
+// epi(I, J, re, im): the accumulated block (I, J) of X Y (SAME: Y is X), for every block of the plan
+// (a 2 x 2 tile on the diagonal also computes its block below it: I > J, to be skipped).
+// X, Y: slab matrices (real plane, then imaginary).  s0, s1: buffers of wg_stage_bytes().
+// All waves call it, after a barrier that follows the writes of X and Y; it ends with one itself.
+template <typename S, bool CPLX, int DE, bool SAME, typename Epi>
+__device__ __forceinline__ void wg_product(const S* X, const S* Y, unsigned char* s0, unsigned char* s1, int tid,
+                                           Epi&& epi) {
+  using P = WgPlan<DE>;
+  using F = WgMfma<S>;
+  using G = WgStage<S, CPLX, DE, SAME>;
+  static_assert(G::NK % 2 == 0, "stages alternate between the buffers");
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64;
+  const int lr = l >> 4, lc = l & 15;
+  wg_fill<S, CPLX, DE, SAME>(X, Y, 0, s0, wave, l);
+#pragma unroll 1
+  for (int pass = 0; pass < P::passes; ++pass) {
+    const int t = pass * P::waves + wave;
+    int ia[P::na], jb[P::nb], oa[P::na], ob[P::nb];
+#pragma unroll
+    for (int q = 0; q < P::na; ++q) {
+      ia[q] = wg_block<DE>(t, q);
+      oa[q] = lr * DE + 16 * (ia[q] ^ wg_swizzle<S, DE>(lr)) + lc;
+    }
+#pragma unroll
+    for (int q = 0; q < P::nb; ++q) {
+      jb[q] = wg_block<DE>(t, P::na + q);
+      ob[q] = lr * DE + 16 * (jb[q] ^ wg_swizzle<S, DE>(lr)) + lc + (SAME ? 0 : G::NPL * G::KS * DE);
+    }
+    WgAcc<S, CPLX, DE> acc;
+#pragma unroll
+    for (int b = 0; b < P::nblk; ++b) {
+      acc.p1[b] = typename F::acc{0, 0, 0, 0};
+      if constexpr (CPLX) acc.p2[b] = acc.p3[b] = typename F::acc{0, 0, 0, 0};
+    }
+#pragma unroll 1
+    for (int K = 0; K < G::NK; K += 2) {
+      __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's loads of the stage have landed
+      __syncthreads();                      // and every wave's; the other buffer is no longer read
+      wg_step<S, CPLX, DE, SAME>(reinterpret_cast<const S*>(s0), s1, X, Y, (K + 1) * G::KS, wave, l, oa, ob, acc);
+      __builtin_amdgcn_s_waitcnt(0x0f70);
+      __syncthreads();
+      const int k0 = K + 2 < G::NK ? (K + 2) * G::KS : (pass + 1 < P::passes ? 0 : -1);
+      wg_step<S, CPLX, DE, SAME>(reinterpret_cast<const S*>(s1), s0, X, Y, k0, wave, l, oa, ob, acc);
+    }
+#pragma unroll
+    for (int b = 0; b < P::nblk; ++b) {
+      const int I = ia[P::ab[b]], J = jb[P::bb[b]];
+      if constexpr (CPLX) epi(I, J, acc.p1[b] + acc.p2[b], acc.p3[b] - acc.p1[b] + acc.p2[b]);
+      else epi(I, J, acc.p1[b], acc.p1[b]);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // the epilogues' stores, before anyone stages them
+  __syncthreads();
+}
+
+// Block (I, J), I <= J, of a Hermitian result (vr, vi) to the slab matrix C, and its conjugate
+// transpose to (J, I).
+template <typename D, typename S, bool CPLX, int DE>
+__device__ __forceinline__ void wg_store(D* C, int I, int J, int l, const S (&vr)[4], const S (&vi)[4]) {
+  constexpr int64_t DD = (int64_t)DE * DE;
+  const int j = 16 * J + (l & 15);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int i = 16 * I + WgMfma<S>::row(l, r);
+    C[i * DE + j] = (D)vr[r];
+    if constexpr (CPLX) C[DD + i * DE + j] = (i == j) ? D(0) : (D)vi[r];
+    if (I != J) {
+      C[j * DE + i] = (D)vr[r];
+      if constexpr (CPLX) C[DD + j * DE + i] = -(D)vi[r];
+    }
+  }
+}
+
+// theta_e of a cluster times sc (after subtracting mu on the diagonal) into the slab matrix X: one
+// row per wave, the lanes along it, only j >= i (the rest by symmetry).  With mu == nullptr only
+// the diagonal is formed and its sum returned (this thread's share).
+template <typename T, bool CPLX, int DE>
+__device__ double wg_assemble(const ClusterArgs<T>& A, int64_t c, double* X, T th, double sc, const double* mu, int tid,
+                              int nth) {
+  constexpr int64_t DD = (int64_t)DE * DE;
+  constexpr int NB = log2i(DE);
+  const int64_t ho = A.hoff[c];
+  if (mu == nullptr) {
+    double tr = 0.0;
+    for (int i = tid; i < DE; i += nth) {
+      T vr, vi;
+      theta_elem<T, CPLX>(A, c, DE, NB, ho, i, i, th, vr, vi);
+      tr += (double)vr;
+    }
+    return tr;
+  }
+  const int wave = tid / 64, l = tid % 64;
+  for (int i = wave; i < DE; i += nth / 64)
+    for (int j = i + l; j < DE; j += 64) {
+      T vr, vi;
+      theta_elem<T, CPLX>(A, c, DE, NB, ho, i, j, th, vr, vi);
+      const double xr = sc * (i == j ? (double)vr - *mu : (double)vr);
+      X[i * DE + j] = xr;
+      X[j * DE + i] = xr;
+      if constexpr (CPLX) {
+        const double xi = i == j ? 0.0 : sc * (double)vi;
+        X[DD + i * DE + j] = xi;
+        X[DD + j * DE + i] = -xi;
+      }
+    }
+  return 0.0;
+}
+
+// Outputs of a cluster whose marginal scale * Y sits in a slab matrix: own marginal slot, per-cluster
+// marginal, partial traces onto every child.  One row of the packed upper triangle per wave at a
+// time, the lanes along it.
+template <typename T, typename S, bool CPLX, int DE>
+__device__ void wg_outputs(const ClusterArgs<T>& A, int64_t c, int32_t gid, const S* Y, double scale, int tid, int nth) {
+  constexpr int64_t DD = (int64_t)DE * DE;
+  constexpr int NB = log2i(DE);
+  const int wave = tid / 64, l = tid % 64, nw = nth / 64;
+  const int Dc = A.Dc;
+  const int64_t rs_self = A.rslot ? A.rslot[c] : -1;
+  if ((rs_self >= 0 && A.R) || A.marg) {
+    T* mg = A.marg ? A.marg + A.marg_off[gid] : nullptr;
+    for (int i = wave; i < DE; i += nw)
+      for (int j = i + l; j < DE; j += 64) {
+        const int kr = tri_index(i, j, DE);
+        const T vr = (T)(scale * (double)Y[i * DE + j]);
+        if (rs_self >= 0 && A.R) A.R[(int64_t)kr * A.S + rs_self] = vr;
+        if (mg) mg[kr] = vr;
+        if constexpr (CPLX) {
+          if (i < j) {
+            const int ki = DE * (DE + 1) / 2 + stri_index(i, j, DE);
+            const T vi = (T)(scale * (double)Y[DD + i * DE + j]);
+            if (rs_self >= 0 && A.R) A.R[(int64_t)ki * A.S + rs_self] = vi;
+            if (mg) mg[ki] = vi;
+          }
+        }
+      }
+  }
+  if (!A.Tout || Dc <= 0) return;
+  const int NR = DE / Dc;
+  for (int s = 0; s < A.maxch; ++s) {
+    const int m = A.ch[(int64_t)s * A.n + c];
+    if (m < 0) continue;
+    const int mask = A.chmask[(int64_t)s * A.n + c];
+    for (int a = wave; a < Dc; a += nw)
+      for (int b = a + l; b < Dc; b += 64) {
+        const int i0 = pdep_rt(a, 0, mask, NB), j0 = pdep_rt(b, 0, mask, NB);
+        double sr = 0.0, si = 0.0;
+        for (int x = 0; x < NR; ++x) {
+          const int y = pdep_rt(0, x, mask, NB);
+          const int o = (i0 | y) * DE + (j0 | y);
+          sr += (double)Y[o];
+          if constexpr (CPLX) si += (double)Y[DD + o];
+        }
+        A.Tout[(int64_t)tri_index(a, b, Dc) * A.Mc + m] = (T)(scale * sr);
+        if constexpr (CPLX) {
+          if (a < b) A.Tout[(int64_t)(Dc * (Dc + 1) / 2 + stri_index(a, b, Dc)) * A.Mc + m] = (T)(scale * si);
+        }
+      }
+  }
 }
 
 template <typename T, bool CPLX, int DE>
-__global__ __launch_bounds__(256) void k_cluster_expm_wg(ClusterArgs<T> A, double* scratch, int64_t slab) {
+__global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(ClusterArgs<T> A, double* scratch, int64_t slab) {
   constexpr int64_t DD = (int64_t)DE * DE;
   constexpr int NPL = CPLX ? 2 : 1;
-  __shared__ double red[8];
-  const int tid = threadIdx.x, nth = blockDim.x;
+  constexpr int NB16 = DE / 16;
+  __shared__ __attribute__((aligned(1024))) unsigned char stage0[wg_stage_bytes<CPLX, DE>()], stage1[wg_stage_bytes<CPLX, DE>()];
+  __shared__ double red[16];
+  using EP = ExpPoly<T>;
+  const int tid = threadIdx.x, nth = blockDim.x, l = tid % 64;
   double* base = scratch + (int64_t)blockIdx.x * slab;
-  double* mr[5];
-  double* mi[5];
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    mr[k] = base + (int64_t)k * NPL * DD;
-    mi[k] = CPLX ? mr[k] + DD : nullptr;
-  }
-  double *Xr = mr[0], *Xi = mi[0], *P2r = mr[1], *P2i = mi[1], *P3r = mr[2], *P3i = mi[2];
+  double *X = base, *P2 = base + NPL * DD, *P3 = base + 2 * NPL * DD;
   const T th = A.tab ? (T)A.tab->theta_cur : (T)A.theta;
   const double beta = A.tab ? A.tab->beta : A.beta;
-  constexpr double c0 = 1.0, c1 = 1.0, c2 = 1.0 / 2, c3 = 1.0 / 6, c4 = 1.0 / 24, c5 = 1.0 / 120,
-                   c6 = 1.0 / 720, c7 = 1.0 / 5040, c8 = 1.0 / 40320, c9 = 1.0 / 362880, c10 = 1.0 / 3628800,
-                   c11 = 1.0 / 39916800, c12 = 1.0 / 479001600;
-  const GInit zero{0.0, 0.0, 0.0, nullptr, nullptr, nullptr, nullptr};
-  for (int64_t c = blockIdx.x; c < A.n; c += gridDim.x) {
-    double *Mr = mr[3], *Mi = mi[3], *Br = mr[4], *Bi = mi[4];
-    // ---- a1/a2: assemble theta_e at eta ----
-    big_assemble<T, double, CPLX, false>(A, c, DE, Xr, Xi, (double*)nullptr, (double*)nullptr, th, tid, nth);
+  // neighbouring clusters (whose messages share cache lines) to the same XCD
+  for (int64_t c0 = 0; c0 < A.n; c0 += gridDim.x) {
+    const int64_t nc = A.n - c0 < (int64_t)gridDim.x ? A.n - c0 : (int64_t)gridDim.x;
+    if ((int64_t)blockIdx.x >= nc) break;   // block-uniform
+    const int64_t c = c0 + xcd_cluster(blockIdx.x, nc);
+    double *M = base + 3 * NPL * DD, *Q = base + 4 * NPL * DD;
+    // ---- a1/a2: X = -kappa beta (theta_e - mu) at eta ----
+    const double mu = block_sum(wg_assemble<T, CPLX, DE>(A, c, X, th, 0.0, nullptr, tid, nth), red) / DE;
+    wg_assemble<T, CPLX, DE>(A, c, X, th, -EP::kappa * beta, &mu, tid, nth);
     __syncthreads();
-    // ---- shift and scale: X = -(beta / 2^s) (theta - mu) ----
-    double tr = 0.0;
-    for (int k = tid; k < DE; k += nth) tr += Xr[(int64_t)k * DE + k];
-    const double mu = block_sum(tr, red) / DE;
-    double n2 = 0.0;
-    for (int64_t idx = tid; idx < DD; idx += nth) {
-      const double v = Xr[idx] - ((idx / DE == idx % DE) ? mu : 0.0);
-      n2 = fma(v, v, n2);
-      if constexpr (CPLX) n2 = fma(Xi[idx], Xi[idx], n2);
-    }
-    double rmax = 0.0;   // induced 1-norm: one row per thread
-    for (int i = tid; i < DE; i += nth) {
-      const double* xr = Xr + (int64_t)i * DE;
-      double a = 0.0;
-      for (int j = 0; j < DE; ++j) {
-        const double v = xr[j] - (i == j ? mu : 0.0);
-        if constexpr (CPLX) a += sqrt(fma(v, v, Xi[(int64_t)i * DE + j] * Xi[(int64_t)i * DE + j]));
-        else a += fabs(v);
+    // ---- X^2, its column sums (per block row, in the still unused Q) and the scale; see k_cluster_expm ----
+    wg_product<double, CPLX, DE, true>(X, X, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 ar, mfma_f64x4 ai) {
+      if (I > J) return;
+      double vr[4], vi[4], m[4], cs = 0.0;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        vr[r] = ar[r];
+        vi[r] = ai[r];
+        if constexpr (CPLX) m[r] = __builtin_amdgcn_sqrt(fma(ar[r], ar[r], ai[r] * ai[r]));
+        else m[r] = fabs(ar[r]);
+        cs += m[r];
       }
+      cs += __shfl_xor(cs, 16, 64);
+      cs += __shfl_xor(cs, 32, 64);
+      if (l < 16) Q[I * DE + 16 * J + l] = cs;
+      if (I != J) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          m[r] = row_sum16(m[r]);
+          if ((l & 15) == 0) Q[J * DE + 16 * I + 4 * r + (l >> 4)] = m[r];
+        }
+      }
+      wg_store<double, double, CPLX, DE>(P2, I, J, l, vr, vi);
+    });
+    double rmax = 0.0;
+    for (int i = tid; i < DE; i += nth) {
+      double a = 0.0;
+      for (int b = 0; b < NB16; ++b) a += Q[b * DE + i];
       rmax = fmax(rmax, a);
     }
-    const double nrm = beta * fmin(sqrt(block_sum(n2, red)), block_max(rmax, red));
-    int s = 0;
-    while (s < 200 && nrm > ldexp(0.5, s)) ++s;   // block-uniform
-    const double sc = -ldexp(beta, -s);
-    for (int64_t idx = tid; idx < DD; idx += nth) {
-      Xr[idx] = sc * (Xr[idx] - ((idx / DE == idx % DE) ? mu : 0.0));
-      if constexpr (CPLX) Xi[idx] *= sc;
-    }
-    __syncthreads();
-    // ---- E0 = T_m(X): m = 12, or 8 for float messages (one product fewer; see k_cluster_expm) ----
-    constexpr bool kDeg8 = std::is_same<T, float>::value;
-    gmm<CPLX, DE>(Xr, Xi, Xr, Xi, P2r, P2i, 1.0, zero, tid);
-    __syncthreads();
-    gmm<CPLX, DE>(Xr, Xi, P2r, P2i, P3r, P3i, 1.0, zero, tid);
-    __syncthreads();
-    for (int64_t idx = tid; idx < DD; idx += nth) {
-      const bool diag = idx / DE == idx % DE;
-      if constexpr (kDeg8) {
-        Mr[idx] = fma(c8, P2r[idx], c7 * Xr[idx]) + (diag ? c6 : 0.0);
-        if constexpr (CPLX) Mi[idx] = fma(c8, P2i[idx], c7 * Xi[idx]);
-      } else {
-        Mr[idx] = fma(c12, P3r[idx], fma(c11, P2r[idx], c10 * Xr[idx])) + (diag ? c9 : 0.0);
-        if constexpr (CPLX) Mi[idx] = fma(c12, P3i[idx], fma(c11, P2i[idx], c10 * Xi[idx]));
+    const int s = __builtin_amdgcn_readfirstlane(expm_squarings<T>(sqrt(block_max(rmax, red)) * (1.0 / EP::kappa)));
+    const double f1 = ldexp(1.0, -s), f2 = ldexp(1.0, -2 * s);
+    // ---- E0 = p(X / kappa) (see ExpPoly): P3 = X P2, M = b(X) ----
+    wg_product<double, CPLX, DE, false>(X, P2, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 ar, mfma_f64x4 ai) {
+      if (I > J) return;
+      double vr[4], vi[4], wr[4], wi[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int o = (16 * I + 4 * r + (l >> 4)) * DE + 16 * J + (l & 15);
+        vr[r] = f1 * f2 * ar[r];
+        wr[r] = fma(EP::b2 * f2, P2[o], fma(EP::b1 * f1, X[o], vr[r]));
+        if constexpr (CPLX) {
+          vi[r] = f1 * f2 * ai[r];
+          wi[r] = fma(EP::b2 * f2, P2[DD + o], fma(EP::b1 * f1, X[DD + o], vi[r]));
+        }
       }
-    }
-    __syncthreads();
-    const double hc[3][3] = {{c6, c7, c8}, {c3, c4, c5}, {c0, c1, c2}};
-    double trp = 0.0;
-    for (int h = kDeg8 ? 1 : 0; h < 3; ++h) {
-      const GInit in{hc[h][0], hc[h][1], hc[h][2], Xr, Xi, P2r, P2i};
-      trp = gmm<CPLX, DE>(P3r, P3i, Mr, Mi, Br, Bi, 1.0, in, tid);
-      __syncthreads();
-      double* tp = Mr; Mr = Br; Br = tp;
-      tp = Mi; Mi = Bi; Bi = tp;
-    }
+      wg_store<double, double, CPLX, DE>(P3, I, J, l, vr, vi);
+      wg_store<double, double, CPLX, DE>(M, I, J, l, wr, wi);
+    });
+    // Q = a6, and a6 + s3 y3 + s2 y2 + s1 y + s0 over P3 (each element is read only by the thread
+    // that replaces it; the mirrored ones are not read at all)
+    wg_product<double, CPLX, DE, true>(M, M, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 ar, mfma_f64x4 ai) {
+      if (I > J) return;
+      double vr[4], vi[4], wr[4], wi[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * I + 4 * r + (l >> 4), j = 16 * J + (l & 15), o = i * DE + j;
+        const double x1 = f1 * X[o], x2 = f2 * P2[o], x3 = P3[o];
+        vr[r] = fma(EP::r3, x3, fma(EP::r2, x2, fma(EP::r1, x1, ar[r])));
+        wr[r] = fma(EP::s3, x3, fma(EP::s2, x2, fma(EP::s1, x1, vr[r]))) + (i == j ? EP::s0 : 0.0);
+        if constexpr (CPLX) {
+          const double y1 = f1 * X[DD + o], y2 = f2 * P2[DD + o], y3 = P3[DD + o];
+          vi[r] = fma(EP::r3, y3, fma(EP::r2, y2, fma(EP::r1, y1, ai[r])));
+          wi[r] = fma(EP::s3, y3, fma(EP::s2, y2, fma(EP::s1, y1, vi[r])));
+        }
+      }
+      wg_store<double, double, CPLX, DE>(Q, I, J, l, vr, vi);
+      wg_store<double, double, CPLX, DE>(P3, I, J, l, wr, wi);
+    });
+    double trp = 0.0;   // this thread's share of the trace
+    wg_product<double, CPLX, DE, false>(P3, Q, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 ar, mfma_f64x4 ai) {
+      if (I > J) return;
+      double vr[4], vi[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * I + 4 * r + (l >> 4), j = 16 * J + (l & 15), o = i * DE + j;
+        vr[r] = fma(EP::t2 * f2, P2[o], fma(EP::t1 * f1, X[o], ar[r])) + (i == j ? 1.0 : 0.0);
+        if (i == j) trp += vr[r];
+        if constexpr (CPLX) vi[r] = fma(EP::t2 * f2, P2[DD + o], fma(EP::t1 * f1, X[DD + o], ai[r]));
+      }
+      wg_store<double, double, CPLX, DE>(M, I, J, l, vr, vi);
+    });
     // ---- normalise and square: Z_{j+1} = Z_j^2 / (Tr Z_j)^2 ----
-    // (float messages: the squarings after the first kF64Squarings in FP32, in the buffers of X^2
-    // and X^3, which the polynomial no longer needs; see k_cluster_expm)
+    // Float messages: the squarings after the first kF64Squarings in FP32 (see k_cluster_expm), on
+    // float matrices in the slabs of X^2 and X^3, which the polynomial no longer needs; the last
+    // FP64 squaring writes its result in float.
+    constexpr bool kF32 = std::is_same<T, float>::value;
     double t = block_sum(trp, red);
     double L = log(t);
-    const int n64 = std::is_same<T, float>::value ? (s < 4 ? s : 4) : s;
+    const int n64 = kF32 ? (s < kF64Squarings ? s : kF64Squarings) : s;
+    float* fa = reinterpret_cast<float*>(P2);
+    float* fb = reinterpret_cast<float*>(P3);
     for (int j = 0; j < n64; ++j) {
-      trp = gmm<CPLX, DE>(Mr, Mi, Mr, Mi, Br, Bi, 1.0 / (t * t), zero, tid);
-      __syncthreads();
-      double* tp = Mr; Mr = Br; Br = tp;
-      tp = Mi; Mi = Bi; Bi = tp;
+      const double scale = 1.0 / (t * t);
+      const bool last32 = kF32 && j + 1 == n64 && n64 < s;
+      trp = 0.0;
+      wg_product<double, CPLX, DE, true>(M, M, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 ar, mfma_f64x4 ai) {
+        if (I > J) return;
+        double vr[4], vi[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          vr[r] = scale * ar[r];
+          vi[r] = scale * ai[r];
+          if (I == J && 4 * r + (l >> 4) == (l & 15)) trp += vr[r];
+        }
+        if (last32) wg_store<float, double, CPLX, DE>(fa, I, J, l, vr, vi);
+        else wg_store<double, double, CPLX, DE>(Q, I, J, l, vr, vi);
+      });
+      double* tp = M;
+      M = Q;
+      Q = tp;
       t = block_sum(trp, red);
       L = fma(2.0, L, log(t));
     }
-    if (n64 < s) {
-      float* fa_r = reinterpret_cast<float*>(P2r);
-      float* fa_i = CPLX ? fa_r + DD : nullptr;
-      float* fb_r = fa_r + NPL * DD;
-      float* fb_i = CPLX ? fb_r + DD : nullptr;
-      for (int64_t idx = tid; idx < DD; idx += nth) {
-        fa_r[idx] = (float)Mr[idx];
-        if constexpr (CPLX) fa_i[idx] = (float)Mi[idx];
-      }
-      __syncthreads();
+    if constexpr (kF32) {
       for (int j = n64; j < s; ++j) {
-        trp = gsq32<CPLX, DE>(fa_r, fa_i, fb_r, fb_i, (float)(1.0 / (t * t)), tid);
-        __syncthreads();
-        float* tp = fa_r; fa_r = fb_r; fb_r = tp;
-        tp = fa_i; fa_i = fb_i; fb_i = tp;
+        const float scale = (float)(1.0 / (t * t));
+        trp = 0.0;
+        wg_product<float, CPLX, DE, true>(fa, fa, stage0, stage1, tid, [&](int I, int J, mfma_f32x4 ar, mfma_f32x4 ai) {
+          if (I > J) return;
+          float vr[4], vi[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            vr[r] = scale * ar[r];
+            vi[r] = scale * ai[r];
+            if (I == J && 4 * (l >> 4) + r == (l & 15)) trp += (double)vr[r];
+          }
+          wg_store<float, float, CPLX, DE>(fb, I, J, l, vr, vi);
+        });
+        float* tp = fa;
+        fa = fb;
+        fb = tp;
         t = block_sum(trp, red);
         L = fma(2.0, L, log(t));
       }
-      for (int64_t idx = tid; idx < DD; idx += nth) {
-        Mr[idx] = (double)fa_r[idx];
-        if constexpr (CPLX) Mi[idx] = (double)fa_i[idx];
-      }
-      __syncthreads();
     }
     const double F = mu - L / beta;
     const int32_t gid = A.gid[c];
@@ -2844,7 +3018,8 @@ __global__ __launch_bounds__(256) void k_cluster_expm_wg(ClusterArgs<T> A, doubl
       if (!isfinite(F) && A.nonfinite) atomicAdd(A.nonfinite, 1ull);
     }
     // ---- a5: outputs of rho = Z_s / Tr Z_s ----
-    big_outputs<T, double, CPLX>(A, c, DE, gid, Mr, Mi, 1.0 / t, tid, nth);
+    if (kF32 && n64 < s) wg_outputs<T, float, CPLX, DE>(A, c, gid, fa, 1.0 / t, tid, nth);
+    else wg_outputs<T, double, CPLX, DE>(A, c, gid, M, 1.0 / t, tid, nth);
     __syncthreads();
   }
 }
@@ -3950,13 +4125,13 @@ static hipError_t launch_cluster_m(const ClusterArgs<T>& a, int block, int W, hi
       else if (a.De >= 32 && a.De <= 256 && a.expm_scratch != nullptr && a.expm_blocks > 0) {
         const unsigned grid = (unsigned)std::min<int64_t>(a.n, a.expm_blocks);
         if (a.De == 32)
-          hipLaunchKernelGGL((k_cluster_expm_wg<T, CPLX, 32>), dim3(grid), dim3(256), 0, s, a, a.expm_scratch, a.expm_slab);
+          hipLaunchKernelGGL((k_cluster_expm_wg<T, CPLX, 32>), dim3(grid), dim3(WgPlan<32>::waves * 64), 0, s, a, a.expm_scratch, a.expm_slab);
         else if (a.De == 64)
-          hipLaunchKernelGGL((k_cluster_expm_wg<T, CPLX, 64>), dim3(grid), dim3(256), 0, s, a, a.expm_scratch, a.expm_slab);
+          hipLaunchKernelGGL((k_cluster_expm_wg<T, CPLX, 64>), dim3(grid), dim3(WgPlan<64>::waves * 64), 0, s, a, a.expm_scratch, a.expm_slab);
         else if (a.De == 128)
-          hipLaunchKernelGGL((k_cluster_expm_wg<T, CPLX, 128>), dim3(grid), dim3(256), 0, s, a, a.expm_scratch, a.expm_slab);
+          hipLaunchKernelGGL((k_cluster_expm_wg<T, CPLX, 128>), dim3(grid), dim3(WgPlan<128>::waves * 64), 0, s, a, a.expm_scratch, a.expm_slab);
         else if (a.De == 256)
-          hipLaunchKernelGGL((k_cluster_expm_wg<T, CPLX, 256>), dim3(grid), dim3(256), 0, s, a, a.expm_scratch, a.expm_slab);
+          hipLaunchKernelGGL((k_cluster_expm_wg<T, CPLX, 256>), dim3(grid), dim3(WgPlan<256>::waves * 64), 0, s, a, a.expm_scratch, a.expm_slab);
         else
           return hipErrorInvalidValue;
       } else
