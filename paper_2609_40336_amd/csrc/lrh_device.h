@@ -2514,17 +2514,17 @@ __global__ __launch_bounds__(64) void k_cluster_expm(ClusterArgs<T> A) {
   }
 }
 
-// Workgroup variant for De = 32, 64, 128, 256: five matrices in a per-workgroup slab, row-major, real
-// plane then imaginary plane.  Only the 16 x 16 blocks on and above the diagonal of a product are
-// computed (every product here is a polynomial in one Hermitian matrix), an off-diagonal block is
-// also written conjugate-transposed.  The A operand of block (I, K) is read as the conjugate of
-// block (K, I), so both operands of a k-step come from the same rows of the matrix: KS whole rows
-// at a time go to LDS (global_load_lds, two buffers, one barrier per step), where every wave reads
-// the fragments of its blocks.  A staged row thus serves all blocks of the pass; reading fragments
-// from the slab instead (32 x 32 tiles per wave, no LDS) moved 10 MB per 256 x 256 product through
-// the last-level cache and HBM, which at 5 TB/s was the bound (MFMA 40 % busy), now 4 MB.
-//
-// A complex product takes three real ones (R1 R2, N1 N2, (R1 + N1)(R2 + N2)) instead of four.
+// Workgroup variant for De = 32, 64, 128, 256: five matrices in a per-workgroup slab, row-major.  A
+// complex Hermitian matrix R + i N (R symmetric, N antisymmetric) is kept as the one real matrix
+// Z = R + N (so Z^T = R - N), half the memory of two planes.  For commuting Hermitian factors
+//     Z' = Z1 Z2 - 2 N1 N2,   Z'^T = Z1^T Z2^T - 2 N1 N2,
+// so the two off-diagonal blocks (I, J) and (J, I) of a product take three real block products (four
+// with separate planes) and the second comes out transposed, as the lanes need it.  Only the 16 x 16
+// blocks on and above the diagonal are computed.  For both, the operands of a k-step are rows and
+// columns k of the matrix: KS whole rows, and for complex matrices KS whole columns, go to LDS at a
+// time (LDS-direct loads, two buffers, one barrier per step), where every wave reads the fragments of
+// its blocks.  The kernel is bound by the memory traffic of the products: reading fragments from the
+// slab (32 x 32 tiles per wave, no LDS, two planes) moved 10 MB per 256 x 256 product at 5 TB/s.
 //
 // Blocks of a product and the waves that compute them: `passes` sweeps over the rows, in each of
 // which a wave holds the accumulators of `nblk` blocks (ab[b], bb[b] index its A and B fragments).
@@ -2607,16 +2607,23 @@ struct WgMfma<float> {
   static __device__ __forceinline__ int row(int l, int r) { return 4 * (l >> 4) + r; }
 };
 
-// Bank swizzle of a staged row k: the four rows that one fragment read touches would start on the
-// same bank; row k holds its blocks of 16 elements permuted by block ^ wg_swizzle(k), which depends
-// on the low bits of k only (those of l / 16 for a reading lane).
+// Bank swizzles of a stage.  Row k: the four rows that one fragment read touches would start on the
+// same bank, so its blocks of 16 elements are permuted by block ^ wg_swizzle(k), which depends on the
+// low bits of k only (those of l / 16 for a reading lane).  Columns are staged as DE pieces of CC
+// 16-byte chunks (element (i, k0 + .)); piece i has its chunks permuted by chunk ^ wg_csw(i), which
+// spreads the 16 pieces of a fragment over the banks.
 template <typename S, int DE>
 __device__ __forceinline__ int wg_swizzle(int k) {
   return sizeof(S) == 8 ? (k & 1) : (DE >= 64 ? (k & 3) : ((k >> 1) & 1));
 }
+template <int CC>
+__device__ __forceinline__ int wg_csw(int i) {
+  static_assert(CC == 2 || CC == 4 || CC == 8 || CC == 16, "chunks per piece");
+  return CC == 16 ? (i & 15) : CC == 8 ? ((i >> 1) & 7) : CC == 4 ? ((i >> 2) & 3) : ((i >> 3) & 1);
+}
 
-// Sizes of a stage: KS rows of every plane of X (and of Y unless SAME).  A float stage holds twice
-// the rows of a double one, two matrices' stage half of them.
+// Sizes of a stage: KS rows (complex: and columns) of X (and of Y unless SAME).  A float stage holds
+// twice the rows of a double one, two matrices' stage half of them.
 template <typename S, bool CPLX, int DE, bool SAME>
 struct WgStage {
   using P = WgPlan<DE>;
@@ -2624,78 +2631,91 @@ struct WgStage {
   static constexpr int KS0 = P::ks * (int)(sizeof(double) / sizeof(S)) / (SAME ? 1 : 2);
   static constexpr int KS = KS0 < DE ? KS0 : DE;
   static constexpr int NK = DE / KS;
-  static constexpr int NROW = KS * NPL * (SAME ? 1 : 2);
+  static constexpr int PB = KS * DE * (int)sizeof(S);    // bytes of a panel (rows or columns)
+  static constexpr int NINS = PB / 1024;                 // wave loads per panel
   static constexpr int CPR = DE * (int)sizeof(S) / 16;   // 16-byte chunks per row
-  static constexpr int NINS = NROW * CPR / 64;           // wave loads per stage
-  static_assert(NINS * 64 == NROW * CPR && KS % 4 == 0 && NK * KS == DE, "whole wave loads and stages");
-  static_assert(NROW * DE * (int)sizeof(S) <= wg_stage_bytes<CPLX, DE>(), "stage fits its buffer");
+  static constexpr int CC = KS * (int)sizeof(S) / 16;    // and per column piece
+  static constexpr int NPAN = NPL * (SAME ? 1 : 2);
+  static_assert(NINS * 1024 == PB && KS % 4 == 0 && NK * KS == DE, "whole wave loads and stages");
+  static_assert(NPAN * PB <= wg_stage_bytes<CPLX, DE>(), "stage fits its buffer");
 };
 
-// Rows k0 .. k0 + KS - 1 to the buffer, by LDS-direct loads spread over the waves.
+// Rows (and columns) k0 .. k0 + KS - 1 to the buffer, by LDS-direct loads spread over the waves:
+// panels X rows, X columns, Y rows, Y columns.
 template <typename S, bool CPLX, int DE, bool SAME>
 __device__ __forceinline__ void wg_fill(const S* X, const S* Y, int k0, unsigned char* buf, int wave, int l) {
   using G = WgStage<S, CPLX, DE, SAME>;
-  constexpr int64_t DD = (int64_t)DE * DE;
+  constexpr int EPC = 16 / (int)sizeof(S);   // elements per chunk
+#pragma unroll
+  for (int pan = 0; pan < G::NPAN; ++pan) {
+    const S* Z = pan < G::NPL ? X : Y;
 #pragma unroll 2
-  for (int q = wave; q < G::NINS; q += G::P::waves) {
-    const int ch = q * 64 + l;
-    const int row = ch / G::CPR, cp = ch % G::CPR;
-    const int k = row % G::KS, pl = row / G::KS;                           // pl: matrix * NPL + plane
-    const int cg = cp ^ (wg_swizzle<S, DE>(k) * (int)sizeof(S));          // sizeof(S) chunks per block
-    const S* src = (SAME || pl < G::NPL ? X : Y - G::NPL * DD) + pl * DD + (int64_t)(k0 + k) * DE +
-                   cg * (16 / (int)sizeof(S));
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                     (__attribute__((address_space(3))) void*)(buf + q * 1024), 16, 0, 0);
+    for (int q = wave; q < G::NINS; q += G::P::waves) {
+      const int ch = q * 64 + l;
+      int64_t o;
+      if (pan % G::NPL == 0) {
+        const int k = ch / G::CPR, cp = ch % G::CPR;
+        o = (int64_t)(k0 + k) * DE + (cp ^ (wg_swizzle<S, DE>(k) * (int)sizeof(S))) * EPC;   // sizeof(S) chunks per block
+      } else {
+        const int i = ch / G::CC, cp = ch % G::CC;
+        o = (int64_t)i * DE + k0 + (cp ^ wg_csw<G::CC>(i)) * EPC;
+      }
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Z + o),
+                                       (__attribute__((address_space(3))) void*)(buf + pan * G::PB + q * 1024), 16, 0, 0);
+    }
   }
 }
 
-// Accumulators of a wave's blocks
+// Accumulators of a wave's blocks: real: s1 the block; complex: s1 of Z1 Z2, s4 of (Z1^T Z2^T), p2 of
+// -(2 N1)(2 N2)
 template <typename S, bool CPLX, int DE>
 struct WgAcc {
   static constexpr int N = WgPlan<DE>::nblk;
-  typename WgMfma<S>::acc p1[N], p2[CPLX ? N : 1], p3[CPLX ? N : 1];
+  typename WgMfma<S>::acc s1[N], s4[CPLX ? N : 1], p2[CPLX ? N : 1];
 };
 
 // One stage: the next one's loads are issued into `nxt` (k0 >= 0), then the products of the rows in
 // `st` are accumulated.  The two are different buffers: `restrict` tells the compiler so, which
-// would otherwise wait for the loads before the first read.
+// would otherwise wait for the loads before the first read.  oz, ow: byte offsets of a lane's row and
+// column elements at kk = 0 (A blocks, then B blocks).
 template <typename S, bool CPLX, int DE, bool SAME>
-__device__ __forceinline__ void wg_step(const S* __restrict__ st, unsigned char* __restrict__ nxt, const S* X, const S* Y,
-                                        int k0, int wave, int l, const int (&oa)[WgPlan<DE>::na],
-                                        const int (&ob)[WgPlan<DE>::nb], WgAcc<S, CPLX, DE>& acc) {
+__device__ __forceinline__ void wg_step(const unsigned char* __restrict__ st, unsigned char* __restrict__ nxt, const S* X,
+                                        const S* Y, int k0, int wave, int l,
+                                        const int (&oz)[WgPlan<DE>::na + WgPlan<DE>::nb],
+                                        const int (&ow)[WgPlan<DE>::na + WgPlan<DE>::nb], WgAcc<S, CPLX, DE>& acc) {
   using P = WgPlan<DE>;
   using F = WgMfma<S>;
   using G = WgStage<S, CPLX, DE, SAME>;
+  constexpr int NF = P::na + P::nb;
   if (k0 >= 0) wg_fill<S, CPLX, DE, SAME>(X, Y, k0, nxt, wave, l);
 #pragma unroll 4
   for (int kk = 0; kk < G::KS / 4; ++kk) {
-    S ar[P::na], an[P::na], br[P::nb], bn[P::nb];
+    S z[NF], w[NF];
 #pragma unroll
-    for (int q = 0; q < P::na; ++q) {
-      ar[q] = st[oa[q] + kk * 4 * DE];
-      if constexpr (CPLX) an[q] = st[oa[q] + kk * 4 * DE + G::KS * DE];
-    }
-#pragma unroll
-    for (int q = 0; q < P::nb; ++q) {
-      br[q] = st[ob[q] + kk * 4 * DE];
-      if constexpr (CPLX) bn[q] = st[ob[q] + kk * 4 * DE + G::KS * DE];
+    for (int q = 0; q < NF; ++q) {
+      z[q] = *reinterpret_cast<const S*>(st + oz[q] + kk * 4 * DE * (int)sizeof(S));
+      // chunk (4 kk + l / 16) / EPC of the piece, permuted: kk only toggles bits of the offset
+      if constexpr (CPLX) w[q] = *reinterpret_cast<const S*>(st + (ow[q] ^ (kk * 4 * (int)sizeof(S))));
     }
 #pragma unroll
     for (int b = 0; b < P::nblk; ++b) {
-      acc.p1[b] = F::mma(ar[P::ab[b]], br[P::bb[b]], acc.p1[b]);
+      const int ia = P::ab[b], ib = P::na + P::bb[b];
       if constexpr (CPLX) {
-        // the A operands are transposes: N^T = -N, (R - N)^T = R + N
-        acc.p2[b] = F::mma(an[P::ab[b]], bn[P::bb[b]], acc.p2[b]);   // -N1 N2
-        acc.p3[b] = F::mma(ar[P::ab[b]] - an[P::ab[b]], br[P::bb[b]] + bn[P::bb[b]], acc.p3[b]);
+        // A operands are transposes of what the lanes hold
+        acc.s1[b] = F::mma(w[ia], z[ib], acc.s1[b]);
+        acc.s4[b] = F::mma(z[ia], w[ib], acc.s4[b]);
+        acc.p2[b] = F::mma(z[ia] - w[ia], z[ib] - w[ib], acc.p2[b]);
+      } else {
+        acc.s1[b] = F::mma(z[ia], z[ib], acc.s1[b]);
       }
     }
   }
 }
 
-// epi(I, J, re, im): the accumulated block (I, J) of X Y (SAME: Y is X), for every block of the plan
-// (a 2 x 2 tile on the diagonal also computes its block below it: I > J, to be skipped).
-// X, Y: slab matrices (real plane, then imaginary).  s0, s1: buffers of wg_stage_bytes().
-// All waves call it, after a barrier that follows the writes of X and Y; it ends with one itself.
+// epi(I, J, v, u): the block (I, J) of X Y (SAME: Y is X), v[r] element (i, j) of the result's Z, u[r]
+// element (j, i), for every block I <= J.  X, Y: slab matrices.  s0, s1: buffers of
+// wg_stage_bytes().  All waves call it, after a barrier that follows the writes of X and Y; it ends
+// with one itself.
 template <typename S, bool CPLX, int DE, bool SAME, typename Epi>
 __device__ __forceinline__ void wg_product(const S* X, const S* Y, unsigned char* s0, unsigned char* s1, int tid,
                                            Epi&& epi) {
@@ -2703,75 +2723,84 @@ __device__ __forceinline__ void wg_product(const S* X, const S* Y, unsigned char
   using F = WgMfma<S>;
   using G = WgStage<S, CPLX, DE, SAME>;
   static_assert(G::NK % 2 == 0, "stages alternate between the buffers");
+  constexpr int NF = P::na + P::nb;
+  constexpr int ES = (int)sizeof(S);
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64;
   const int lr = l >> 4, lc = l & 15;
   wg_fill<S, CPLX, DE, SAME>(X, Y, 0, s0, wave, l);
 #pragma unroll 1
   for (int pass = 0; pass < P::passes; ++pass) {
     const int t = pass * P::waves + wave;
-    int ia[P::na], jb[P::nb], oa[P::na], ob[P::nb];
+    int blk[NF], oz[NF], ow[NF];
 #pragma unroll
-    for (int q = 0; q < P::na; ++q) {
-      ia[q] = wg_block<DE>(t, q);
-      oa[q] = lr * DE + 16 * (ia[q] ^ wg_swizzle<S, DE>(lr)) + lc;
-    }
-#pragma unroll
-    for (int q = 0; q < P::nb; ++q) {
-      jb[q] = wg_block<DE>(t, P::na + q);
-      ob[q] = lr * DE + 16 * (jb[q] ^ wg_swizzle<S, DE>(lr)) + lc + (SAME ? 0 : G::NPL * G::KS * DE);
+    for (int q = 0; q < NF; ++q) {
+      blk[q] = wg_block<DE>(t, q);
+      const int pan = q < P::na || SAME ? 0 : G::NPL * G::PB;   // X's panels, or Y's
+      oz[q] = pan + (lr * DE + 16 * (blk[q] ^ wg_swizzle<S, DE>(lr)) + lc) * ES;
+      ow[q] = pan + G::PB + (16 * blk[q] + lc) * G::CC * 16 + (((lr * ES / 16) ^ wg_csw<G::CC>(lc)) * 16 | (lr * ES & 15));
     }
     WgAcc<S, CPLX, DE> acc;
 #pragma unroll
     for (int b = 0; b < P::nblk; ++b) {
-      acc.p1[b] = typename F::acc{0, 0, 0, 0};
-      if constexpr (CPLX) acc.p2[b] = acc.p3[b] = typename F::acc{0, 0, 0, 0};
+      acc.s1[b] = typename F::acc{0, 0, 0, 0};
+      if constexpr (CPLX) acc.s4[b] = acc.p2[b] = typename F::acc{0, 0, 0, 0};
     }
 #pragma unroll 1
     for (int K = 0; K < G::NK; K += 2) {
       __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's loads of the stage have landed
       __syncthreads();                      // and every wave's; the other buffer is no longer read
-      wg_step<S, CPLX, DE, SAME>(reinterpret_cast<const S*>(s0), s1, X, Y, (K + 1) * G::KS, wave, l, oa, ob, acc);
+      wg_step<S, CPLX, DE, SAME>(s0, s1, X, Y, (K + 1) * G::KS, wave, l, oz, ow, acc);
       __builtin_amdgcn_s_waitcnt(0x0f70);
       __syncthreads();
       const int k0 = K + 2 < G::NK ? (K + 2) * G::KS : (pass + 1 < P::passes ? 0 : -1);
-      wg_step<S, CPLX, DE, SAME>(reinterpret_cast<const S*>(s1), s0, X, Y, k0, wave, l, oa, ob, acc);
+      wg_step<S, CPLX, DE, SAME>(s1, s0, X, Y, k0, wave, l, oz, ow, acc);
     }
 #pragma unroll
     for (int b = 0; b < P::nblk; ++b) {
-      const int I = ia[P::ab[b]], J = jb[P::bb[b]];
-      if constexpr (CPLX) epi(I, J, acc.p1[b] + acc.p2[b], acc.p3[b] - acc.p1[b] + acc.p2[b]);
-      else epi(I, J, acc.p1[b], acc.p1[b]);
+      const int I = blk[P::ab[b]], J = blk[P::na + P::bb[b]];
+      if (I > J) continue;   // a 2 x 2 tile on the diagonal also covers its block below it
+      if constexpr (CPLX) {
+        const typename F::acc p = S(0.5) * acc.p2[b];
+        epi(I, J, acc.s1[b] + p, acc.s4[b] + p);
+      } else {
+        epi(I, J, acc.s1[b], acc.s1[b]);
+      }
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0f70);   // the epilogues' stores, before anyone stages them
   __syncthreads();
 }
 
-// Block (I, J), I <= J, of a Hermitian result (vr, vi) to the slab matrix C, and its conjugate
-// transpose to (J, I).
-template <typename D, typename S, bool CPLX, int DE>
-__device__ __forceinline__ void wg_store(D* C, int I, int J, int l, const S (&vr)[4], const S (&vi)[4]) {
+// Elements (i, j) of block (I, J), I <= J, to the slab matrix C: v, and u to (j, i).
+template <typename D, typename S, int DE>
+__device__ __forceinline__ void wg_store(D* C, int I, int J, int l, const S (&v)[4], const S (&u)[4]) {
+  const int j = 16 * J + (l & 15);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int i = 16 * I + WgMfma<S>::row(l, r);
+    C[i * DE + j] = (D)v[r];
+    if (I != J) C[j * DE + i] = (D)u[r];
+  }
+}
+// The final result instead as planes R and N of its upper triangle, as the outputs read it.
+template <bool CPLX, typename D, typename S, int DE>
+__device__ __forceinline__ void wg_store_planes(D* C, int I, int J, int l, const S (&v)[4], const S (&u)[4]) {
   constexpr int64_t DD = (int64_t)DE * DE;
   const int j = 16 * J + (l & 15);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int i = 16 * I + WgMfma<S>::row(l, r);
-    C[i * DE + j] = (D)vr[r];
-    if constexpr (CPLX) C[DD + i * DE + j] = (i == j) ? D(0) : (D)vi[r];
-    if (I != J) {
-      C[j * DE + i] = (D)vr[r];
-      if constexpr (CPLX) C[DD + j * DE + i] = -(D)vi[r];
-    }
+    C[i * DE + j] = CPLX ? (D)(S(0.5) * (v[r] + u[r])) : (D)v[r];
+    if constexpr (CPLX) C[DD + i * DE + j] = (D)(S(0.5) * (v[r] - u[r]));
   }
 }
 
-// theta_e of a cluster times sc (after subtracting mu on the diagonal) into the slab matrix X: one
+// theta_e of a cluster times sc (after subtracting mu on the diagonal) into the slab matrix X (Z form): one
 // row per wave, the lanes along it, only j >= i (the rest by symmetry).  With mu == nullptr only
 // the diagonal is formed and its sum returned (this thread's share).
 template <typename T, bool CPLX, int DE>
 __device__ double wg_assemble(const ClusterArgs<T>& A, int64_t c, double* X, T th, double sc, const double* mu, int tid,
                               int nth) {
-  constexpr int64_t DD = (int64_t)DE * DE;
   constexpr int NB = log2i(DE);
   const int64_t ho = A.hoff[c];
   if (mu == nullptr) {
@@ -2788,20 +2817,18 @@ __device__ double wg_assemble(const ClusterArgs<T>& A, int64_t c, double* X, T t
     for (int j = i + l; j < DE; j += 64) {
       T vr, vi;
       theta_elem<T, CPLX>(A, c, DE, NB, ho, i, j, th, vr, vi);
-      const double xr = sc * (i == j ? (double)vr - *mu : (double)vr);
-      X[i * DE + j] = xr;
-      X[j * DE + i] = xr;
-      if constexpr (CPLX) {
-        const double xi = i == j ? 0.0 : sc * (double)vi;
-        X[DD + i * DE + j] = xi;
-        X[DD + j * DE + i] = -xi;
+      if (i == j) {
+        X[i * DE + j] = sc * ((double)vr - *mu);
+      } else {
+        X[i * DE + j] = CPLX ? sc * ((double)vr + (double)vi) : sc * (double)vr;
+        X[j * DE + i] = CPLX ? sc * ((double)vr - (double)vi) : sc * (double)vr;
       }
     }
   return 0.0;
 }
 
-// Outputs of a cluster whose marginal scale * Y sits in a slab matrix: own marginal slot, per-cluster
-// marginal, partial traces onto every child.  One row of the packed upper triangle per wave at a
+// Outputs of a cluster whose marginal scale * Y sits in the slab (planes of the upper triangle): own
+// marginal slot, per-cluster marginal, partial traces onto every child.  One row of the packed upper triangle per wave at a
 // time, the lanes along it.
 template <typename T, typename S, bool CPLX, int DE>
 __device__ void wg_outputs(const ClusterArgs<T>& A, int64_t c, int32_t gid, const S* Y, double scale, int tid, int nth) {
@@ -2876,15 +2903,14 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
     wg_assemble<T, CPLX, DE>(A, c, X, th, -EP::kappa * beta, &mu, tid, nth);
     __syncthreads();
     // ---- X^2, its column sums (per block row, in the still unused Q) and the scale; see k_cluster_expm ----
-    wg_product<double, CPLX, DE, true>(X, X, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 ar, mfma_f64x4 ai) {
-      if (I > J) return;
-      double vr[4], vi[4], m[4], cs = 0.0;
+    wg_product<double, CPLX, DE, true>(X, X, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
+      double v[4], u[4], m[4], cs = 0.0;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        vr[r] = ar[r];
-        vi[r] = ai[r];
-        if constexpr (CPLX) m[r] = __builtin_amdgcn_sqrt(fma(ar[r], ar[r], ai[r] * ai[r]));
-        else m[r] = fabs(ar[r]);
+        v[r] = av[r];
+        u[r] = au[r];
+        // modulus: R^2 + N^2 = (v^2 + u^2) / 2
+        m[r] = CPLX ? __builtin_amdgcn_sqrt(0.5 * fma(v[r], v[r], u[r] * u[r])) : fabs(v[r]);
         cs += m[r];
       }
       cs += __shfl_xor(cs, 16, 64);
@@ -2897,7 +2923,7 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
           if ((l & 15) == 0) Q[J * DE + 16 * I + 4 * r + (l >> 4)] = m[r];
         }
       }
-      wg_store<double, double, CPLX, DE>(P2, I, J, l, vr, vi);
+      wg_store<double, double, DE>(P2, I, J, l, v, u);
     });
     double rmax = 0.0;
     for (int i = tid; i < DE; i += nth) {
@@ -2908,80 +2934,98 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
     const int s = __builtin_amdgcn_readfirstlane(expm_squarings<T>(sqrt(block_max(rmax, red)) * (1.0 / EP::kappa)));
     const double f1 = ldexp(1.0, -s), f2 = ldexp(1.0, -2 * s);
     // ---- E0 = p(X / kappa) (see ExpPoly): P3 = X P2, M = b(X) ----
-    wg_product<double, CPLX, DE, false>(X, P2, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 ar, mfma_f64x4 ai) {
-      if (I > J) return;
-      double vr[4], vi[4], wr[4], wi[4];
+    // (offsets of register r: o of (i, j), ot of (j, i))
+    const auto off = [&](int I, int J, int r) { return (16 * I + 4 * r + (l >> 4)) * DE + 16 * J + (l & 15); };
+    const auto offt = [&](int I, int J, int r) { return (16 * J + (l & 15)) * DE + 16 * I + 4 * r + (l >> 4); };
+    wg_product<double, CPLX, DE, false>(X, P2, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
+      double v[4], u[4], wv[4], wu[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int o = (16 * I + 4 * r + (l >> 4)) * DE + 16 * J + (l & 15);
-        vr[r] = f1 * f2 * ar[r];
-        wr[r] = fma(EP::b2 * f2, P2[o], fma(EP::b1 * f1, X[o], vr[r]));
+        const int o = off(I, J, r);
+        v[r] = f1 * f2 * av[r];
+        wv[r] = fma(EP::b2 * f2, P2[o], fma(EP::b1 * f1, X[o], v[r]));
+        u[r] = v[r];
+        wu[r] = wv[r];
         if constexpr (CPLX) {
-          vi[r] = f1 * f2 * ai[r];
-          wi[r] = fma(EP::b2 * f2, P2[DD + o], fma(EP::b1 * f1, X[DD + o], vi[r]));
+          const int ot = offt(I, J, r);
+          u[r] = f1 * f2 * au[r];
+          wu[r] = fma(EP::b2 * f2, P2[ot], fma(EP::b1 * f1, X[ot], u[r]));
         }
       }
-      wg_store<double, double, CPLX, DE>(P3, I, J, l, vr, vi);
-      wg_store<double, double, CPLX, DE>(M, I, J, l, wr, wi);
+      wg_store<double, double, DE>(P3, I, J, l, v, u);
+      wg_store<double, double, DE>(M, I, J, l, wv, wu);
     });
-    // Q = a6, and a6 + s3 y3 + s2 y2 + s1 y + s0 over P3 (each element is read only by the thread
-    // that replaces it; the mirrored ones are not read at all)
-    wg_product<double, CPLX, DE, true>(M, M, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 ar, mfma_f64x4 ai) {
-      if (I > J) return;
-      double vr[4], vi[4], wr[4], wi[4];
+    // Q = a6, and a6 + s3 y3 + s2 y2 + s1 y + s0 over P3 (off the diagonal blocks each element is read
+    // only by the thread that replaces it; within a diagonal block the whole wave reads first)
+    wg_product<double, CPLX, DE, true>(M, M, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
+      double v[4], u[4], wv[4], wu[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int i = 16 * I + 4 * r + (l >> 4), j = 16 * J + (l & 15), o = i * DE + j;
+        const int o = off(I, J, r);
         const double x1 = f1 * X[o], x2 = f2 * P2[o], x3 = P3[o];
-        vr[r] = fma(EP::r3, x3, fma(EP::r2, x2, fma(EP::r1, x1, ar[r])));
-        wr[r] = fma(EP::s3, x3, fma(EP::s2, x2, fma(EP::s1, x1, vr[r]))) + (i == j ? EP::s0 : 0.0);
+        v[r] = fma(EP::r3, x3, fma(EP::r2, x2, fma(EP::r1, x1, av[r])));
+        wv[r] = fma(EP::s3, x3, fma(EP::s2, x2, fma(EP::s1, x1, v[r])));
+        u[r] = v[r];
+        wu[r] = wv[r];
         if constexpr (CPLX) {
-          const double y1 = f1 * X[DD + o], y2 = f2 * P2[DD + o], y3 = P3[DD + o];
-          vi[r] = fma(EP::r3, y3, fma(EP::r2, y2, fma(EP::r1, y1, ai[r])));
-          wi[r] = fma(EP::s3, y3, fma(EP::s2, y2, fma(EP::s1, y1, vi[r])));
+          if (I != J) {
+            const int ot = offt(I, J, r);
+            const double y1 = f1 * X[ot], y2 = f2 * P2[ot], y3 = P3[ot];
+            u[r] = fma(EP::r3, y3, fma(EP::r2, y2, fma(EP::r1, y1, au[r])));
+            wu[r] = fma(EP::s3, y3, fma(EP::s2, y2, fma(EP::s1, y1, u[r])));
+          }
         }
+        if (I == J && 4 * r + (l >> 4) == (l & 15)) wv[r] += EP::s0;
       }
-      wg_store<double, double, CPLX, DE>(Q, I, J, l, vr, vi);
-      wg_store<double, double, CPLX, DE>(P3, I, J, l, wr, wi);
+      wg_store<double, double, DE>(Q, I, J, l, v, u);
+      wg_store<double, double, DE>(P3, I, J, l, wv, wu);
     });
-    double trp = 0.0;   // this thread's share of the trace
-    wg_product<double, CPLX, DE, false>(P3, Q, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 ar, mfma_f64x4 ai) {
-      if (I > J) return;
-      double vr[4], vi[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = 16 * I + 4 * r + (l >> 4), j = 16 * J + (l & 15), o = i * DE + j;
-        vr[r] = fma(EP::t2 * f2, P2[o], fma(EP::t1 * f1, X[o], ar[r])) + (i == j ? 1.0 : 0.0);
-        if (i == j) trp += vr[r];
-        if constexpr (CPLX) vi[r] = fma(EP::t2 * f2, P2[DD + o], fma(EP::t1 * f1, X[DD + o], ai[r]));
-      }
-      wg_store<double, double, CPLX, DE>(M, I, J, l, vr, vi);
-    });
-    // ---- normalise and square: Z_{j+1} = Z_j^2 / (Tr Z_j)^2 ----
     // Float messages: the squarings after the first kF64Squarings in FP32 (see k_cluster_expm), on
-    // float matrices in the slabs of X^2 and X^3, which the polynomial no longer needs; the last
-    // FP64 squaring writes its result in float.
+    // float matrices in the slabs of X^2 and X^3, which the polynomial no longer needs by then; the
+    // product before them writes its result in float.  The last product of all writes planes.
     constexpr bool kF32 = std::is_same<T, float>::value;
-    double t = block_sum(trp, red);
-    double L = log(t);
     const int n64 = kF32 ? (s < kF64Squarings ? s : kF64Squarings) : s;
     float* fa = reinterpret_cast<float*>(P2);
     float* fb = reinterpret_cast<float*>(P3);
+    double trp = 0.0;   // this thread's share of the trace
+    wg_product<double, CPLX, DE, false>(P3, Q, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
+      double v[4], u[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int o = off(I, J, r);
+        v[r] = fma(EP::t2 * f2, P2[o], fma(EP::t1 * f1, X[o], av[r]));
+        u[r] = v[r];
+        if constexpr (CPLX) {
+          const int ot = offt(I, J, r);
+          u[r] = fma(EP::t2 * f2, P2[ot], fma(EP::t1 * f1, X[ot], au[r]));
+        }
+        if (I == J && 4 * r + (l >> 4) == (l & 15)) {
+          v[r] += 1.0;
+          u[r] += 1.0;
+          trp += v[r];
+        }
+      }
+      if (s == 0) wg_store_planes<CPLX, double, double, DE>(M, I, J, l, v, u);
+      else wg_store<double, double, DE>(M, I, J, l, v, u);
+    });
+    // ---- normalise and square: Z_{j+1} = Z_j^2 / (Tr Z_j)^2 ----
+    double t = block_sum(trp, red);
+    double L = log(t);
     for (int j = 0; j < n64; ++j) {
       const double scale = 1.0 / (t * t);
       const bool last32 = kF32 && j + 1 == n64 && n64 < s;
       trp = 0.0;
-      wg_product<double, CPLX, DE, true>(M, M, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 ar, mfma_f64x4 ai) {
-        if (I > J) return;
-        double vr[4], vi[4];
+      wg_product<double, CPLX, DE, true>(M, M, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
+        double v[4], u[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          vr[r] = scale * ar[r];
-          vi[r] = scale * ai[r];
-          if (I == J && 4 * r + (l >> 4) == (l & 15)) trp += vr[r];
+          v[r] = scale * av[r];
+          u[r] = scale * au[r];
+          if (I == J && 4 * r + (l >> 4) == (l & 15)) trp += v[r];
         }
-        if (last32) wg_store<float, double, CPLX, DE>(fa, I, J, l, vr, vi);
-        else wg_store<double, double, CPLX, DE>(Q, I, J, l, vr, vi);
+        if (last32) wg_store<float, double, DE>(fa, I, J, l, v, u);
+        else if (j + 1 == s) wg_store_planes<CPLX, double, double, DE>(Q, I, J, l, v, u);
+        else wg_store<double, double, DE>(Q, I, J, l, v, u);
       });
       double* tp = M;
       M = Q;
@@ -2993,16 +3037,16 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
       for (int j = n64; j < s; ++j) {
         const float scale = (float)(1.0 / (t * t));
         trp = 0.0;
-        wg_product<float, CPLX, DE, true>(fa, fa, stage0, stage1, tid, [&](int I, int J, mfma_f32x4 ar, mfma_f32x4 ai) {
-          if (I > J) return;
-          float vr[4], vi[4];
+        wg_product<float, CPLX, DE, true>(fa, fa, stage0, stage1, tid, [&](int I, int J, mfma_f32x4 av, mfma_f32x4 au) {
+          float v[4], u[4];
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            vr[r] = scale * ar[r];
-            vi[r] = scale * ai[r];
-            if (I == J && 4 * (l >> 4) + r == (l & 15)) trp += (double)vr[r];
+            v[r] = scale * av[r];
+            u[r] = scale * au[r];
+            if (I == J && 4 * (l >> 4) + r == (l & 15)) trp += (double)v[r];
           }
-          wg_store<float, float, CPLX, DE>(fb, I, J, l, vr, vi);
+          if (j + 1 == s) wg_store_planes<CPLX, float, float, DE>(fb, I, J, l, v, u);
+          else wg_store<float, float, DE>(fb, I, J, l, v, u);
         });
         float* tp = fa;
         fa = fb;
