@@ -807,49 +807,82 @@ __device__ T lds_assemble(const ClusterArgs<T>& A, int64_t c, int lt, const T* x
                           const T* zp, T th, bool with_h, T offs, T* dr, T* di) {
   constexpr int LD = DE + 1;
   constexpr int NB = log2i(DE);
+  // A lane's elements in groups of up to 8 whose loads are issued together: every candidate element
+  // is loaded from a valid address and then selected, and the index of a child or parent message is
+  // read once per group (element by element, with a branch per child, the assembly was a chain of
+  // dependent loads: half of the 45 us the adjoint of 8192 8 x 8 clusters took).
+  constexpr int NE = DE * DE > W ? DE * DE / W : 1;
+  constexpr int CH = NE < 8 ? NE : 8;
+  static_assert(NE % CH == 0, "whole groups");
+  if (W > DE * DE && lt >= DE * DE) return T(0);
   const int64_t ho = with_h ? A.hoff[c] : -1;
   const int Dc = A.Dc;
   T my_n2 = T(0);
-  for (int idx = lt; idx < DE * DE; idx += W) {
-    const int i = idx / DE, j = idx % DE;
-    T vr = T(0), vi = T(0);
+  for (int base = 0; base < NE; base += CH) {
+    T vr[CH], vi[CH];
+#pragma unroll
+    for (int e = 0; e < CH; ++e) vr[e] = vi[e] = T(0);
     if (ho >= 0) {
       const double* h = A.h + ho;
-      herm_elem<T>([&](int k) { return (T)h[k]; }, i, j, DE, CPLX, vr, vi);
+#pragma unroll
+      for (int e = 0; e < CH; ++e) {
+        const int idx = lt + (base + e) * W;
+        herm_elem_bf<T, CPLX>([&](int k) { return (T)h[k]; }, idx / DE, idx % DE, DE, vr[e], vi[e]);
+      }
     }
     for (int s = 0; s < A.maxch; ++s) {
       const int m = A.ch[(int64_t)s * A.n + c];
-      if (m < 0) continue;
       const int mask = A.chmask[(int64_t)s * A.n + c];
-      if (((i ^ j) & ~mask & (DE - 1)) != 0) continue;
-      const int a = pext_rt(i, mask, NB), b = pext_rt(j, mask, NB);
-      T er, ei;
-      if (zc)
-        herm_elem<T>([&](int k) { const int64_t o = (int64_t)k * A.Mc + m;
-                                  return extrap<T>(xc[o], zc[o], th); }, a, b, Dc, CPLX, er, ei);
-      else
-        herm_elem<T>([&](int k) { return xc[(int64_t)k * A.Mc + m]; }, a, b, Dc, CPLX, er, ei);
-      const T sc = (a == b) ? T(1) : offs;
-      vr -= sc * er;
-      vi -= sc * ei;
+      if (m < 0) continue;
+      T er[CH], ei[CH];
+#pragma unroll
+      for (int e = 0; e < CH; ++e) {
+        const int idx = lt + (base + e) * W;
+        const int a = pext_rt(idx / DE, mask, NB), b = pext_rt(idx % DE, mask, NB);
+        if (zc)
+          herm_elem_bf<T, CPLX>([&](int k) { const int64_t o = (int64_t)k * A.Mc + m;
+                                             return extrap<T>(xc[o], zc[o], th); }, a, b, Dc, er[e], ei[e]);
+        else
+          herm_elem_bf<T, CPLX>([&](int k) { return xc[(int64_t)k * A.Mc + m]; }, a, b, Dc, er[e], ei[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < CH; ++e) {
+        const int idx = lt + (base + e) * W, i = idx / DE, j = idx % DE;
+        const bool ok = ((i ^ j) & ~mask & (DE - 1)) == 0;
+        const T sc = i == j ? T(1) : offs;   // a lifted element is diagonal where the child's is
+        vr[e] -= ok ? sc * er[e] : T(0);
+        if constexpr (CPLX) vi[e] -= ok ? sc * ei[e] : T(0);
+      }
     }
     for (int s = 0; s < A.maxpar; ++s) {
       const int m = A.par[(int64_t)s * A.n + c];
       if (m < 0) continue;
-      T er, ei;
-      if (zp)
-        herm_elem<T>([&](int k) { const int64_t o = (int64_t)k * A.Mp + m;
-                                  return extrap<T>(xp[o], zp[o], th); }, i, j, DE, CPLX, er, ei);
-      else
-        herm_elem<T>([&](int k) { return xp[(int64_t)k * A.Mp + m]; }, i, j, DE, CPLX, er, ei);
-      const T sc = (i == j) ? T(1) : offs;
-      vr += sc * er;
-      vi += sc * ei;
+      T er[CH], ei[CH];
+#pragma unroll
+      for (int e = 0; e < CH; ++e) {
+        const int idx = lt + (base + e) * W;
+        if (zp)
+          herm_elem_bf<T, CPLX>([&](int k) { const int64_t o = (int64_t)k * A.Mp + m;
+                                             return extrap<T>(xp[o], zp[o], th); }, idx / DE, idx % DE, DE, er[e], ei[e]);
+        else
+          herm_elem_bf<T, CPLX>([&](int k) { return xp[(int64_t)k * A.Mp + m]; }, idx / DE, idx % DE, DE, er[e], ei[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < CH; ++e) {
+        const int idx = lt + (base + e) * W;
+        const T sc = idx / DE == idx % DE ? T(1) : offs;
+        vr[e] += sc * er[e];
+        if constexpr (CPLX) vi[e] += sc * ei[e];
+      }
     }
-    dr[i * LD + j] = vr;
-    if constexpr (CPLX) di[i * LD + j] = vi;
-    my_n2 = dfma<T>(vr, vr, my_n2);
-    if constexpr (CPLX) my_n2 = dfma<T>(vi, vi, my_n2);
+#pragma unroll
+    for (int e = 0; e < CH; ++e) {
+      const int idx = lt + (base + e) * W, i = idx / DE, j = idx % DE;
+      dr[i * LD + j] = vr[e];
+      if constexpr (CPLX) di[i * LD + j] = vi[e];
+      my_n2 = dfma<T>(vr[e], vr[e], my_n2);
+      if constexpr (CPLX) my_n2 = dfma<T>(vi[e], vi[e], my_n2);
+    }
   }
   return my_n2;
 }
@@ -986,6 +1019,236 @@ __device__ bool lds_jacobi(T* sar, T* sai, T* sur, T* sui, JacobiScratch<T, DE /
   return conv;
 }
 
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_seq(F& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// v of lane l ^ M, M < 16, by DPP moves: quad_perm (M = 1, 2, 3), row_half_mirror (7) and row_mirror
+// (15) within the 16-lane rows, and their products.
+template <int CTRL, typename T>
+__device__ __forceinline__ T dpp_any(T v) {
+  if constexpr (sizeof(T) == 8) {
+    return dpp_mov<CTRL>(v);
+  } else {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+  }
+}
+template <int M, typename T>
+__device__ __forceinline__ T xor_lane(T v) {
+  static_assert(M >= 0 && M < 16, "within a row of 16 lanes");
+  if constexpr (M == 0) return v;
+  else if constexpr (M == 1) return dpp_any<0xB1>(v);
+  else if constexpr (M == 2) return dpp_any<0x4E>(v);
+  else if constexpr (M == 3) return dpp_any<0x1B>(v);
+  else if constexpr (M < 8) return dpp_any<0x141>(xor_lane<7 ^ M>(v));
+  else return dpp_any<0x140>(xor_lane<15 ^ M>(v));
+}
+
+// 1 / x and 1 / sqrt(x) of a positive normal number: the hardware estimate and two Newton steps
+// (within about one unit in the last place), a third of the dependent instructions of the exact
+// division and root.
+__device__ __forceinline__ double rcp_nr(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ double rsq_nr(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+
+// Cyclic two-sided Jacobi of a DE x DE matrix (DE = 2, 4, 8, 16) on DE lanes, in registers.  Lane j
+// holds column j of A and of U, register k the element of row j ^ k, so that with the pairs
+// (j, j ^ r), r = 1 .. DE - 1, of a sweep the diagonal is register 0, the element to annihilate
+// register r, the partner's element of the same row its register k ^ r, and the row rotations act on
+// registers k and k ^ r: every index is a constant and every exchange an xor of the lane.  (In
+// LDS with four barriers per round the 8 x 8 problem was bound by their latency: 8192 of them
+// with vectors and the adjoint's products took 83 us.)  Rotations, exact 2 x 2 blocks and the FP64
+// convergence test are those of the register kernel; G = [[c, conj(g)], [-g, c]], g = s e^{-i phi}.
+// The matrix is read from LDS (sar, sai) and written back with U; lanes lt >= DE of a cluster's
+// group and inactive clusters take part with a zero matrix.  Returns true (lanes lt < DE) when the
+// off-diagonal norm fell below tol2 within max_sweeps sweeps.
+template <typename T, bool CPLX, int DE, bool VEC>
+__device__ bool xor_jacobi(T* sar, T* sai, T* sur, T* sui, double tol2, int max_sweeps, int lt, bool active) {
+  constexpr int LD = DE + 1;
+  const bool mine = active && lt < DE;
+  const int j = lt & (DE - 1);
+  T ar[DE], ai[CPLX ? DE : 1], ur[VEC ? DE : 1], ui[VEC && CPLX ? DE : 1];
+#pragma unroll
+  for (int k = 0; k < DE; ++k) {
+    const int o = (j ^ k) * LD + j;
+    ar[k] = mine ? sar[o] : T(0);
+    if constexpr (CPLX) ai[k] = mine ? sai[o] : T(0);
+    if constexpr (VEC) ur[k] = k == 0 ? T(1) : T(0);
+    if constexpr (VEC && CPLX) ui[k] = T(0);
+  }
+  bool done = !mine, conv = false;
+  for (int sweep = 0;; ++sweep) {
+    double off = 0.0;   // the convergence test in FP64 whatever T
+#pragma unroll
+    for (int k = 1; k < DE; ++k) {
+      off = fma((double)ar[k], (double)ar[k], off);
+      if constexpr (CPLX) off = fma((double)ai[k], (double)ai[k], off);
+    }
+    static_for<log2i(DE)>([&](auto b) { off += xor_lane<(1 << decltype(b)::value)>(off); });
+    if (!done) {
+      if (off <= tol2) { done = true; conv = true; }
+      else if (sweep >= max_sweeps) { done = true; }
+    }
+    if (__all(done ? 1 : 0)) break;
+    static_for<DE - 1>([&](auto rc) {
+      constexpr int r = decltype(rc)::value + 1;
+      constexpr int HB = 1 << log2i(r);                // j < j ^ r where this bit of j is clear
+      const bool isp = (j & HB) == 0;
+      const T dx = xor_lane<r>(ar[0]), ox = xor_lane<r>(ar[r]);
+      const T app = isp ? ar[0] : dx, aqq = isp ? dx : ar[0];
+      const T xr = isp ? ar[r] : ox;                   // a_qp, as lane p holds it, for both lanes
+      T xi = T(0);
+      if constexpr (CPLX) {
+        const T oi = xor_lane<r>(ai[r]);
+        xi = -(isp ? ai[r] : oi);                      // Im a_pq
+      }
+      // r = |a_pq| (an element below `tiny`, or whose square underflows, is left as it is), then
+      // rot_params with the reciprocals that the whole wave waits for done by Newton steps
+      constexpr bool dbl = sizeof(T) == 8;
+      const T tiny = dbl ? T(1e-290) : T(FLT_MIN);
+      T rr, ir, t, c;   // r, 1 / r
+      bool nz;
+      if constexpr (CPLX) {
+        const T r2 = dfma<T>(xr, xr, xi * xi);
+        nz = !(r2 < tiny) && !done;
+        if constexpr (dbl) ir = rsq_nr(nz ? r2 : T(1));
+        else ir = drsq<T>(nz ? r2 : T(1));
+        rr = r2 * ir;
+      } else {
+        rr = fabs(xr);
+        nz = !(rr < tiny) && !done;
+        if constexpr (dbl) ir = rcp_nr(nz ? rr : T(1));
+        else ir = ddiv<T>(T(1), nz ? rr : T(1));
+      }
+      {
+        const T tau = T(0.5) * (aqq - app) * ir;
+        T at = fabs(tau);
+        if constexpr (dbl) {
+          at = at > 1e150 ? 1e150 : at;   // its square must not overflow (a NaN stays)
+          const T v = fma(at, at, 1.0);
+          t = rcp_nr(fma(v, rsq_nr(v), at));
+        } else {
+          t = ddiv<T>(T(1), at + dsqrt<T>(dfma<T>(tau, tau, T(1))));
+        }
+        t = tau >= T(0) ? t : -t;
+        t = nz ? t : T(0);
+        if constexpr (dbl) c = rsq_nr(fma(t, t, 1.0));
+        else c = drsq<T>(dfma<T>(t, t, T(1)));
+        c = nz ? c : T(1);
+      }
+      const T s = t * c;
+      // own column: c own + gam other, gam = -g (lane p) or conj(g) (lane q)
+      T gr, gi = T(0);
+      if constexpr (CPLX) {
+        gr = s * xr * ir;
+        gi = s * xi * ir;
+        gr = isp ? -gr : gr;
+      } else {
+        gr = ((xr < T(0)) == isp) ? s : -s;
+      }
+      const auto cols = [&](auto& vr, auto& vi) {
+#pragma unroll
+        for (int k = 0; k < DE; ++k) {
+          if (k > (k ^ r)) continue;
+          const T xk = xor_lane<r>(vr[k ^ r]), xq = xor_lane<r>(vr[k]);
+          if constexpr (CPLX) {
+            const T yk = xor_lane<r>(vi[k ^ r]), yq = xor_lane<r>(vi[k]);
+            const T nk = dfma<T>(-gi, yk, dfma<T>(gr, xk, c * vr[k])), mk = dfma<T>(gi, xk, dfma<T>(gr, yk, c * vi[k]));
+            const T nq = dfma<T>(-gi, yq, dfma<T>(gr, xq, c * vr[k ^ r])),
+                    mq = dfma<T>(gi, xq, dfma<T>(gr, yq, c * vi[k ^ r]));
+            vr[k] = nk;
+            vi[k] = mk;
+            vr[k ^ r] = nq;
+            vi[k ^ r] = mq;
+          } else {
+            const T nk = dfma<T>(gr, xk, c * vr[k]);
+            vr[k ^ r] = dfma<T>(gr, xq, c * vr[k ^ r]);
+            vr[k] = nk;
+          }
+        }
+      };
+      cols(ar, ai);
+      if constexpr (VEC) cols(ur, ui);
+      // rows i = j ^ k and i ^ r, with lane i's c and gam
+      static_for<DE>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        if constexpr (k < (k ^ r)) {
+          const T ck = xor_lane<k>(c), hr = xor_lane<k>(gr);
+          const T x = ar[k], y = ar[k ^ r];
+          if constexpr (CPLX) {
+            const T hi = xor_lane<k>(gi);
+            const T xi2 = ai[k], yi2 = ai[k ^ r];
+            ar[k] = dfma<T>(hi, yi2, dfma<T>(hr, y, ck * x));
+            ai[k] = dfma<T>(-hi, y, dfma<T>(hr, yi2, ck * xi2));
+            ar[k ^ r] = dfma<T>(hi, xi2, dfma<T>(-hr, x, ck * y));
+            ai[k ^ r] = dfma<T>(-hi, x, dfma<T>(-hr, xi2, ck * yi2));
+          } else {
+            ar[k] = dfma<T>(hr, y, ck * x);
+            ar[k ^ r] = dfma<T>(-hr, x, ck * y);
+          }
+        }
+      });
+      ar[0] = isp ? app - t * rr : aqq + t * rr;
+      ar[r] = nz ? T(0) : ar[r];
+      if constexpr (CPLX) {
+        ai[0] = T(0);
+        ai[r] = nz ? T(0) : ai[r];
+      }
+    });
+  }
+  if (mine) {
+#pragma unroll
+    for (int k = 0; k < DE; ++k) {
+      const int o = (j ^ k) * LD + j;
+      sar[o] = ar[k];
+      if constexpr (CPLX) sai[o] = ai[k];
+      if constexpr (VEC) sur[o] = ur[k];
+      if constexpr (VEC && CPLX) sui[o] = ui[k];
+    }
+  }
+  __syncthreads();
+  return conv;
+}
+
+// Rotation scratch of a kernel: none where the matrix is solved in registers.
+template <typename T, int DE>
+using ScratchFor = JacobiScratch<T, (DE > 16 ? DE / 2 : 1)>;
+
+// Eigenvalues onto the diagonal of (sar, sai), eigenvectors into (sur, sui) when VEC, W >= min(DE, 64)
+// lanes per cluster: registers up to DE = 16, else LDS.
+template <typename T, bool CPLX, int DE, bool VEC, int W>
+__device__ __forceinline__ bool cluster_jacobi(T* sar, T* sai, T* sur, T* sui, ScratchFor<T, DE>& J, double tol2,
+                                               int max_sweeps, int lt, bool active) {
+  if constexpr (DE <= 16) {
+    static_assert(W >= DE, "one lane per column");
+    return xor_jacobi<T, CPLX, DE, VEC>(sar, sai, sur, sui, tol2, max_sweeps, lt, active);
+  } else {
+    if constexpr (VEC) {
+      if (active)
+        for (int idx = lt; idx < DE * DE; idx += W) {
+          const int i = idx / DE, j = idx % DE;
+          sur[i * (DE + 1) + j] = (i == j) ? T(1) : T(0);
+          if constexpr (CPLX) sui[i * (DE + 1) + j] = T(0);
+        }
+      __syncthreads();
+    }
+    return lds_jacobi<T, CPLX, DE, VEC, W>(sar, sai, sur, sui, J, tol2, max_sweeps, lt, active);
+  }
+}
+
 // component k of a packed D x D Hermitian -> (i, j, imaginary?)
 __device__ __forceinline__ void decode_comp(int k, int D, int& i, int& j, bool& im) {
   im = false;
@@ -1090,7 +1353,7 @@ __global__ __launch_bounds__(64) void k_cluster_lds(ClusterArgs<T> A) {
   __shared__ T sai_[CPLX ? G * SZ : 1];
   __shared__ T sur_[VEC ? G * SZ : 1];
   __shared__ T sui_[(VEC && CPLX) ? G * SZ : 1];
-  __shared__ JacobiScratch<T, DE / 2> J_[G];
+  __shared__ ScratchFor<T, DE> J_[G];
   __shared__ T sp_[G * DE];
   const int g = threadIdx.x / W, lt = threadIdx.x % W;
   const int64_t c = (int64_t)blockIdx.x * G + g;
@@ -1106,19 +1369,10 @@ __global__ __launch_bounds__(64) void k_cluster_lds(ClusterArgs<T> A) {
   T n2 = T(0);
   if (active) n2 = lds_assemble<T, CPLX, DE, W>(A, c, lt, A.nu_c, A.ze_c, A.nu_p, A.ze_p, th, true, T(1), sar, sai);
   const T nrm2 = seg_sum<W>(n2);
-  if constexpr (VEC) {
-    if (active) {
-      for (int idx = lt; idx < DE * DE; idx += W) {
-        const int i = idx / DE, j = idx % DE;
-        sur[i * LD + j] = (i == j) ? T(1) : T(0);
-        if constexpr (CPLX) sui[i * LD + j] = T(0);
-      }
-    }
-  }
   __syncthreads();
   // ---- a3: parallel cyclic Jacobi ----
-  const bool conv = lds_jacobi<T, CPLX, DE, VEC, W>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
-                                                    A.max_sweeps, lt, active);
+  const bool conv = cluster_jacobi<T, CPLX, DE, VEC, W>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
+                                                        A.max_sweeps, lt, active);
   if (active && !conv && lt == 0 && A.noconv) atomicAdd(A.noconv, 1ull);
   T lmin = T(INFINITY);
   if (active)
@@ -1263,7 +1517,7 @@ __global__ __launch_bounds__(64) void k_cluster_gen(ClusterArgs<T> A) {
   __shared__ T sai_[CPLX ? G * SZ : 1];
   __shared__ T sur_[VEC ? G * SZ : 1];
   __shared__ T sui_[(VEC && CPLX) ? G * SZ : 1];
-  __shared__ JacobiScratch<T, DEP / 2> J_[G];
+  __shared__ ScratchFor<T, DEP> J_[G];
   __shared__ T sp_[G * DEP];
   const int g = threadIdx.x / W, lt = threadIdx.x % W;
   const int64_t c = (int64_t)blockIdx.x * G + g;
@@ -1283,19 +1537,10 @@ __global__ __launch_bounds__(64) void k_cluster_gen(ClusterArgs<T> A) {
   __syncthreads();
   if (active)
     for (int k = De + lt; k < DEP; k += W) sar[k * LD + k] = T(2) * dsqrt<T>(nrm2) + T(1);   // > every eigenvalue
-  if constexpr (VEC) {
-    if (active) {
-      for (int idx = lt; idx < DEP * DEP; idx += W) {
-        const int i = idx / DEP, j = idx % DEP;
-        sur[i * LD + j] = (i == j) ? T(1) : T(0);
-        if constexpr (CPLX) sui[i * LD + j] = T(0);
-      }
-    }
-  }
   __syncthreads();
   // ---- a3: parallel cyclic Jacobi over DEP (the padding stays decoupled) ----
-  const bool conv = lds_jacobi<T, CPLX, DEP, VEC, W>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
-                                                     A.max_sweeps, lt, active);
+  const bool conv = cluster_jacobi<T, CPLX, DEP, VEC, W>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
+                                                         A.max_sweeps, lt, active);
   if (active && !conv && lt == 0 && A.noconv) atomicAdd(A.noconv, 1ull);
   T lmin = T(INFINITY);
   if (active)
@@ -2795,36 +3040,66 @@ __device__ __forceinline__ void wg_store_planes(D* C, int I, int J, int l, const
   }
 }
 
-// theta_e of a cluster times sc (after subtracting mu on the diagonal) into the slab matrix X (Z form): one
-// row per wave, the lanes along it, only j >= i (the rest by symmetry).  With mu == nullptr only
-// the diagonal is formed and its sum returned (this thread's share).
+// Trace of theta_e (this thread's share).
 template <typename T, bool CPLX, int DE>
-__device__ double wg_assemble(const ClusterArgs<T>& A, int64_t c, double* X, T th, double sc, const double* mu, int tid,
-                              int nth) {
-  constexpr int NB = log2i(DE);
-  const int64_t ho = A.hoff[c];
-  if (mu == nullptr) {
-    double tr = 0.0;
-    for (int i = tid; i < DE; i += nth) {
-      T vr, vi;
-      theta_elem<T, CPLX>(A, c, DE, NB, ho, i, i, th, vr, vi);
-      tr += (double)vr;
-    }
-    return tr;
+__device__ double wg_trace(const ClusterArgs<T>& A, int64_t c, T th, int tid, int nth) {
+  double tr = 0.0;
+  for (int i = tid; i < DE; i += nth) {
+    T vr, vi;
+    theta_elem<T, CPLX>(A, c, DE, log2i(DE), A.hoff[c], i, i, th, vr, vi);
+    tr += (double)vr;
   }
-  const int wave = tid / 64, l = tid % 64;
-  for (int i = wave; i < DE; i += nth / 64)
-    for (int j = i + l; j < DE; j += 64) {
+  return tr;
+}
+
+// X = sc (theta_e - mu) into the slab (Z form): one row per wave at a time, a lane on fixed columns,
+// only j >= i (the rest by symmetry).  With NORMS returns min(||X||_1, ||X||_F), each sum in a fixed
+// order; part: (nth / 64 + 1) DE doubles of LDS.
+template <typename T, bool CPLX, int DE, bool NORMS>
+__device__ double wg_assemble(const ClusterArgs<T>& A, int64_t c, double* X, T th, double sc, double mu, double* part,
+                              double* red, int tid, int nth) {
+  constexpr int NC = DE > 64 ? DE / 64 : 1;   // columns per lane
+  const int64_t ho = A.hoff[c];
+  const int wave = tid / 64, l = tid % 64, nw = nth / 64;
+  double col[NC], n2 = 0.0;
+#pragma unroll
+  for (int t = 0; t < NC; ++t) col[t] = 0.0;
+  for (int i = wave; i < DE; i += nw) {
+    double row = 0.0;
+#pragma unroll
+    for (int t = 0; t < NC; ++t) {
+      const int j = 64 * t + l;
+      if (j < i || j >= DE) continue;
       T vr, vi;
-      theta_elem<T, CPLX>(A, c, DE, NB, ho, i, j, th, vr, vi);
-      if (i == j) {
-        X[i * DE + j] = sc * ((double)vr - *mu);
-      } else {
-        X[i * DE + j] = CPLX ? sc * ((double)vr + (double)vi) : sc * (double)vr;
-        X[j * DE + i] = CPLX ? sc * ((double)vr - (double)vi) : sc * (double)vr;
+      theta_elem<T, CPLX>(A, c, DE, log2i(DE), ho, i, j, th, vr, vi);
+      const double xr = sc * ((double)vr - (i == j ? mu : 0.0));
+      const double xi = CPLX && i != j ? sc * (double)vi : 0.0;
+      X[i * DE + j] = xr + xi;
+      if (i != j) X[j * DE + i] = xr - xi;
+      if constexpr (NORMS) {
+        const double m2 = fma(xr, xr, xi * xi), m = __builtin_amdgcn_sqrt(m2);
+        row += m;
+        col[t] += i != j ? m : 0.0;
+        n2 += i != j ? 2.0 * m2 : m2;
       }
     }
-  return 0.0;
+    if constexpr (NORMS) {
+      row = wave_sum(row);
+      if (l == 0) part[nw * DE + i] = row;
+    }
+  }
+  if constexpr (!NORMS) return 0.0;
+#pragma unroll
+  for (int t = 0; t < NC; ++t)
+    if (64 * t + l < DE) part[wave * DE + 64 * t + l] = col[t];
+  __syncthreads();
+  double rmax = 0.0;
+  for (int i = tid; i < DE; i += nth) {
+    double a = part[nw * DE + i];
+    for (int w = 0; w < nw; ++w) a += part[w * DE + i];
+    rmax = fmax(rmax, a);
+  }
+  return fmin(sqrt(block_sum(n2, red)), block_max(rmax, red));
 }
 
 // Outputs of a cluster whose marginal scale * Y sits in the slab (planes of the upper triangle): own
@@ -3963,60 +4238,60 @@ __global__ __launch_bounds__(64) void k_cluster_tridiag_w(ClusterArgs<double> A)
 //     Gamma_aa = -beta p_a.
 // nu_bar = B^* Y is then the message kernel's gradient stage (Y_f - Tr_{e\f} Y_e).  At beta = 0
 // the cotangent of Q is Y_e = qbar mu_e (the ground projector; gbar must be absent).
-template <typename T, bool CPLX, int DE, int MODE>
+// W lanes per cluster, 64/W clusters per single-wave block.
+template <typename T, bool CPLX, int DE, int MODE, int W>
 __global__ __launch_bounds__(64) void k_cluster_vjp(ClusterArgs<T> A) {
   constexpr int LD = DE + 1;
-  __shared__ T sar[DE * LD];
-  __shared__ T sai[CPLX ? DE * LD : 1];
-  __shared__ T sur[DE * LD];
-  __shared__ T sui[CPLX ? DE * LD : 1];
-  __shared__ T sxr[DE * LD];
-  __shared__ T sxi[CPLX ? DE * LD : 1];
-  __shared__ T str[DE * LD];
-  __shared__ T sti[CPLX ? DE * LD : 1];
-  __shared__ JacobiScratch<T, DE / 2> J;
-  __shared__ T sp[DE];
-  __shared__ T slam[DE];
-  const int64_t c = xcd_cluster(blockIdx.x, A.n);
-  if (c >= A.n) return;
-  const int tid = threadIdx.x;
+  constexpr int G = 64 / W;
+  constexpr int SZ = DE * LD;
+  __shared__ T sar_[G * SZ], sur_[G * SZ], sxr_[G * SZ], str_[G * SZ];
+  __shared__ T sai_[CPLX ? G * SZ : 1], sui_[CPLX ? G * SZ : 1], sxi_[CPLX ? G * SZ : 1], sti_[CPLX ? G * SZ : 1];
+  __shared__ ScratchFor<T, DE> J_[G];
+  __shared__ T sp_[G * DE];
+  __shared__ T slam_[G * DE];
+  const int g = threadIdx.x / W, tid = threadIdx.x % W;
+  const int64_t c = xcd_cluster(blockIdx.x, gridDim.x) * G + g;
+  const bool active = c < A.n;
+  T *sar = sar_ + g * SZ, *sur = sur_ + g * SZ, *sxr = sxr_ + g * SZ, *str = str_ + g * SZ;
+  T *sai = CPLX ? sai_ + g * SZ : sai_, *sui = CPLX ? sui_ + g * SZ : sui_, *sxi = CPLX ? sxi_ + g * SZ : sxi_,
+    *sti = CPLX ? sti_ + g * SZ : sti_;
+  T *sp = sp_ + g * DE, *slam = slam_ + g * DE;
   const bool has_g = (A.gb_c != nullptr || A.gb_p != nullptr);
-  const T nrm2 = wave_sum(lds_assemble<T, CPLX, DE, 64>(A, c, tid, A.nu_c, nullptr, A.nu_p, nullptr, T(0), true,
-                                                        T(1), sar, sai));
-  if (has_g) lds_assemble<T, CPLX, DE, 64>(A, c, tid, A.gb_c, nullptr, A.gb_p, nullptr, T(0), false,
-                                           (T)A.gb_offscale, sxr, sxi);
-  for (int idx = tid; idx < DE * DE; idx += 64) {
-    const int i = idx / DE, j = idx % DE;
-    sur[i * LD + j] = (i == j) ? T(1) : T(0);
-    if constexpr (CPLX) sui[i * LD + j] = T(0);
+  T n2 = T(0);
+  if (active) {
+    n2 = lds_assemble<T, CPLX, DE, W>(A, c, tid, A.nu_c, nullptr, A.nu_p, nullptr, T(0), true, T(1), sar, sai);
+    if (has_g) lds_assemble<T, CPLX, DE, W>(A, c, tid, A.gb_c, nullptr, A.gb_p, nullptr, T(0), false,
+                                            (T)A.gb_offscale, sxr, sxi);
   }
+  const T nrm2 = seg_sum<W>(n2);
   __syncthreads();
-  const bool conv = lds_jacobi<T, CPLX, DE, true, 64>(sar, sai, sur, sui, J, A.tol * A.tol * (double)nrm2,
-                                                      A.max_sweeps, tid, true);
-  if (!conv && tid == 0 && A.noconv) atomicAdd(A.noconv, 1ull);
+  const bool conv = cluster_jacobi<T, CPLX, DE, true, W>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
+                                                         A.max_sweeps, tid, active);
+  if (active && !conv && tid == 0 && A.noconv) atomicAdd(A.noconv, 1ull);
   T lmin = T(INFINITY);
-  for (int k = tid; k < DE; k += 64) {
-    slam[k] = sar[k * LD + k];
-    lmin = fmin(lmin, sar[k * LD + k]);
-  }
-  lmin = wave_min(lmin);
+  if (active)
+    for (int k = tid; k < DE; k += W) {
+      slam[k] = sar[k * LD + k];
+      lmin = fmin(lmin, sar[k * LD + k]);
+    }
+  lmin = seg_min<W>(lmin);
   const T beta = (T)A.beta;
-  lds_weights<T, DE, MODE, 64>(sar, sp, lmin, beta, (T)A.tau_rel * fmax(T(1), dsqrt<T>(nrm2)), tid, true);
+  lds_weights<T, DE, MODE, W>(sar, sp, lmin, beta, (T)A.tau_rel * fmax(T(1), dsqrt<T>(nrm2)), tid, active);
   // rho (or mu) over A
-  lds_rebuild<T, CPLX, DE, 64>(sur, sui, sp, sar, sai, tid);
+  if (active) lds_rebuild<T, CPLX, DE, W>(sur, sui, sp, sar, sai, tid);
   __syncthreads();
-  const int32_t gid = A.gid[c];
-  const T qb = A.qbar ? (T)A.qbar[A.cinst[gid]] : T(0);
+  const int32_t gid = active ? A.gid[c] : 0;
+  const T qb = active && A.qbar ? (T)A.qbar[A.cinst[gid]] : T(0);
   if (MODE == MODE_GIBBS && has_g) {
     // <rho, X>
     T rx = T(0);
-    for (int idx = tid; idx < DE * DE; idx += 64) {
+    for (int idx = tid; active && idx < DE * DE; idx += W) {
       rx = dfma<T>(sar[idx / DE * LD + idx % DE], sxr[idx / DE * LD + idx % DE], rx);
       if constexpr (CPLX) rx = dfma<T>(sai[idx / DE * LD + idx % DE], sxi[idx / DE * LD + idx % DE], rx);
     }
-    rx = wave_sum(rx);
+    rx = seg_sum<W>(rx);
     // Tm = U^H X
-    for (int idx = tid; idx < DE * DE; idx += 64) {
+    for (int idx = tid; active && idx < DE * DE; idx += W) {
       const int a = idx / DE, j = idx % DE;
       T sr = T(0), si = T(0);
       for (int k = 0; k < DE; ++k) {
@@ -4034,7 +4309,7 @@ __global__ __launch_bounds__(64) void k_cluster_vjp(ClusterArgs<T> A) {
     }
     __syncthreads();
     // M = (U^H X) U, then Gamma o M (into X)
-    for (int idx = tid; idx < DE * DE; idx += 64) {
+    for (int idx = tid; active && idx < DE * DE; idx += W) {
       const int a = idx / DE, b = idx % DE;
       T sr = T(0), si = T(0);
       for (int k = 0; k < DE; ++k) {
@@ -4055,7 +4330,7 @@ __global__ __launch_bounds__(64) void k_cluster_vjp(ClusterArgs<T> A) {
     }
     __syncthreads();
     // Tm = U (Gamma o M)
-    for (int idx = tid; idx < DE * DE; idx += 64) {
+    for (int idx = tid; active && idx < DE * DE; idx += W) {
       const int i = idx / DE, b = idx % DE;
       T sr = T(0), si = T(0);
       for (int k = 0; k < DE; ++k) {
@@ -4074,7 +4349,7 @@ __global__ __launch_bounds__(64) void k_cluster_vjp(ClusterArgs<T> A) {
     __syncthreads();
     // Y = Tm U^H + (beta <rho,X> + qbar) rho  (into X)
     const T w = beta * rx + qb;
-    for (int idx = tid; idx < DE * DE; idx += 64) {
+    for (int idx = tid; active && idx < DE * DE; idx += W) {
       const int i = idx / DE, j = idx % DE;
       T sr = T(0), si = T(0);
       for (int k = 0; k < DE; ++k) {
@@ -4092,7 +4367,7 @@ __global__ __launch_bounds__(64) void k_cluster_vjp(ClusterArgs<T> A) {
     }
     __syncthreads();
     // symmetrise (Y is Hermitian up to rounding): keep the upper triangle mirrored
-    for (int idx = tid; idx < DE * DE; idx += 64) {
+    for (int idx = tid; active && idx < DE * DE; idx += W) {
       const int i = idx / DE, j = idx % DE;
       if (i < j) {
         sxr[j * LD + i] = sxr[i * LD + j];
@@ -4101,15 +4376,15 @@ __global__ __launch_bounds__(64) void k_cluster_vjp(ClusterArgs<T> A) {
       if constexpr (CPLX) { if (i == j) sxi[i * LD + i] = T(0); }
     }
     __syncthreads();
-    lds_outputs<T, CPLX, DE, 64>(A, c, tid, gid, sxr, sxi);
+    if (active) lds_outputs<T, CPLX, DE, W>(A, c, tid, gid, sxr, sxi);
   } else {
-    for (int idx = tid; idx < DE * DE; idx += 64) {
+    for (int idx = tid; active && idx < DE * DE; idx += W) {
       const int i = idx / DE, j = idx % DE;
       sxr[i * LD + j] = qb * sar[i * LD + j];
       if constexpr (CPLX) sxi[i * LD + j] = qb * sai[i * LD + j];
     }
     __syncthreads();
-    lds_outputs<T, CPLX, DE, 64>(A, c, tid, gid, sxr, sxi);
+    if (active) lds_outputs<T, CPLX, DE, W>(A, c, tid, gid, sxr, sxi);
   }
 }
 

@@ -76,6 +76,7 @@ struct CBucket {
   int block = 64;     // threads per block (register kernels)
   int W = 64;         // FP32 iterations: lanes per cluster (1 = register kernel, else LDS kernel)
   int W64 = 64;       // FP64 iterations
+  int Wit = 64;       // FP32 accelerated iterations, which return no value (0: W, picked by the caller or tuner)
   double tuned_us = 0.0;
   int64_t n = 0;
   int mb_child = -1;  // message bucket of the children (dimension Dc)
@@ -273,6 +274,26 @@ inline int comps_of(int D, bool cplx) { return cplx ? D * D : D * (D + 1) / 2; }
 // ------------------------------------------------------------------------------------------
 // problem construction
 // ------------------------------------------------------------------------------------------
+
+// Launch shape of a bucket until the autotuner or the caller picks one: the first compiled, except for
+// 8 x 8 clusters, where the lanes kernel (W = 8) is faster until one lane per cluster fills the chip.
+// Gibbs pass, us, W = 1 / 8 / 16 (complex double has no W = 1): real float 1022 clusters 37 / 17 / 15,
+// 8190 37 / 19 / 24, 32766 40 / 44 / 69; real double 1022 80 / 25 / 23, 8190 80 / 28 / 40, 32766 86 /
+// 78 / 130; complex float 1022 77 / 27 / 24, 16382 77 / 48 / 76; complex double 1022 - / 40 / 37,
+// 16382 - / 90 / 156.  Float evaluations that return a value keep W = 1: F_beta is the float
+// arithmetic's there, and another order of the rotations rounds it differently.
+int default_shape(int De, int Dc, int64_t n, bool dbl, bool cplx) {
+  int shapes[8];
+  const int k = cluster_shapes(De, Dc, dbl, cplx, MODE_GIBBS, shapes);
+  if (k == 0) return 1;
+  if (De == 8) {
+    const int want = n <= 2048 ? 16 : (n <= (dbl ? 32768 : 24576) ? 8 : 1);
+    for (int i = 0; i < k; ++i)
+      if (shapes[i] == want) return want;
+    if (want == 1) return 8;
+  }
+  return shapes[0];
+}
 
 lrh_status build(const lrh_problem_desc* d, lrh_problem_s* P) {
   if (!d) return fail(LRH_E_INVALID, "null problem description");
@@ -530,10 +551,11 @@ lrh_status build(const lrh_problem_desc* d, lrh_problem_s* P) {
     P->cb[b].h_gid.push_back((int32_t)g);
   }
   for (auto& B : P->cb) {
+    B.n = (int64_t)B.h_gid.size();
     int shapes[8];
     if (cluster_shapes(B.De, B.Dc, false, P->cplx, MODE_GIBBS, shapes) > 0) B.W = shapes[0];
-    if (cluster_shapes(B.De, B.Dc, true, P->cplx, MODE_GIBBS, shapes) > 0) B.W64 = shapes[0];
-    B.n = (int64_t)B.h_gid.size();
+    B.W64 = default_shape(B.De, B.Dc, B.n, true, P->cplx);
+    B.Wit = default_shape(B.De, B.Dc, B.n, false, P->cplx);
     for (int32_t g : B.h_gid) {
       B.maxch = std::max<int>(B.maxch, (int)children[g].size());
       B.maxpar = std::max<int>(B.maxpar, (int)parents[g].size());
@@ -1007,13 +1029,14 @@ template <> double default_tol<float>() { return 4.0 * 1.1920928955078125e-07; }
 template <> double default_tol<double>() { return 4.0 * 2.220446049250313e-16; }
 
 // The bucket's chosen shape if it is compiled for this precision / mode, else the first that is.
-int shape_for(const lrh_problem_s* P, const CBucket& B, bool dbl, int mode) {
+// value: the pass returns dual values.
+int shape_for(const lrh_problem_s* P, const CBucket& B, bool dbl, int mode, bool value = true) {
   int shapes[8];
   const int n = cluster_shapes(B.De, B.Dc, dbl, P->cplx, mode, shapes);
   if (mode == MODE_CERTIFY)
     for (int i = 0; i < n; ++i)
       if (shapes[i] == 2) return 2;   // eigenvalues only: tridiagonalisation whenever compiled
-  const int want = dbl ? B.W64 : B.W;
+  const int want = dbl ? B.W64 : (value || B.Wit == 0 ? B.W : B.Wit);
   for (int i = 0; i < n; ++i)
     if (shapes[i] == want) return want;
   return n > 0 ? shapes[0] : 64;
@@ -1093,10 +1116,10 @@ ClusterArgs<T> pass_args(lrh_problem_s* P, const CBucket& B, const T* nu, const 
 
 template <typename T>
 lrh_status cluster_pass(lrh_problem_s* P, const T* nu, const T* ze, double theta, int mode, double beta,
-                        T* marg, hipStream_t s, const FusedParams* tab = nullptr) {
+                        T* marg, hipStream_t s, const FusedParams* tab = nullptr, bool value = true) {
   for (const CBucket& B : P->cb) {
     ClusterArgs<T> a = pass_args<T>(P, B, nu, ze, theta, beta, marg, tab);
-    HIP_TRY(launch_cluster<T>(a, P->cplx, mode, B.block, shape_for(P, B, sizeof(T) == 8, mode), s));
+    HIP_TRY(launch_cluster<T>(a, P->cplx, mode, B.block, shape_for(P, B, sizeof(T) == 8, mode, value), s));
   }
   return LRH_OK;
 }
@@ -1223,7 +1246,7 @@ lrh_status nesterov_plain(lrh_problem_s* P, T* nu, T* ze, lrh_nesterov_state* st
   if (st != LRH_OK) return st;
   for (int j = 0; j < n_iter; ++j) {
     const double th = stt->theta;
-    if ((st = cluster_pass<T>(P, nu, ze, th, MODE_GIBBS, stt->beta, nullptr, s)) != LRH_OK) return st;
+    if ((st = cluster_pass<T>(P, nu, ze, th, MODE_GIBBS, stt->beta, nullptr, s, nullptr, false)) != LRH_OK) return st;
     for (const MBucket& M : P->mb) {
       MsgArgs<T> a = msg_args<T>(P, M);
       a.nu = nu + M.offset;
@@ -1403,7 +1426,7 @@ template <typename T>
 lrh_status table_enqueue(lrh_problem_s* P, T* nu, T* ze, int n, hipStream_t s) {
   lrh_status st;
   for (int j = 0; j < n; ++j) {
-    if ((st = cluster_pass<T>(P, nu, ze, 0.0, MODE_GIBBS, 0.0, nullptr, s, P->fp + j)) != LRH_OK) return st;
+    if ((st = cluster_pass<T>(P, nu, ze, 0.0, MODE_GIBBS, 0.0, nullptr, s, P->fp + j, false)) != LRH_OK) return st;
     for (const MBucket& M : P->mb) {
       MsgArgs<T> a = msg_args<T>(P, M);
       a.nu = nu + M.offset;
@@ -1653,6 +1676,7 @@ lrh_status autotune_t(lrh_problem_s* P, const char* cache, hipStream_t s) {
     const std::string key = shape_key(B, P->cplx, prec);
     const bool dbl = sizeof(T) == 8;
     int& Wsel = dbl ? B.W64 : B.W;
+    if (!dbl) B.Wit = 0;
     auto it = cached.find(key);
     if (it != cached.end()) {
       B.block = it->second.first;
@@ -2067,6 +2091,7 @@ lrh_status lrh_set_shape(lrh_problem p, int32_t De, int32_t block, int32_t W, ui
     if (!ok) return fail(LRH_E_UNSUPPORTED, "launch shape not compiled for this bucket");
     B.block = block;
     (dbl ? B.W64 : B.W) = W;
+    if (!dbl) B.Wit = 0;
     any = true;
   }
   if (!any) return fail(LRH_E_INVALID, "no cluster bucket with that dimension");

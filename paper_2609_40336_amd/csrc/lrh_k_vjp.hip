@@ -5,29 +5,28 @@ namespace lrh {
 
 hipError_t launch_cluster_vjp(const ClusterArgs<double>& a, bool cplx, int mode, hipStream_t s) {
   if (a.n == 0) return hipSuccess;
-  const dim3 g((unsigned)a.n), b(64);
-#define VJP_CASE(DE)                                                                                   \
-  if (a.De == DE) {                                                                                    \
-    if (mode == MODE_GIBBS) {                                                                          \
-      if (cplx) hipLaunchKernelGGL((k_cluster_vjp<double, true, DE, MODE_GIBBS>), g, b, 0, s, a);      \
-      else hipLaunchKernelGGL((k_cluster_vjp<double, false, DE, MODE_GIBBS>), g, b, 0, s, a);          \
-    } else {                                                                                           \
-      if (cplx) hipLaunchKernelGGL((k_cluster_vjp<double, true, DE, MODE_GROUND>), g, b, 0, s, a);     \
-      else hipLaunchKernelGGL((k_cluster_vjp<double, false, DE, MODE_GROUND>), g, b, 0, s, a);         \
-    }                                                                                                  \
-    return hipGetLastError();                                                                          \
+  const dim3 b(64);
+  // lanes per cluster: one per column up to D = 16 (the eigensolver in registers), else a whole wave
+#define VJP_LAUNCH(DE, CPLX, W)                                                                             \
+  {                                                                                                         \
+    const dim3 g((unsigned)((a.n + 64 / W - 1) / (64 / W)));                                                \
+    if (mode == MODE_GIBBS) hipLaunchKernelGGL((k_cluster_vjp<double, CPLX, DE, MODE_GIBBS, W>), g, b, 0, s, a); \
+    else hipLaunchKernelGGL((k_cluster_vjp<double, CPLX, DE, MODE_GROUND, W>), g, b, 0, s, a);              \
+    return hipGetLastError();                                                                               \
   }
-  VJP_CASE(2)
-  VJP_CASE(4)
-  VJP_CASE(8)
-  VJP_CASE(16)
-  VJP_CASE(32)
-  if (a.De == 64 && !cplx) {
-    if (mode == MODE_GIBBS) hipLaunchKernelGGL((k_cluster_vjp<double, false, 64, MODE_GIBBS>), g, b, 0, s, a);
-    else hipLaunchKernelGGL((k_cluster_vjp<double, false, 64, MODE_GROUND>), g, b, 0, s, a);
-    return hipGetLastError();
+#define VJP_CASE(DE, W)                    \
+  if (a.De == DE) {                        \
+    if (cplx) VJP_LAUNCH(DE, true, W)      \
+    else VJP_LAUNCH(DE, false, W)          \
   }
+  VJP_CASE(2, 2)
+  VJP_CASE(4, 4)
+  VJP_CASE(8, 8)
+  VJP_CASE(16, 16)
+  VJP_CASE(32, 64)
+  if (a.De == 64 && !cplx) VJP_LAUNCH(64, false, 64)
 #undef VJP_CASE
+#undef VJP_LAUNCH
   return hipErrorInvalidValue;
 }
 
