@@ -2000,26 +2000,26 @@ constexpr int kF64Squarings = 2;   // float-message path: squarings kept in FP64
 // four products,
 //     a6 = (y3 + b2 y2 + b1 y)^2 + r3 y3 + r2 y2 + r1 y,   p = (a6 + s3 y3 + s2 y2 + s1 y + s0) a6
 //          + t2 y2 + t1 y + 1,    y2 = y y, y3 = y y2,
-// kappa chosen to make the leading coefficient one.  Double messages: error 1.2e-14 on |x| <= 0.9
+// kappa chosen to make the leading coefficient one.  Double messages: error 1.2e-15 on |x| <= 0.75
 // (a degree-12 Taylor polynomial takes five products and has 2e-14 on |x| <= 1/2); float messages:
-// 3.9e-9 on |x| <= 2.4 (degree-8 Taylor: four products, 5.4e-9 on |x| <= 1/2).
+// 3.5e-10 on |x| <= 2 (degree-8 Taylor: four products, 5.4e-9 on |x| <= 1/2).
 template <typename T>
 struct ExpPoly;
 template <>
 struct ExpPoly<double> {
-  static constexpr double kMax = 0.9, kappa = 0.18882898470408857303, b2 = 0.58464362112354427638,
-                          b1 = 0.6831284791247130648, r3 = -0.023881684476552449845, r2 = 1.9385928716127867965,
-                          r1 = 1.0589551634691213031, s3 = 3.4831354272642447593, s2 = 1.7307059423721896079,
-                          s1 = 4.8156775029998268864, s0 = 8.0579615953395820167, t2 = -11.579710521939010742,
-                          t1 = -3.2372228833013124739;
+  static constexpr double kMax = 0.75, kappa = 0.18890286463643001186, b2 = 0.57937322089049180036,
+                          b1 = 0.68740475750695858833, r3 = -0.0226260036235939413, r2 = 1.9368132151596933149,
+                          r1 = 1.0421080289587672922, s3 = 3.4844151622963205626, s2 = 1.7202447934751227396,
+                          s1 = 4.8466204810446821081, s0 = 8.0545185343475532364, t2 = -11.530985678296578198,
+                          t1 = -3.0999524658049970433;
 };
 template <>
 struct ExpPoly<float> {
-  static constexpr double kMax = 2.4, kappa = 0.18744074848716354881, b2 = 0.6860333548991685841,
-                          b1 = 0.60433167933303673257, r3 = -0.050660677725442783478, r2 = 1.9738009571293383397,
-                          r1 = 1.3925347923639631316, s3 = 3.4378842818474047335, s2 = 1.9047025547120234848,
-                          s1 = 4.2055893558107449546, s0 = 8.0977661592032409989, t2 = -12.50518558919466365,
-                          t1 = -5.9414018746586668523;
+  static constexpr double kMax = 2.0, kappa = 0.18794616950573157704, b2 = 0.65021617857486515946,
+                          b1 = 0.63003546334208741425, r3 = -0.041946904752406594485, r2 = 1.9627374771981224214,
+                          r1 = 1.275754058867548299, s3 = 3.4605728791216365827, s2 = 1.8490087327993450794,
+                          s1 = 4.4199263533945864807, s0 = 8.0978796474404292981, t2 = -12.219931968853453924,
+                          t1 = -5.0102304112831659341;
 };
 
 // The number of squarings for a matrix of spectral radius at most nrm: the least s >= 0 with
@@ -2560,8 +2560,8 @@ __global__ __launch_bounds__(64) void k_cluster_expm(ClusterArgs<T> A) {
   }
   // Float messages: the squarings after the first kF64Squarings run on the FP32 matrix cores.  A
   // relative rounding error e in Y_j acts on rho like an error of about 2^(s-j) e in
-  // X = beta (theta - mu); ||X|| is between kMax/2 and kMax (2.4) times 2^s, so after two squarings
-  // the float ones perturb X by at most about ||X|| u_32 / 5 times the product's error growth, the
+  // X = beta (theta - mu); ||X|| is between 1 and 2 (kMax) times 2^s, so after two squarings
+  // the float ones perturb X by at most about ||X|| u_32 / 4 times the product's error growth, the
   // order of what the float rounding of the messages themselves puts on X (beta ||nu|| u_32).  The
   // polynomial and the first squarings, where the error would be amplified most, stay in FP64.
   int n64 = s;
@@ -3016,6 +3016,106 @@ __device__ __forceinline__ void wg_product(const S* X, const S* Y, unsigned char
   __syncthreads();
 }
 
+// Plan of a float squaring: all tiles of 32 x 32 in one pass at D = 256 (half the accumulators of a
+// double product), else as WgPlan.
+template <int DE>
+struct WgPlan32 : WgPlan<DE> {};
+template <>
+struct WgPlan32<256> {
+  static constexpr int waves = 12, passes = 1, na = 6, nb = 6, nblk = 12, ks = 16;
+  static constexpr int ab[12] = {0, 0, 1, 1, 2, 2, 3, 3, 4, 4, 5, 5}, bb[12] = {0, 1, 0, 1, 2, 3, 2, 3, 4, 5, 4, 5};
+};
+// block index of A fragment q (q < na), or B fragment q - na
+template <int DE>
+__device__ __forceinline__ int wg_block32(int wave, int q) {
+  if constexpr (DE == 256) {
+    const int a = q < 6 ? q : q - 6;
+    return wg_block<256>(wave + 12 * (a >> 1), (q < 6 ? 0 : 2) + (a & 1));
+  } else {
+    return wg_block<DE>(wave, q);
+  }
+}
+
+// One step of wg_square32: when the stage in `st` has landed, the next one's loads into `nxt`, then the
+// products (`restrict`: see wg_step).
+template <typename Fill, typename Prod>
+__device__ __forceinline__ void wg_square32_step(const unsigned char* __restrict__ st, unsigned char* __restrict__ nxt,
+                                                 Fill&& fill, Prod&& products) {
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+  __syncthreads();
+  fill(nxt);
+  products(reinterpret_cast<const float*>(st));
+}
+
+// epi(I, J, re, im): block (I, J) of Y Y for a Hermitian float matrix in two planes (real: one), on the
+// FP32 matrix cores, four real products per complex one.  A 2 x 2 tile on the diagonal also gives
+// its block below it.  Buffers and barriers as wg_product.
+template <bool CPLX, int DE, typename Epi>
+__device__ __forceinline__ void wg_square32(const float* Y, unsigned char* s0, unsigned char* s1, int tid, Epi&& epi) {
+  using P = WgPlan32<DE>;
+  constexpr int NPL = CPLX ? 2 : 1;
+  constexpr int KS = 2 * P::ks < DE / 2 ? 2 * P::ks : DE / 2;
+  constexpr int NK = DE / KS, CPR = DE / 4, NINS = KS * CPR / 64, PB = KS * DE * 4, NF = P::na + P::nb;
+  static_assert(NINS * 64 == KS * CPR && NK % 2 == 0 && KS % 4 == 0 && NPL * PB <= wg_stage_bytes<CPLX, DE>(), "stages");
+  constexpr int64_t DD = (int64_t)DE * DE;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64;
+  const int lr = l >> 4, lc = l & 15;
+  const auto fill = [&](int k0, unsigned char* buf) {
+#pragma unroll
+    for (int pl = 0; pl < NPL; ++pl)
+#pragma unroll 2
+      for (int q = wave; q < NINS; q += P::waves) {
+        const int ch = q * 64 + l, k = ch / CPR, cp = ch % CPR;
+        const float* src = Y + pl * DD + (int64_t)(k0 + k) * DE + (cp ^ (wg_swizzle<float, DE>(k) * 4)) * 4;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                         (__attribute__((address_space(3))) void*)(buf + pl * PB + q * 1024), 16, 0, 0);
+      }
+  };
+  int blk[NF], off[NF];
+#pragma unroll
+  for (int q = 0; q < NF; ++q) {
+    blk[q] = wg_block32<DE>(wave, q);
+    off[q] = lr * DE + 16 * (blk[q] ^ wg_swizzle<float, DE>(lr)) + lc;
+  }
+  mfma_f32x4 cr[P::nblk], ci[CPLX ? P::nblk : 1];
+#pragma unroll
+  for (int b = 0; b < P::nblk; ++b) {
+    cr[b] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (CPLX) ci[b] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const auto products = [&](const float* __restrict__ st) {
+#pragma unroll 2
+    for (int kk = 0; kk < KS / 4; ++kk) {
+      float r[NF], n[NF];
+#pragma unroll
+      for (int q = 0; q < NF; ++q) {
+        r[q] = st[off[q] + kk * 4 * DE];
+        if constexpr (CPLX) n[q] = st[off[q] + kk * 4 * DE + KS * DE];
+      }
+#pragma unroll
+      for (int b = 0; b < P::nblk; ++b) {
+        const int ia = P::ab[b], ib = P::na + P::bb[b];
+        cr[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(r[ia], r[ib], cr[b], 0, 0, 0);
+        if constexpr (CPLX) {
+          cr[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(n[ia], n[ib], cr[b], 0, 0, 0);
+          ci[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(r[ia], n[ib], ci[b], 0, 0, 0);
+          ci[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(-n[ia], r[ib], ci[b], 0, 0, 0);
+        }
+      }
+    }
+  };
+  fill(0, s0);
+#pragma unroll 1
+  for (int K = 0; K < NK; K += 2) {
+    wg_square32_step(s0, s1, [&](unsigned char* nxt) { fill((K + 1) * KS, nxt); }, products);
+    wg_square32_step(s1, s0, [&](unsigned char* nxt) { if (K + 2 < NK) fill((K + 2) * KS, nxt); }, products);
+  }
+#pragma unroll
+  for (int b = 0; b < P::nblk; ++b) epi(blk[P::ab[b]], blk[P::na + P::bb[b]], cr[b], CPLX ? ci[b] : cr[b]);
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // the epilogues' stores, before anyone stages them
+  __syncthreads();
+}
+
 // Elements (i, j) of block (I, J), I <= J, to the slab matrix C: v, and u to (j, i).
 template <typename D, typename S, int DE>
 __device__ __forceinline__ void wg_store(D* C, int I, int J, int l, const S (&v)[4], const S (&u)[4]) {
@@ -3027,16 +3127,22 @@ __device__ __forceinline__ void wg_store(D* C, int I, int J, int l, const S (&v)
     if (I != J) C[j * DE + i] = (D)u[r];
   }
 }
-// The final result instead as planes R and N of its upper triangle, as the outputs read it.
-template <bool CPLX, typename D, typename S, int DE>
+// The result instead as planes R and N: of its upper triangle, as the outputs read it, or (FULL) whole.
+template <bool CPLX, typename D, typename S, int DE, bool FULL = false>
 __device__ __forceinline__ void wg_store_planes(D* C, int I, int J, int l, const S (&v)[4], const S (&u)[4]) {
   constexpr int64_t DD = (int64_t)DE * DE;
   const int j = 16 * J + (l & 15);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int i = 16 * I + WgMfma<S>::row(l, r);
-    C[i * DE + j] = CPLX ? (D)(S(0.5) * (v[r] + u[r])) : (D)v[r];
-    if constexpr (CPLX) C[DD + i * DE + j] = (D)(S(0.5) * (v[r] - u[r]));
+    const D re = CPLX ? (D)(S(0.5) * (v[r] + u[r])) : (D)v[r];
+    C[i * DE + j] = re;
+    if (FULL && I != J) C[j * DE + i] = re;
+    if constexpr (CPLX) {
+      const D im = (D)(S(0.5) * (v[r] - u[r]));
+      C[DD + i * DE + j] = im;
+      if (FULL && I != J) C[DD + j * DE + i] = -im;
+    }
   }
 }
 
@@ -3174,8 +3280,11 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
     const int64_t c = c0 + xcd_cluster(blockIdx.x, nc);
     double *M = base + 3 * NPL * DD, *Q = base + 4 * NPL * DD;
     // ---- a1/a2: X = -kappa beta (theta_e - mu) at eta ----
-    const double mu = block_sum(wg_assemble<T, CPLX, DE>(A, c, X, th, 0.0, nullptr, tid, nth), red) / DE;
-    wg_assemble<T, CPLX, DE>(A, c, X, th, -EP::kappa * beta, &mu, tid, nth);
+    constexpr bool kF32 = std::is_same<T, float>::value;
+    const double mu = block_sum(wg_trace<T, CPLX, DE>(A, c, th, tid, nth), red) / DE;
+    const double xn = wg_assemble<T, CPLX, DE, kF32>(A, c, X, th, -EP::kappa * beta, mu,
+                                                     reinterpret_cast<double*>(stage0), red, tid, nth);
+    __builtin_amdgcn_s_waitcnt(0x0f70);
     __syncthreads();
     // ---- X^2, its column sums (per block row, in the still unused Q) and the scale; see k_cluster_expm ----
     wg_product<double, CPLX, DE, true>(X, X, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
@@ -3206,7 +3315,20 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
       for (int b = 0; b < NB16; ++b) a += Q[b * DE + i];
       rmax = fmax(rmax, a);
     }
-    const int s = __builtin_amdgcn_readfirstlane(expm_squarings<T>(sqrt(block_max(rmax, red)) * (1.0 / EP::kappa)));
+    int n32 = 0;   // squarings in FP32, see below
+    if constexpr (kF32) {
+      int e;
+      const double x = xn * (1.0 / EP::kappa), m = frexp(x, &e);   // x = m 2^e, 0.5 <= m < 1
+      if (m == 0.5) --e;                                           // the least e with x <= 2^e
+      n32 = x > 8.0 && x <= 0x1p199 ? e - 3 : 0;                   // (a NaN norm: none)
+    }
+    n32 = __builtin_amdgcn_readfirstlane(n32);
+    // (at least one double squaring before the float ones)
+    const int s = max(__builtin_amdgcn_readfirstlane(expm_squarings<T>(sqrt(block_max(rmax, red)) * (1.0 / EP::kappa))),
+                      n32 > 0 ? n32 + 1 : 0);
+    const int n64 = s - n32;
+    float* fa = reinterpret_cast<float*>(P2);
+    float* fb = reinterpret_cast<float*>(P3);
     const double f1 = ldexp(1.0, -s), f2 = ldexp(1.0, -2 * s);
     // ---- E0 = p(X / kappa) (see ExpPoly): P3 = X P2, M = b(X) ----
     // (offsets of register r: o of (i, j), ot of (j, i))
@@ -3255,13 +3377,12 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
       wg_store<double, double, DE>(Q, I, J, l, v, u);
       wg_store<double, double, DE>(P3, I, J, l, wv, wu);
     });
-    // Float messages: the squarings after the first kF64Squarings in FP32 (see k_cluster_expm), on
-    // float matrices in the slabs of X^2 and X^3, which the polynomial no longer needs by then; the
-    // product before them writes its result in float.  The last product of all writes planes.
-    constexpr bool kF32 = std::is_same<T, float>::value;
-    const int n64 = kF32 ? (s < kF64Squarings ? s : kF64Squarings) : s;
-    float* fa = reinterpret_cast<float*>(P2);
-    float* fb = reinterpret_cast<float*>(P3);
+    // Float messages: the last n32 squarings in FP32, a relative rounding error e in the first of them
+    // acting on X = beta (theta - mu) like 2^n32 e: 2^n32 stays below ||X|| / 4, ||X|| the smaller of X's
+    // 1- and Frobenius norms, so that this stays near what the float rounding of the messages already
+    // puts on X.  They work on two float planes in the slabs of X^2 and X^3, which the polynomial no
+    // longer needs by then; the double squaring before them writes these.  The last product of all
+    // writes planes too.
     double trp = 0.0;   // this thread's share of the trace
     wg_product<double, CPLX, DE, false>(P3, Q, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
       double v[4], u[4];
@@ -3298,7 +3419,7 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
           u[r] = scale * au[r];
           if (I == J && 4 * r + (l >> 4) == (l & 15)) trp += v[r];
         }
-        if (last32) wg_store<float, double, DE>(fa, I, J, l, v, u);
+        if (last32) wg_store_planes<CPLX, float, double, DE, true>(fa, I, J, l, v, u);
         else if (j + 1 == s) wg_store_planes<CPLX, double, double, DE>(Q, I, J, l, v, u);
         else wg_store<double, double, DE>(Q, I, J, l, v, u);
       });
@@ -3312,16 +3433,23 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
       for (int j = n64; j < s; ++j) {
         const float scale = (float)(1.0 / (t * t));
         trp = 0.0;
-        wg_product<float, CPLX, DE, true>(fa, fa, stage0, stage1, tid, [&](int I, int J, mfma_f32x4 av, mfma_f32x4 au) {
-          float v[4], u[4];
+        wg_square32<CPLX, DE>(fa, stage0, stage1, tid, [&](int I, int J, mfma_f32x4 ar, mfma_f32x4 ai) {
+          // (the blocks of a 2 x 2 tile on the diagonal stand as computed, the others are mirrored)
+          const bool mirror = I < J && !(DE == 256 && I / 2 == J / 2);
+          const int jj = 16 * J + (l & 15);
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            v[r] = scale * av[r];
-            u[r] = scale * au[r];
-            if (I == J && 4 * (l >> 4) + r == (l & 15)) trp += (double)v[r];
+            const int i = 16 * I + 4 * (l >> 4) + r;
+            const float vr = scale * ar[r];
+            if (i == jj) trp += (double)vr;
+            fb[i * DE + jj] = vr;
+            if (mirror) fb[jj * DE + i] = vr;
+            if constexpr (CPLX) {
+              const float vi = i == jj ? 0.f : scale * ai[r];
+              fb[DD + i * DE + jj] = vi;
+              if (mirror) fb[DD + jj * DE + i] = -vi;
+            }
           }
-          if (j + 1 == s) wg_store_planes<CPLX, float, float, DE>(fb, I, J, l, v, u);
-          else wg_store<float, float, DE>(fb, I, J, l, v, u);
         });
         float* tp = fa;
         fa = fb;
