@@ -70,34 +70,64 @@ __global__ __launch_bounds__(256) void k_msg(MsgArgs<T> A) {
   }
 }
 
+// (s, e) <- (s, e) + (t, f), e the rounding errors of s so far
+__device__ __forceinline__ void add_comp(double& s, double& e, double t, double f) {
+  const double r = s + t, z = r - s;
+  e += ((s - (r - z)) + (t - z)) + f;
+  s = r;
+}
+__device__ __forceinline__ void wave_sum_comp(double& s, double& e) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) add_comp(s, e, __shfl_xor(s, o, 64), __shfl_xor(e, o, 64));
+}
+
 // Per-instance sums over the contiguous library-cluster range of each instance, in a fixed
-// order (strided per-thread partial sums, then a fixed tree): bitwise reproducible.
-__global__ __launch_bounds__(256) void k_reduce(const double* scal, const int64_t* ptr, double* out,
-                                                const double* scal2, double* out2, double* q_best,
-                                                int32_t* improved, double* q_hist) {
-  __shared__ double sh[256];
-  __shared__ double sh2[256];
+// order (strided per-thread partial sums, then a fixed tree that carries its rounding errors, so that
+// the sum of tens of thousands of clusters is good to its last place): bitwise reproducible.  One workgroup
+// per instance; a thread keeps 8 loads in flight (one at a time, the 20 470 clusters of a single
+// chain took 21 us).
+constexpr int kReduceThreads = 512;
+template <bool TWO>
+__global__ __launch_bounds__(kReduceThreads) void k_reduce(const double* scal, const int64_t* ptr, double* out,
+                                                           const double* scal2, double* out2, double* q_best,
+                                                           int32_t* improved, double* q_hist) {
+  constexpr int NT = kReduceThreads, U = 8;
+  __shared__ double sh[NT / 64], she[NT / 64], sh2[NT / 64];
   const int i = blockIdx.x;
   const int64_t a = ptr[i], b = ptr[i + 1];
   double s = 0.0, s2 = 0.0;
-  for (int64_t j = a + threadIdx.x; j < b; j += 256) {
-    s += scal[j];
-    if (scal2) s2 += scal2[j];
-  }
-  sh[threadIdx.x] = s;
-  sh2[threadIdx.x] = s2;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      sh[threadIdx.x] += sh[threadIdx.x + w];
-      sh2[threadIdx.x] += sh2[threadIdx.x + w];
+  for (int64_t j = a + threadIdx.x; j < b; j += (int64_t)NT * U) {
+    double v[U], w[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int64_t o = j + (int64_t)k * NT;
+      v[k] = o < b ? scal[o] : 0.0;
+      w[k] = TWO && o < b ? scal2[o] : 0.0;
     }
-    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      s += v[k];
+      if constexpr (TWO) s2 += w[k];
+    }
   }
+  double e = 0.0;
+  wave_sum_comp(s, e);
+  if constexpr (TWO) s2 = wave_sum(s2);
+  if (threadIdx.x % 64 == 0) {
+    sh[threadIdx.x / 64] = s;
+    she[threadIdx.x / 64] = e;
+    sh2[threadIdx.x / 64] = s2;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    const double q = sh[0];
+    double q = 0.0, qe = 0.0, q2 = 0.0;
+    for (int k = 0; k < NT / 64; ++k) {
+      add_comp(q, qe, sh[k], she[k]);
+      q2 += sh2[k];
+    }
+    if (isfinite(q)) q += qe;   // (an infinite sum has no error term)
     if (out) out[i] = q;
-    if (out2) out2[i] = sh2[0];
+    if (out2) out2[i] = q2;
     if (q_hist) q_hist[i] = q;
     if (q_best) {
       const bool better = q > q_best[i];
@@ -338,8 +368,12 @@ hipError_t launch_reduce(const double* scal, const int64_t* inst_ptr, int64_t n_
                          const double* scal2, double* out2, double* q_best, int32_t* improved,
                          double* q_hist, hipStream_t s) {
   if (n_inst == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_reduce, dim3((unsigned)n_inst), dim3(256), 0, s, scal, inst_ptr, out, scal2,
-                     out2, q_best, improved, q_hist);
+  if (scal2)
+    hipLaunchKernelGGL((k_reduce<true>), dim3((unsigned)n_inst), dim3(kReduceThreads), 0, s, scal, inst_ptr, out, scal2,
+                       out2, q_best, improved, q_hist);
+  else
+    hipLaunchKernelGGL((k_reduce<false>), dim3((unsigned)n_inst), dim3(kReduceThreads), 0, s, scal, inst_ptr, out, scal2,
+                       out2, q_best, improved, q_hist);
   return hipGetLastError();
 }
 
