@@ -1492,6 +1492,10 @@ lrh_status nesterov_t(lrh_problem_s* P, T* nu, T* ze, lrh_nesterov_state* stt, i
 // adjoint drivers
 // ------------------------------------------------------------------------------------------
 
+const char* const kNoAdjoint = "adjoint of complex clusters with D_e = 64 or of D_e > 64";
+// dimensions that launch_cluster_vjp takes
+bool vjp_supported(int De, bool cplx) { return De == 2 || De == 4 || De == 8 || De == 16 || De == 32 || (De == 64 && !cplx); }
+
 lrh_status ensure_adjoint(lrh_problem_s* P) {
   lrh_status st = ensure_work<double>(P, false);
   if (st != LRH_OK) return st;
@@ -1530,7 +1534,7 @@ lrh_status vjp_pass(lrh_problem_s* P, const double* nu, double beta, const doubl
     a.marg_off = P->marg_off;
     a.beta = beta;
     hipError_t e = launch_cluster_vjp(a, P->cplx, beta > 0 ? MODE_GIBBS : MODE_GROUND, s);
-    if (e == hipErrorInvalidValue) return fail(LRH_E_UNSUPPORTED, "adjoint of complex clusters with D_e = 64 or of D_e > 64");
+    if (e == hipErrorInvalidValue) return fail(LRH_E_UNSUPPORTED, kNoAdjoint);
     HIP_TRY(e);
   }
   return LRH_OK;
@@ -1562,7 +1566,11 @@ lrh_status unrolled_grad(lrh_problem_s* P, const double* nu0, double beta, doubl
   lrh_status st = ensure_adjoint(P);
   if (st != LRH_OK) return st;
   const int64_t n = std::max<int64_t>(P->nu_len, 1);
-  const int64_t need = 7 + (int64_t)T;
+  // what the reverse sweep cannot do is refused with or without one
+  for (const CBucket& B : P->cb)
+    if (!vjp_supported(B.De, P->cplx)) return fail(LRH_E_UNSUPPORTED, kNoAdjoint);
+  const bool reverse = pbar != nullptr || nu0bar != nullptr;
+  const int64_t need = 5 + (reverse ? (int64_t)T : 0);
   if ((int64_t)P->adj_ws.size() < need) {
     for (int64_t i = (int64_t)P->adj_ws.size(); i < need; ++i) {
       double* b = nullptr;
@@ -1573,19 +1581,20 @@ lrh_status unrolled_grad(lrh_problem_s* P, const double* nu0, double beta, doubl
   double* nu = P->adj_ws[0];
   double* ze = P->adj_ws[1];
   double* a = P->adj_ws[2];
-  double* b = P->adj_ws[3];
-  double* btot = P->adj_ws[4];
-  double* gb = P->adj_ws[5];
-  double* eb = P->adj_ws[6];
-  auto eta = [&](int k) { return P->adj_ws[7 + k]; };
+  double* btot = P->adj_ws[3];
+  double* gb = P->adj_ws[4];
+  auto eta = [&](int k) { return P->adj_ws[5 + k]; };
   if (nu0) HIP_TRY(launch_copy<double>(nu, nu0, P->nu_len, s));
   else HIP_TRY(hipMemsetAsync(nu, 0, n * sizeof(double), s));
   HIP_TRY(launch_copy<double>(ze, nu, P->nu_len, s));
   std::vector<double> ths;
   double th = 1.0;
   for (int k = 0; k < T; ++k) {
-    HIP_TRY(launch_extrap<double>(eta(k), nu, ze, th, P->nu_len, s));
-    if ((st = cluster_pass<double>(P, eta(k), nullptr, 0.0, MODE_GIBBS, beta, nullptr, s)) != LRH_OK) return st;
+    if (reverse) HIP_TRY(launch_extrap<double>(eta(k), nu, ze, th, P->nu_len, s));
+    // (without a reverse sweep the points are extrapolated in the loads, to the same bits)
+    if ((st = cluster_pass<double>(P, reverse ? eta(k) : nu, reverse ? nullptr : ze, reverse ? 0.0 : th, MODE_GIBBS,
+                                   beta, nullptr, s)) != LRH_OK)
+      return st;
     for (const MBucket& M : P->mb) {
       MsgArgs<double> m = msg_args<double>(P, M);
       m.nu = nu + M.offset;
@@ -1600,21 +1609,33 @@ lrh_status unrolled_grad(lrh_problem_s* P, const double* nu0, double beta, doubl
   // B_T = Q(nu^T) and its cotangent
   if ((st = cluster_pass<double>(P, nu, nullptr, 0.0, MODE_GROUND, 0.0, nullptr, s)) != LRH_OK) return st;
   HIP_TRY(launch_reduce(P->scal, P->inst_ptr, P->n_inst, bound, nullptr, nullptr, nullptr, nullptr, nullptr, s));
+  if (!reverse) return LRH_OK;
   const double* qb = qbar ? qbar : P->ones;
   if ((st = vjp_pass(P, nu, 0.0, qb, nullptr, 1.0, s)) != LRH_OK) return st;
   if ((st = scatter_grad(P, a, s)) != LRH_OK) return st;
   if ((st = param_bar(P, pbar, 0, s)) != LRH_OK) return st;
-  HIP_TRY(hipMemsetAsync(b, 0, n * sizeof(double), s));
+  HIP_TRY(hipMemsetAsync(btot, 0, n * sizeof(double), s));
+  // cotangents of step T - 1 (of the start when T = 0: nu0_bar = a), then each reverse step forms those
+  // of the step before it
+  auto before = [&](int k) { return k > 0 ? ths[k - 1] : 1.0; };
+  if (T > 0) HIP_TRY(launch_adj_pre(a, btot, btot, gb, ths[T - 1], 1.0 / (ths[T - 1] * L), P->nu_len, s));
+  else HIP_TRY(launch_copy<double>(btot, a, P->nu_len, s));
   for (int k = T - 1; k >= 0; --k) {
-    const double t = ths[k];
-    HIP_TRY(launch_adj_pre(a, b, btot, gb, t, 1.0 / (t * L), P->nu_len, s));
     if ((st = vjp_pass(P, eta(k), beta, nullptr, gb, 1.0, s)) != LRH_OK) return st;
-    if ((st = scatter_grad(P, eb, s)) != LRH_OK) return st;
     if ((st = param_bar(P, pbar, 1, s)) != LRH_OK) return st;
-    HIP_TRY(launch_adj_post(a, b, btot, eb, t, P->nu_len, s));
+    for (const MBucket& M : P->mb) {
+      MsgArgs<double> m = msg_args<double>(P, M);
+      m.nu = a + M.offset;
+      m.ze = btot + M.offset;
+      m.grad = gb + M.offset;
+      m.theta = ths[k];
+      m.alpha = before(k);
+      m.inv_thL = 1.0 / (before(k) * L);
+      HIP_TRY(launch_msg<double>(m, MSG_ADJOINT, 256, s));
+    }
   }
   if (nu0bar) {
-    HIP_TRY(launch_adj_pre(a, b, nu0bar, gb, 1.0, 0.0, P->nu_len, s));  // nu0_bar = a + b
+    HIP_TRY(launch_copy<double>(nu0bar, btot, P->nu_len, s));   // nu0_bar = a + b
     if (packed && (st = to_packed(P, nu0bar, s)) != LRH_OK) return st;
   }
   return LRH_OK;

@@ -18,6 +18,8 @@ enum MsgMode : int {
   MSG_GRAD = 0,      // grad[m] = R[child] - T[m]
   MSG_SUBGRAD = 1,   // nu_best copy where improved, then nu += alpha g
   MSG_NESTEROV = 2,  // zeta += g / (theta L); nu = (1 - theta) nu + theta zeta
+  MSG_ADJOINT = 3,   // reverse of a step, eta_bar = g: nu = a <- (1 - theta)(a + g), ze = b_tot <-
+                     // alpha a + theta g + b_tot (alpha, inv_thL: the step before it), grad = b_tot inv_thL
 };
 
 // Packed Hermitian layout: upper-triangle real parts (row-major), then the imaginary
@@ -159,11 +161,9 @@ hipError_t launch_set_params(double* h, const double* hfix, const int64_t* pc_ho
 hipError_t launch_param_bar(double* out, int accumulate, int64_t n_params, const int64_t* pp_ptr,
                             const int64_t* pp_yoff, const int64_t* pp_doff, const int32_t* pp_D, const double* Y,
                             const double* dterm, bool cplx, hipStream_t s);
-// reverse Nesterov step on message vectors (length n)
+// btot = b + th a, gbar = btot invthL on message vectors (length n): the first reverse step
 hipError_t launch_adj_pre(const double* a, const double* b, double* btot, double* gbar, double th, double invthL,
                           int64_t n, hipStream_t s);
-hipError_t launch_adj_post(double* a, double* b, const double* btot, const double* etabar, double th, int64_t n,
-                           hipStream_t s);
 // x[i] = scale * (uniform(-1, 1) from a 64-bit mix of (seed, i))
 template <typename T>
 hipError_t launch_fill_noise(T* x, int64_t n, double scale, uint32_t seed, hipStream_t s);

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) void k_msg(MsgArgs<T> A) {
     const int64_t o = k * A.M + m;
     tv[kk] = A.Tm[o];
     if constexpr (MODE != MSG_GRAD) nv[kk] = nsrc[o];
-    if constexpr (MODE == MSG_NESTEROV) zv[kk] = zsrc[o];
+    if constexpr (MODE == MSG_NESTEROV || MODE == MSG_ADJOINT) zv[kk] = zsrc[o];
   }
 #pragma unroll
   for (int kk = 0; kk < CH; ++kk) {
@@ -61,6 +61,13 @@ __global__ __launch_bounds__(256) void k_msg(MsgArgs<T> A) {
         const T v = nv[kk];
         if (copy_best) A.nu_best[o] = v;
         A.nu[o] = dfma<T>(alpha, g, v);
+      } else if constexpr (MODE == MSG_ADJOINT) {
+        // the reverse of an accelerated step from eta_bar = g, and the cotangents of the one before it
+        const T a = (T(1) - th) * (nv[kk] + g);
+        const T bt = dfma<T>(alpha, a, dfma<T>(th, g, zv[kk]));
+        A.nu[o] = a;
+        A.ze[o] = bt;
+        A.grad[o] = bt * ith;
       } else {
         const T z = dfma<T>(g, ith, zv[kk]);
         A.ze[o] = z;
@@ -235,14 +242,6 @@ __global__ __launch_bounds__(256) void k_adj_pre(const double* a, const double* 
   gbar[i] = bt * invthL;
 }
 
-__global__ __launch_bounds__(256) void k_adj_post(double* a, double* b, const double* btot, const double* etabar,
-                                                  double th, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  a[i] = (1.0 - th) * (a[i] + etabar[i]);
-  b[i] = fma(th, etabar[i], btot[i]);
-}
-
 __global__ __launch_bounds__(256) void k_scale_offdiag(double* x, int64_t M, int D, int cplx, double f) {
   const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= M) return;
@@ -355,6 +354,7 @@ hipError_t launch_msg(const MsgArgs<T>& a, int mode, int block, hipStream_t s) {
     constexpr int CH = decltype(chc)::value;
     if (mode == MSG_GRAD) hipLaunchKernelGGL((k_msg<T, MSG_GRAD, CH>), g, b, 0, s, a);
     else if (mode == MSG_SUBGRAD) hipLaunchKernelGGL((k_msg<T, MSG_SUBGRAD, CH>), g, b, 0, s, a);
+    else if (mode == MSG_ADJOINT) hipLaunchKernelGGL((k_msg<T, MSG_ADJOINT, CH>), g, b, 0, s, a);
     else hipLaunchKernelGGL((k_msg<T, MSG_NESTEROV, CH>), g, b, 0, s, a);
   };
   if (ch == 3) go(std::integral_constant<int, 3>{});
@@ -438,13 +438,6 @@ hipError_t launch_adj_pre(const double* a, const double* b, double* btot, double
                           int64_t n, hipStream_t s) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_adj_pre, dim3(grid_for(n, 256)), dim3(256), 0, s, a, b, btot, gbar, th, invthL, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_adj_post(double* a, double* b, const double* btot, const double* etabar, double th, int64_t n,
-                           hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_adj_post, dim3(grid_for(n, 256)), dim3(256), 0, s, a, b, btot, etabar, th, n);
   return hipGetLastError();
 }
 

@@ -633,7 +633,9 @@ def _autograd():
         @staticmethod
         def forward(ctx, params, problem, beta, T, L):
             problem.set_params(params.detach())
-            b, _, _ = problem.unrolled_bound_grad(beta, T, L)
+            # the value alone: no gradient is asked for, so no reverse sweep runs
+            b = problem.qbuf()
+            lrh_unrolled_bound_grad(problem.h, None, beta, 0.0 if L is None else float(L), T, None, b)
             ctx.problem, ctx.beta, ctx.T, ctx.L = problem, beta, T, L
             ctx.save_for_backward(params.detach())
             return b
