@@ -1224,27 +1224,32 @@ __device__ bool xor_jacobi(T* sar, T* sai, T* sur, T* sui, double tol2, int max_
 }
 
 // Rotation scratch of a kernel: none where the matrix is solved in registers.
-template <typename T, int DE>
-using ScratchFor = JacobiScratch<T, (DE > 16 ? DE / 2 : 1)>;
+template <typename T, int DE, bool REG>
+using ScratchFor = JacobiScratch<T, (REG && DE <= 16 ? 1 : DE / 2)>;
 
-// Eigenvalues onto the diagonal of (sar, sai), eigenvectors into (sur, sui) when VEC, W >= min(DE, 64)
-// lanes per cluster: registers up to DE = 16, else LDS.
-template <typename T, bool CPLX, int DE, bool VEC, int W>
-__device__ __forceinline__ bool cluster_jacobi(T* sar, T* sai, T* sur, T* sui, ScratchFor<T, DE>& J, double tol2,
+// The identity into (sur, sui) where the solve is in LDS, before the barrier that precedes it.
+template <typename T, bool CPLX, int DE, bool VEC, int W, bool REG>
+__device__ __forceinline__ void init_vectors(T* sur, T* sui, int lt, bool active) {
+  if constexpr (VEC && !(REG && DE <= 16)) {
+    if (active)
+      for (int idx = lt; idx < DE * DE; idx += W) {
+        const int i = idx / DE, j = idx % DE;
+        sur[i * (DE + 1) + j] = (i == j) ? T(1) : T(0);
+        if constexpr (CPLX) sui[i * (DE + 1) + j] = T(0);
+      }
+  }
+}
+
+// Eigenvalues onto the diagonal of (sar, sai), eigenvectors into (sur, sui) when VEC (see
+// init_vectors), W >= min(DE, 64) lanes per cluster: in registers up to DE = 16 (REG), else LDS.  Float passes that return values
+// keep the LDS order of rotations, whose rounding is part of the value.
+template <typename T, bool CPLX, int DE, bool VEC, int W, bool REG>
+__device__ __forceinline__ bool cluster_jacobi(T* sar, T* sai, T* sur, T* sui, ScratchFor<T, DE, REG>& J, double tol2,
                                                int max_sweeps, int lt, bool active) {
-  if constexpr (DE <= 16) {
+  if constexpr (REG && DE <= 16) {
     static_assert(W >= DE, "one lane per column");
     return xor_jacobi<T, CPLX, DE, VEC>(sar, sai, sur, sui, tol2, max_sweeps, lt, active);
   } else {
-    if constexpr (VEC) {
-      if (active)
-        for (int idx = lt; idx < DE * DE; idx += W) {
-          const int i = idx / DE, j = idx % DE;
-          sur[i * (DE + 1) + j] = (i == j) ? T(1) : T(0);
-          if constexpr (CPLX) sui[i * (DE + 1) + j] = T(0);
-        }
-      __syncthreads();
-    }
     return lds_jacobi<T, CPLX, DE, VEC, W>(sar, sai, sur, sui, J, tol2, max_sweeps, lt, active);
   }
 }
@@ -1353,7 +1358,8 @@ __global__ __launch_bounds__(64) void k_cluster_lds(ClusterArgs<T> A) {
   __shared__ T sai_[CPLX ? G * SZ : 1];
   __shared__ T sur_[VEC ? G * SZ : 1];
   __shared__ T sui_[(VEC && CPLX) ? G * SZ : 1];
-  __shared__ ScratchFor<T, DE> J_[G];
+  constexpr bool REG = sizeof(T) == 8 || MODE == MODE_GIBBS;   // (float Gibbs values: the register kernel's)
+  __shared__ ScratchFor<T, DE, REG> J_[G];
   __shared__ T sp_[G * DE];
   const int g = threadIdx.x / W, lt = threadIdx.x % W;
   const int64_t c = (int64_t)blockIdx.x * G + g;
@@ -1369,9 +1375,10 @@ __global__ __launch_bounds__(64) void k_cluster_lds(ClusterArgs<T> A) {
   T n2 = T(0);
   if (active) n2 = lds_assemble<T, CPLX, DE, W>(A, c, lt, A.nu_c, A.ze_c, A.nu_p, A.ze_p, th, true, T(1), sar, sai);
   const T nrm2 = seg_sum<W>(n2);
+  init_vectors<T, CPLX, DE, VEC, W, REG>(sur, sui, lt, active);
   __syncthreads();
   // ---- a3: parallel cyclic Jacobi ----
-  const bool conv = cluster_jacobi<T, CPLX, DE, VEC, W>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
+  const bool conv = cluster_jacobi<T, CPLX, DE, VEC, W, REG>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
                                                         A.max_sweeps, lt, active);
   if (active && !conv && lt == 0 && A.noconv) atomicAdd(A.noconv, 1ull);
   T lmin = T(INFINITY);
@@ -1517,7 +1524,8 @@ __global__ __launch_bounds__(64) void k_cluster_gen(ClusterArgs<T> A) {
   __shared__ T sai_[CPLX ? G * SZ : 1];
   __shared__ T sur_[VEC ? G * SZ : 1];
   __shared__ T sui_[(VEC && CPLX) ? G * SZ : 1];
-  __shared__ ScratchFor<T, DEP> J_[G];
+  constexpr bool REG = sizeof(T) == 8;
+  __shared__ ScratchFor<T, DEP, REG> J_[G];
   __shared__ T sp_[G * DEP];
   const int g = threadIdx.x / W, lt = threadIdx.x % W;
   const int64_t c = (int64_t)blockIdx.x * G + g;
@@ -1537,9 +1545,10 @@ __global__ __launch_bounds__(64) void k_cluster_gen(ClusterArgs<T> A) {
   __syncthreads();
   if (active)
     for (int k = De + lt; k < DEP; k += W) sar[k * LD + k] = T(2) * dsqrt<T>(nrm2) + T(1);   // > every eigenvalue
+  init_vectors<T, CPLX, DEP, VEC, W, REG>(sur, sui, lt, active);
   __syncthreads();
   // ---- a3: parallel cyclic Jacobi over DEP (the padding stays decoupled) ----
-  const bool conv = cluster_jacobi<T, CPLX, DEP, VEC, W>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
+  const bool conv = cluster_jacobi<T, CPLX, DEP, VEC, W, REG>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
                                                          A.max_sweeps, lt, active);
   if (active && !conv && lt == 0 && A.noconv) atomicAdd(A.noconv, 1ull);
   T lmin = T(INFINITY);
@@ -4374,7 +4383,7 @@ __global__ __launch_bounds__(64) void k_cluster_vjp(ClusterArgs<T> A) {
   constexpr int SZ = DE * LD;
   __shared__ T sar_[G * SZ], sur_[G * SZ], sxr_[G * SZ], str_[G * SZ];
   __shared__ T sai_[CPLX ? G * SZ : 1], sui_[CPLX ? G * SZ : 1], sxi_[CPLX ? G * SZ : 1], sti_[CPLX ? G * SZ : 1];
-  __shared__ ScratchFor<T, DE> J_[G];
+  __shared__ ScratchFor<T, DE, true> J_[G];
   __shared__ T sp_[G * DE];
   __shared__ T slam_[G * DE];
   const int g = threadIdx.x / W, tid = threadIdx.x % W;
@@ -4392,8 +4401,9 @@ __global__ __launch_bounds__(64) void k_cluster_vjp(ClusterArgs<T> A) {
                                             (T)A.gb_offscale, sxr, sxi);
   }
   const T nrm2 = seg_sum<W>(n2);
+  init_vectors<T, CPLX, DE, true, W, true>(sur, sui, tid, active);
   __syncthreads();
-  const bool conv = cluster_jacobi<T, CPLX, DE, true, W>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
+  const bool conv = cluster_jacobi<T, CPLX, DE, true, W, true>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
                                                          A.max_sweeps, tid, active);
   if (active && !conv && tid == 0 && A.noconv) atomicAdd(A.noconv, 1ull);
   T lmin = T(INFINITY);
