@@ -253,6 +253,119 @@ __device__ __forceinline__ void ptrace_reg(const HMat<T, CPLX, DE>& Rh, HMat<T, 
 // One cyclic sweep of two-sided Jacobi rotations over all pairs (p < q), row-cyclic order.
 // Branch-free: a pair with a_pq == 0 gets the identity rotation (t = 0, c = 1, s = 0), so the
 // unrolled sweep is straight-line code.
+// 1 / x and 1 / sqrt(x) of a positive normal number: the hardware estimate and two Newton steps
+// (within about one unit in the last place), a third of the dependent instructions of the exact
+// division and root.
+__device__ __forceinline__ double rcp_nr(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ double rsq_nr(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+
+// A rotation that annihilates a_pq = r e^{i phi}: t, c and g = s e^{-i phi} (real: gi unused), from
+// the diagonal and a_pq, by Newton reciprocals.  An element below 1e-290 (or, complex, whose square
+// is) is left as it is: nz false, t = 0, c = 1, g = 0.
+template <bool CPLX>
+__device__ __forceinline__ void rot_nr(double app, double aqq, double xr, double xi, bool on, bool& nz, double& rr, double& t,
+                                       double& c, double& gr, double& gi) {
+  double ir;   // 1 / r
+  if constexpr (CPLX) {
+    const double r2 = fma(xr, xr, xi * xi);
+    nz = !(r2 < 1e-290) && on;
+    ir = rsq_nr(nz ? r2 : 1.0);
+    rr = r2 * ir;
+  } else {
+    rr = fabs(xr);
+    nz = !(rr < 1e-290) && on;
+    ir = rcp_nr(nz ? rr : 1.0);
+  }
+  const double tau = 0.5 * (aqq - app) * ir;
+  double at = fabs(tau);
+  at = at > 1e150 ? 1e150 : at;   // its square must not overflow (a NaN stays)
+  const double v = fma(at, at, 1.0);
+  t = rcp_nr(fma(v, rsq_nr(v), at));
+  t = tau >= 0.0 ? t : -t;
+  t = nz ? t : 0.0;
+  c = nz ? rsq_nr(fma(t, t, 1.0)) : 1.0;
+  const double s = t * c;
+  if constexpr (CPLX) {
+    gr = s * xr * ir;
+    gi = -(s * xi * ir);
+  } else {
+    gr = xr < 0.0 ? -s : s;
+    gi = 0.0;
+  }
+}
+
+// A sweep of the register solver in double for D = 2, 4: rounds r = 1 .. D - 1 of the disjoint pairs
+// (p, p ^ r), whose rotations are computed together before they are applied, so that their chains of dependent
+// instructions overlap.  (Row by row with exact divisions and roots, a wave of 4 x 4 complex
+// clusters took 15 us whatever its size: latency.)  G = [[c, conj(g)], [-g, c]].
+template <bool CPLX, int D, bool VEC>
+__device__ __forceinline__ void jacobi_sweep_rounds(HMat<double, CPLX, D>& A, double (&ur)[D][D], double (&ui)[D][D]) {
+#pragma unroll
+  for (int r = 1; r < D; ++r) {
+    bool nz[D / 2];
+    double rr[D / 2], t[D / 2], c[D / 2], gr[D / 2], gi[D / 2];
+    int n = 0;
+#pragma unroll
+    for (int p = 0; p < D; ++p) {
+      const int q = p ^ r;
+      if (q < p) continue;
+      rot_nr<CPLX>(A.re(p, p), A.re(q, q), A.re(p, q), A.im(p, q), true, nz[n], rr[n], t[n], c[n], gr[n], gi[n]);
+      ++n;
+    }
+    n = 0;
+#pragma unroll
+    for (int p = 0; p < D; ++p) {
+      const int q = p ^ r;
+      if (q < p) continue;
+      const double cc = c[n], g_r = gr[n], g_i = gi[n];
+      const double app = A.re(p, p), aqq = A.re(q, q), xr = A.re(p, q), xi = A.im(p, q);
+#pragma unroll
+      for (int k = 0; k < D; ++k) {
+        if (k == p || k == q) continue;
+        // column update (A G); rows follow by Hermitian symmetry
+        const double pr = A.re(k, p), pi = A.im(k, p), qr = A.re(k, q), qi = A.im(k, q);
+        if constexpr (CPLX) {
+          A.set(k, p, fma(g_i, qi, fma(-g_r, qr, cc * pr)), fma(-g_i, qr, fma(-g_r, qi, cc * pi)));
+          A.set(k, q, fma(g_i, pi, fma(g_r, pr, cc * qr)), fma(-g_i, pr, fma(g_r, pi, cc * qi)));
+        } else {
+          A.set(k, p, fma(-g_r, qr, cc * pr), 0.0);
+          A.set(k, q, fma(g_r, pr, cc * qr), 0.0);
+        }
+      }
+      A.set(p, p, app - t[n] * rr[n], 0.0);
+      A.set(q, q, aqq + t[n] * rr[n], 0.0);
+      A.set(p, q, nz[n] ? 0.0 : xr, nz[n] ? 0.0 : xi);
+      if constexpr (VEC) {
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+          const double pr = ur[k][p], qr = ur[k][q];
+          if constexpr (CPLX) {
+            const double pi = ui[k][p], qi = ui[k][q];
+            ur[k][p] = fma(g_i, qi, fma(-g_r, qr, cc * pr));
+            ui[k][p] = fma(-g_i, qr, fma(-g_r, qi, cc * pi));
+            ur[k][q] = fma(g_i, pi, fma(g_r, pr, cc * qr));
+            ui[k][q] = fma(-g_i, pr, fma(g_r, pi, cc * qi));
+          } else {
+            ur[k][p] = fma(-g_r, qr, cc * pr);
+            ur[k][q] = fma(g_r, pr, cc * qr);
+          }
+        }
+      }
+      ++n;
+    }
+  }
+}
+
+// A sweep in float, and at D = 8 in double (where the registers are full): pairs row by row.  (The dual
+// values of float evaluations carry this order's rounding, so it stays.)
 template <typename T, bool CPLX, int D, bool VEC>
 __device__ __forceinline__ void jacobi_sweep_reg(HMat<T, CPLX, D>& A, T (&ur)[D][D], T (&ui)[D][D]) {
 #pragma unroll
@@ -574,10 +687,10 @@ __device__ void cluster_reg_body(const ClusterArgs<T>& A, int64_t c) {
   for (int sweep = 0; sweep <= A.max_sweeps; ++sweep) {
     if (offdiag2<T, CPLX, DE>(H) <= tol2) { conv = true; break; }
     if (sweep == A.max_sweeps) break;
-    if constexpr (VEC) jacobi_sweep_reg<T, CPLX, DE, true>(H, ur, ui);
-    else {
-      T dr[DE][DE], di[DE][DE];
-      jacobi_sweep_reg<T, CPLX, DE, false>(H, dr, di);
+    if constexpr (std::is_same<T, double>::value && DE <= 4) {
+      jacobi_sweep_rounds<CPLX, DE, VEC>(H, ur, ui);
+    } else {
+      jacobi_sweep_reg<T, CPLX, DE, VEC>(H, ur, ui);
     }
   }
   if (!conv && A.noconv) atomicAdd(A.noconv, 1ull);
@@ -1048,20 +1161,6 @@ __device__ __forceinline__ T xor_lane(T v) {
   else if constexpr (M == 3) return dpp_any<0x1B>(v);
   else if constexpr (M < 8) return dpp_any<0x141>(xor_lane<7 ^ M>(v));
   else return dpp_any<0x140>(xor_lane<15 ^ M>(v));
-}
-
-// 1 / x and 1 / sqrt(x) of a positive normal number: the hardware estimate and two Newton steps
-// (within about one unit in the last place), a third of the dependent instructions of the exact
-// division and root.
-__device__ __forceinline__ double rcp_nr(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(fma(-x, y, 1.0), y, y);
-  return fma(fma(-x, y, 1.0), y, y);
-}
-__device__ __forceinline__ double rsq_nr(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
 }
 
 // Cyclic two-sided Jacobi of a DE x DE matrix (DE = 2, 4, 8, 16) on DE lanes, in registers.  Lane j
