@@ -2411,12 +2411,12 @@ __device__ __forceinline__ void xpoly(XMat<NB, CPLX>& D, double a, double b, dou
 }
 
 template <typename T, bool CPLX, int DE>
-__global__ __launch_bounds__(64) void k_cluster_expm(ClusterArgs<T> A) {
+__device__ __forceinline__ void cluster_expm_body(const ClusterArgs<T>& A, int64_t block) {
   constexpr int LD = DE + 1;
   constexpr int NB = DE / 16;
   __shared__ T sar[DE * LD];
   __shared__ T sai[CPLX ? DE * LD : 1];
-  const int64_t c = xcd_cluster(blockIdx.x, A.n);
+  const int64_t c = xcd_cluster(block, A.n);
   const int l = threadIdx.x;
   const T th = A.tab ? (T)A.tab->theta_cur : (T)A.theta;
   const double beta = A.tab ? A.tab->beta : A.beta;
@@ -2864,6 +2864,30 @@ __global__ __launch_bounds__(64) void k_cluster_expm(ClusterArgs<T> A) {
       for (int x = 0; x < NR; ++x) sum += y[depL[s][(a << lnr) + x] * LD + depL[s][(b << lnr) + x]];
       A.Tout[(int64_t)k * A.Mc + m] = sum;
     }
+  }
+}
+
+template <typename T, bool CPLX, int DE>
+__global__ __launch_bounds__(64) void k_cluster_expm(ClusterArgs<T> A) {
+  cluster_expm_body<T, CPLX, DE>(A, blockIdx.x);
+}
+
+// The 16-dimensional clusters with the bonds and sites below them in one launch (float): the first
+// nbe + nbs workgroups are those of the pair kernel, whose waves wait on memory and on one
+// another's rotations most of the time (26 000 plaquettes: 14 + 5 us as launches of their own), the
+// rest one wave per 16-dimensional cluster.  The buckets do not depend on one another.
+template <typename T, bool CPLX>
+__global__ __launch_bounds__(64) void k_cluster_expm16_pair(ClusterArgs<T> A, ClusterArgs<T> E, ClusterArgs<T> S, int nbe,
+                                                            int nbs) {
+  const int b = blockIdx.x;
+  if (b < nbe) {
+    const int64_t c = (int64_t)b * 64 + threadIdx.x;
+    if (c < E.n) cluster_reg_body<T, CPLX, 4, 2, MODE_GIBBS>(E, c);
+  } else if (b < nbe + nbs) {
+    const int64_t c = (int64_t)(b - nbe) * 64 + threadIdx.x;
+    if (c < S.n) cluster_reg_body<T, CPLX, 2, 0, MODE_GIBBS>(S, c);
+  } else {
+    cluster_expm_body<T, CPLX, 16>(A, b - nbe - nbs);
   }
 }
 
@@ -4801,6 +4825,18 @@ static hipError_t launch_cluster_m(const ClusterArgs<T>& a, int block, int W, hi
   return hipGetLastError();
 }
 
+
+// The float Gibbs pass of a 16-dimensional bucket (one wave per cluster) with a bond and a site bucket.
+template <typename T, bool CPLX>
+hipError_t launch_expm16_pair(const ClusterArgs<T>& a, const ClusterArgs<T>& e, const ClusterArgs<T>& st, hipStream_t s) {
+  if (a.De != 16 || e.De != 4 || e.Dc != 2 || st.De != 2 || e.maxch < 1 || e.maxch > 2 || a.fp || e.fp || st.fp)
+    return hipErrorInvalidValue;
+  const int64_t nbe = grid_for(e.n, 64), nbs = grid_for(st.n, 64);
+  if (a.n + nbe + nbs > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_cluster_expm16_pair<T, CPLX>), dim3((unsigned)(a.n + nbe + nbs)), dim3(64), 0, s, a, e, st,
+                     (int)nbe, (int)nbs);
+  return hipGetLastError();
+}
 
 // Entry of the cluster kernels for one (precision, field, mode): explicitly instantiated in
 // one translation unit each, so that the kernel families compile in parallel.

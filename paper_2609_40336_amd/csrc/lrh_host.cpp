@@ -1088,6 +1088,19 @@ ClusterArgs<T> base_args(lrh_problem_s* P, const CBucket& B) {
   return a;
 }
 
+// The bond (4 x 4 with site children) and site buckets when both run as register kernels: one launch
+// takes both.
+struct PairOf { const CBucket* edges = nullptr; const CBucket* sites = nullptr; };
+PairOf pair_of(const lrh_problem_s* P, bool dbl, int mode, bool value) {
+  PairOf r;
+  for (const CBucket& B : P->cb) {
+    if (shape_for(P, B, dbl, mode, value) != 1 || B.n == 0) continue;
+    if (B.De == 4 && B.Dc == 2 && B.maxch >= 1 && B.maxch <= 2) r.edges = &B;
+    if (B.De == 2 && B.Dc == 0) r.sites = &B;
+  }
+  return r.edges && r.sites ? r : PairOf{};
+}
+
 // One plain pass of the cluster kernels over every bucket at (nu, zeta, theta).
 template <typename T>
 ClusterArgs<T> pass_args(lrh_problem_s* P, const CBucket& B, const T* nu, const T* ze, double theta, double beta,
@@ -1117,9 +1130,29 @@ ClusterArgs<T> pass_args(lrh_problem_s* P, const CBucket& B, const T* nu, const 
 template <typename T>
 lrh_status cluster_pass(lrh_problem_s* P, const T* nu, const T* ze, double theta, int mode, double beta,
                         T* marg, hipStream_t s, const FusedParams* tab = nullptr, bool value = true) {
+  const bool dbl = sizeof(T) == 8;
+  const PairOf pr = pair_of(P, dbl, mode, value);
+  // The bonds and sites are small launches bound by latency: one launch for both, in float together
+  // with 16-dimensional clusters (in double the pair's registers would halve that kernel's waves).
+  const CBucket* plaq = nullptr;
+  if (!dbl && pr.edges && mode == MODE_GIBBS)
+    for (const CBucket& B : P->cb)
+      if (B.De == 16 && !plaq && shape_for(P, B, dbl, mode, value) == 0) plaq = &B;
   for (const CBucket& B : P->cb) {
+    if (&B == pr.sites || &B == plaq) continue;   // with the edges
     ClusterArgs<T> a = pass_args<T>(P, B, nu, ze, theta, beta, marg, tab);
-    HIP_TRY(launch_cluster<T>(a, P->cplx, mode, B.block, shape_for(P, B, sizeof(T) == 8, mode, value), s));
+    if (&B == pr.edges) {
+      const ClusterArgs<T> st = pass_args<T>(P, *pr.sites, nu, ze, theta, beta, marg, tab);
+      if constexpr (std::is_same<T, float>::value) {
+        if (plaq) {
+          HIP_TRY(launch_plaquette_pass(pass_args<T>(P, *plaq, nu, ze, theta, beta, marg, tab), a, st, P->cplx, s));
+          continue;
+        }
+      }
+      HIP_TRY(launch_cluster_pair<T>(a, st, P->cplx, mode, B.block, s));
+      continue;
+    }
+    HIP_TRY(launch_cluster<T>(a, P->cplx, mode, B.block, shape_for(P, B, dbl, mode, value), s));
   }
   return LRH_OK;
 }
@@ -1917,14 +1950,22 @@ lrh_status lrh_certify(lrh_problem p, const void* nu, uint32_t flags, double* q_
     lrh_status st = p->dalloc(&p->cert_ws, wsl);
     if (st != LRH_OK) return st;
   }
-  for (const CBucket& B : p->cb) {
+  const PairOf pr = pair_of(p, true, MODE_CERTIFY, true);
+  auto args = [&](const CBucket& B) {
     ClusterArgs<double> a = base_args<double>(p, B);
     a.tol = default_tol<double>();   // certification ignores a loosened iteration tolerance
     a.cert_ws = p->cert_ws;
     if (B.mb_child >= 0) a.nu_c = nu64 + p->mb[B.mb_child].offset;
     if (B.mb_self >= 0) a.nu_p = nu64 + p->mb[B.mb_self].offset;
     a.R = nullptr;
-    HIP_TRY(launch_cluster<double>(a, p->cplx, MODE_CERTIFY, B.block, shape_for(p, B, true, MODE_CERTIFY), stream));
+    return a;
+  };
+  for (const CBucket& B : p->cb) {
+    if (&B == pr.sites) continue;   // with the edges
+    if (&B == pr.edges)
+      HIP_TRY(launch_cluster_pair<double>(args(B), args(*pr.sites), p->cplx, MODE_CERTIFY, B.block, stream));
+    else
+      HIP_TRY(launch_cluster<double>(args(B), p->cplx, MODE_CERTIFY, B.block, shape_for(p, B, true, MODE_CERTIFY), stream));
   }
   HIP_TRY(launch_reduce(p->scal, p->inst_ptr, p->n_inst, q_dev, p->scal2, margin_dev, nullptr, nullptr, nullptr,
                         stream));
@@ -1975,7 +2016,8 @@ lrh_status lrh_certify_noalloc(lrh_problem p, const void* nu, uint32_t flags, do
   const size_t ws_bytes = (size_t)cert_ws_len(p) * sizeof(double);
   double* ws = (ws_bytes > 0 && off + slab_bytes + ws_bytes <= kStaticScratchBytes)
                    ? (double*)(base + off + slab_bytes) : nullptr;
-  for (const CBucket& B : p->cb) {
+  const PairOf pr = pair_of(p, true, MODE_CERTIFY, true);
+  auto args = [&](const CBucket& B) {
     ClusterArgs<double> a = base_args<double>(p, B);
     a.tol = default_tol<double>();
     a.big_scratch = nullptr;
@@ -1987,7 +2029,14 @@ lrh_status lrh_certify_noalloc(lrh_problem p, const void* nu, uint32_t flags, do
     if (B.mb_child >= 0) a.nu_c = nu64 + p->mb[B.mb_child].offset;
     if (B.mb_self >= 0) a.nu_p = nu64 + p->mb[B.mb_self].offset;
     a.R = nullptr;
-    HIP_TRY(launch_cluster<double>(a, p->cplx, MODE_CERTIFY, B.block, shape_for(p, B, true, MODE_CERTIFY), stream));
+    return a;
+  };
+  for (const CBucket& B : p->cb) {
+    if (&B == pr.sites) continue;   // with the edges
+    if (&B == pr.edges)
+      HIP_TRY(launch_cluster_pair<double>(args(B), args(*pr.sites), p->cplx, MODE_CERTIFY, B.block, stream));
+    else
+      HIP_TRY(launch_cluster<double>(args(B), p->cplx, MODE_CERTIFY, B.block, shape_for(p, B, true, MODE_CERTIFY), stream));
   }
   HIP_TRY(launch_reduce(p->scal, p->inst_ptr, p->n_inst, q_dev, p->scal2, margin_dev, nullptr, nullptr, nullptr,
                         stream));

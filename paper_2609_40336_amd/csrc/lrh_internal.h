@@ -144,7 +144,10 @@ constexpr int kTableRows = 65;  // rows of the device parameter table (chunk of 
 struct FusedTable { FusedParams p[kFusedTableMax]; };
 hipError_t launch_set_fused(FusedParams* dst, const FusedTable& v, int n, hipStream_t s);
 hipError_t launch_widen(double* dst, const float* src, int64_t n, hipStream_t s);
-// two-bucket fused/plain launch for 2-local problems: edges (De=4, Dc=2) and sites (De=2)
+// float Gibbs pass of 16-dimensional clusters (one wave each), edges (De=4, Dc=2) and sites (De=2)
+hipError_t launch_plaquette_pass(const ClusterArgs<float>& a, const ClusterArgs<float>& e, const ClusterArgs<float>& st,
+                                 bool cplx, hipStream_t s);
+// two-bucket launch, fused (2-local problems) or plain: edges (De=4, Dc=2) and sites (De=2)
 template <typename T>
 hipError_t launch_cluster_pair(const ClusterArgs<T>& edges, const ClusterArgs<T>& sites, bool cplx,
                                int mode, int block, hipStream_t s);

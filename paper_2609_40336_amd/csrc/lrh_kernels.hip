@@ -153,9 +153,9 @@ __global__ __launch_bounds__(256) void k_widen(double* dst, const float* src, in
   if (i < n) dst[i] = (double)src[i];
 }
 
-// Edges and sites of a 2-local problem in one launch: blocks [0, nbe) take edges, the rest
-// take sites.  Both buckets read only the previous iteration's buffers, so they need no
-// ordering between them.
+// Edges and sites in one launch: blocks [0, nbe) take edges, the rest take sites.  Neither bucket
+// reads what the other writes in a pass (the fused loop: both read only the previous iteration's
+// buffers), so they need no ordering between them.
 template <typename T, bool CPLX, int MODE>
 __global__ __launch_bounds__(256) void k_cluster_pair(ClusterArgs<T> E, ClusterArgs<T> S, int nbe) {
   if ((int)blockIdx.x < nbe) {
@@ -343,6 +343,15 @@ hipError_t launch_cluster(const ClusterArgs<T>& a, bool cplx, int mode, int bloc
               : launch_cluster_mode<T, false, MODE_GROUND>(a, block, W, s);
 }
 
+extern template hipError_t launch_expm16_pair<float, false>(const ClusterArgs<float>&, const ClusterArgs<float>&,
+                                                            const ClusterArgs<float>&, hipStream_t);
+extern template hipError_t launch_expm16_pair<float, true>(const ClusterArgs<float>&, const ClusterArgs<float>&,
+                                                           const ClusterArgs<float>&, hipStream_t);
+hipError_t launch_plaquette_pass(const ClusterArgs<float>& a, const ClusterArgs<float>& e, const ClusterArgs<float>& st,
+                                 bool cplx, hipStream_t s) {
+  return cplx ? launch_expm16_pair<float, true>(a, e, st, s) : launch_expm16_pair<float, false>(a, e, st, s);
+}
+
 template <typename T>
 hipError_t launch_msg(const MsgArgs<T>& a, int mode, int block, hipStream_t s) {
   if (a.M == 0 || a.comps == 0) return hipSuccess;
@@ -403,6 +412,10 @@ hipError_t launch_cluster_pair(const ClusterArgs<T>& e, const ClusterArgs<T>& st
   } else if (mode == MODE_GROUND) {
     if (cplx) hipLaunchKernelGGL((k_cluster_pair<T, true, MODE_GROUND>), g, b, 0, s, e, st, nbe);
     else hipLaunchKernelGGL((k_cluster_pair<T, false, MODE_GROUND>), g, b, 0, s, e, st, nbe);
+  } else if constexpr (std::is_same<T, double>::value) {
+    if (mode != MODE_CERTIFY) return hipErrorInvalidValue;
+    if (cplx) hipLaunchKernelGGL((k_cluster_pair<T, true, MODE_CERTIFY>), g, b, 0, s, e, st, nbe);
+    else hipLaunchKernelGGL((k_cluster_pair<T, false, MODE_CERTIFY>), g, b, 0, s, e, st, nbe);
   } else {
     return hipErrorInvalidValue;
   }
