@@ -3790,6 +3790,219 @@ __global__ __launch_bounds__(256) void k_cluster_tridiag(ClusterArgs<double> A, 
   }
 }
 
+// Certification at De = 64, 128 with the matrix in registers: DE / 16 waves, wave g holding rows
+// j = G e + g (e = 0 .. 15, G = DE / 16), lane l of it columns l + 64 q, so every wave keeps work as the
+// trailing block shrinks and the elements of a vector at a row are one LDS broadcast per wave.  The
+// reflections of tridiag_lambda_min with the rank-2 update applied at once; three barriers each: the
+// row to LDS, the partial products of A v (every wave forms the norm by itself), then w = p - K v by
+// the first wave.  Its bracketing too, 4 DE points a round.
+// In the slab, one column per thread read and written per reflection, the 1018 128 x 128 clusters of a
+// 1024-site chain took 5.0 ms, bound by the latency of its memory traffic, the 64 x 64 ones 1.0 ms; here
+// 2.4 and 0.41 ms, three fifths of it the reflections (3 us each at 128, the chain between the barriers).
+template <bool CPLX, int DE>
+__global__ __launch_bounds__(DE * 4) void k_certify_tridiag(ClusterArgs<double> A) {
+  constexpr int G = DE / 16, NE = 16, NC = DE / 64, NI = CPLX ? NE : 1;
+  static_assert(DE % 64 == 0, "columns l + 64 q");
+  __shared__ double2 sx[2][DE], sw[DE], part[G][DE];
+  __shared__ double dg[DE], e2[DE];
+  __shared__ double red[16];
+  const int tid = threadIdx.x, l = tid % 64;
+  const int g = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int64_t c = xcd_cluster(blockIdx.x, A.n);
+  const int64_t ho = A.hoff[c];
+  double ar[NC][NE], ai[NC][NI], my = 0.0;
+#pragma unroll 4   // in full it is 8000 instructions
+  for (int e = 0; e < NE; ++e)
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      double vr, vi;
+      theta_elem<double, CPLX>(A, c, DE, log2i(DE), ho, G * e + g, l + 64 * q, 0.0, vr, vi);
+      my = fma(vr, vr, my);
+      if constexpr (CPLX) my = fma(vi, vi, my);
+#pragma unroll
+      for (int f = 0; f < NE; ++f)
+        if (f == e) {
+          ar[q][f] = vr;
+          if constexpr (CPLX) ai[q][f] = vi;
+        }
+    }
+  const double nrm2 = block_sum(my, red);
+  for (int k = 0; k < DE - 2; ++k) {
+    double2* x = sx[k & 1];
+    // x_j = A[j][k] = conj(A[k][j]), j > k
+    if (k % G == g) {
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const int i = l + 64 * q;
+        double rr = 0.0, ri = 0.0;
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+          if (e == k / G) {
+            rr = ar[q][e];
+            if constexpr (CPLX) ri = ai[q][e];
+          }
+        x[i] = i > k ? double2{rr, -ri} : double2{0.0, 0.0};
+        if (i == k) dg[k] = rr;
+      }
+    }
+    __syncthreads();
+    double2 xi[NC];
+    double xs = 0.0;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      xi[q] = x[l + 64 * q];
+      xs = fma(xi[q].x, xi[q].x, fma(xi[q].y, xi[q].y, xs));
+    }
+    const double xn2 = wave_sum_dpp(xs), xn = sqrt(xn2);
+    const double2 x0 = x[k + 1];
+    const double a0 = sqrt(fma(x0.x, x0.x, x0.y * x0.y));
+    const double vn2 = 2.0 * (xn2 + a0 * xn);
+    // v = x - alpha e1, alpha = -(x0/|x0|) ||x||; x = 0: nothing to reflect
+    const double ia = a0 > 0.0 ? xn / a0 : 0.0;
+    const double2 v0 = a0 > 0.0 ? double2{fma(x0.x, ia, x0.x), fma(x0.y, ia, x0.y)} : double2{xn, 0.0};
+    const double tau = vn2 > 0.0 ? 2.0 / vn2 : 0.0;
+    if (tid == 0) e2[k] = xn2;
+    // (A v)_i = sum_j conj(A[j][i]) v_j over this wave's rows
+    double sr[NC], si[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) sr[q] = si[q] = 0.0;
+#pragma unroll
+    for (int e0 = 0; e0 < NE; e0 += 4) {   // four LDS reads in flight to a branch
+      if (G * (e0 + 4) - 1 <= k) continue;   // rows done with (their v_j is zero)
+      double2 v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = x[G * (e0 + e) + g];
+        if (G * (e0 + e) + g == k + 1) v[e] = v0;
+      }
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        if (64 * q + 63 <= k) continue;   // columns done with
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const double b = ar[q][e0 + e];
+          sr[q] = fma(b, v[e].x, sr[q]);
+          if constexpr (CPLX) {
+            const double d = ai[q][e0 + e];
+            sr[q] = fma(d, v[e].y, sr[q]);
+            si[q] = fma(b, v[e].y, fma(-d, v[e].x, si[q]));
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      part[g][l + 64 * q] = double2{sr[q], si[q]};
+      if (l + 64 * q == k + 1) xi[q] = v0;   // the lane's elements of v
+    }
+    __syncthreads();
+    if (g == 0) {
+      double2 pp[NC];
+      double ks = 0.0;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        double pr = 0.0, pi = 0.0;
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+          const double2 t = part[h][l + 64 * q];
+          pr += t.x;
+          pi += t.y;
+        }
+        pp[q] = l + 64 * q > k ? double2{tau * pr, tau * pi} : double2{0.0, 0.0};
+        ks = fma(xi[q].x, pp[q].x, fma(xi[q].y, pp[q].y, ks));
+      }
+      const double K = 0.5 * tau * wave_sum_dpp(ks);
+#pragma unroll
+      for (int q = 0; q < NC; ++q) sw[l + 64 * q] = double2{fma(-K, xi[q].x, pp[q].x), fma(-K, xi[q].y, pp[q].y)};
+      if (l == 0) x[k + 1] = v0;
+    }
+    __syncthreads();
+    // A22 -= v w^H + w v^H
+    double2 wi[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) wi[q] = sw[l + 64 * q];
+#pragma unroll
+    for (int e0 = 0; e0 < NE; e0 += 4) {
+      if (G * (e0 + 4) - 1 <= k) continue;
+      double2 v[4], w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = x[G * (e0 + e) + g];
+        w[e] = sw[G * (e0 + e) + g];
+      }
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        if (64 * q + 63 <= k) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if constexpr (CPLX) {
+            ar[q][e0 + e] -=
+                fma(v[e].x, wi[q].x, fma(v[e].y, wi[q].y, fma(w[e].x, xi[q].x, w[e].y * xi[q].y)));
+            ai[q][e0 + e] -=
+                fma(v[e].y, wi[q].x, fma(-v[e].x, wi[q].y, fma(w[e].y, xi[q].x, -w[e].x * xi[q].y)));
+          } else {
+            ar[q][e0 + e] -= fma(v[e].x, wi[q].x, w[e].x * xi[q].x);
+          }
+        }
+      }
+    }
+  }
+  {   // the last 2 x 2 block: rows DE - 2 and DE - 1 are the last register of waves G - 2 and G - 1
+    const double zr = ar[NC - 1][NE - 1], zi = CPLX ? ai[NC - 1][NI - 1] : 0.0;
+    if (g == G - 2 && l == 62) dg[DE - 2] = zr;
+    if (g == G - 2 && l == 63) e2[DE - 2] = fma(zr, zr, zi * zi);
+    if (g == G - 1 && l == 63) {
+      dg[DE - 1] = zr;
+      e2[DE - 1] = 0.0;
+    }
+  }
+  __syncthreads();
+  // Gershgorin bracket
+  double lo = INFINITY, hi = -INFINITY, emax = 0.0;
+  if (tid < DE) {
+    const double b = (tid > 0 ? sqrt(e2[tid - 1]) : 0.0) + sqrt(e2[tid]);
+    lo = dg[tid] - b;
+    hi = dg[tid] + b;
+    emax = e2[tid];
+  }
+  lo = block_min(lo, red);
+  hi = block_max(hi, red);
+  emax = block_max(emax, red);
+  const double pivmin = DBL_MIN * fmax(1.0, emax);
+  const double span0 = fmax(hi - lo, DBL_MIN);
+  lo -= 2.0 * DBL_EPSILON * fabs(lo) + span0 * DBL_EPSILON;
+  hi += 2.0 * DBL_EPSILON * fabs(hi) + span0 * DBL_EPSILON;
+  constexpr int NP = DE * 4;
+  for (int round = 0; round < 12; ++round) {
+    if (hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi))) break;   // a few ulps of lambda_min
+    const double y = lo + (hi - lo) * (double)(tid + 1) / (double)(NP + 1);
+    int cnt = 0;
+    double q = dg[0] - y;
+    if (fabs(q) < pivmin) q = -pivmin;
+    cnt += q < 0.0;
+#pragma unroll 4
+    for (int r = 1; r < DE; ++r) {
+      // the reciprocal to an ulp or two: a relative change of e2, as a rounding of the quotient is
+      q = fmin(fmax(fma(-e2[r - 1], rcp_nr(q), dg[r] - y), -1e300), 1e300);
+      if (fabs(q) < pivmin) q = -pivmin;
+      cnt += q < 0.0;
+    }
+    const int t = (int)block_min(cnt > 0 ? (double)tid : (double)NP, red);
+    const double nlo = t == 0 ? lo : lo + (hi - lo) * (double)t / (double)(NP + 1);
+    const double nhi = t == NP ? hi : lo + (hi - lo) * (double)(t + 1) / (double)(NP + 1);
+    if (!(nhi - nlo < hi - lo)) break;
+    lo = nlo;
+    hi = nhi;
+  }
+  if (tid == 0) {
+    const int32_t gid = A.gid[c];
+    if (!isfinite(nrm2)) lo = nrm2;   // a NaN or infinite entry leaves no bracket
+    A.scal[gid] = lo;
+    A.scal2[gid] = 8.0 * DE * DBL_EPSILON * sqrt(nrm2);
+    if (!isfinite(lo) && A.nonfinite) atomicAdd(A.nonfinite, 1ull);
+  }
+}
+
 // ------------------------------------------------------------------------------------------
 // lambda_min-only certification, De = 64, 128, 256 (one workgroup of 256 threads per cluster)
 // ------------------------------------------------------------------------------------------
@@ -4746,7 +4959,8 @@ static hipError_t launch_cluster_m(const ClusterArgs<T>& a, int block, int W, hi
       if (a.expm_scratch == nullptr || a.expm_blocks <= 0) return hipErrorInvalidValue;
       const unsigned grid = (unsigned)std::min<int64_t>(a.n, a.expm_blocks);
       // Lanczos + Cholesky certificate at D_e = 256 by default (methods 2 and 3: every D_e >= 64);
-      // at 64 and 128 the tridiagonalisation is as fast and its margin tighter
+      // at 64 and 128 the tridiagonalisation has the matrix in registers and the tighter margin, at 256
+      // it goes through the slab and takes 3.9 times the certificate
       if (a.cert_method >= 2 || (a.cert_method == 0 && a.De >= 256)) {
         if (a.De == 64)
           hipLaunchKernelGGL((k_certify_lanczos<CPLX, 64>), dim3(grid), dim3(1024), 0, s, a, a.expm_scratch, a.expm_slab);
@@ -4758,10 +4972,11 @@ static hipError_t launch_cluster_m(const ClusterArgs<T>& a, int block, int W, hi
           return hipErrorInvalidValue;
         return hipGetLastError();
       }
+      if (a.n > 0x7fffffff) return hipErrorInvalidValue;
       if (a.De == 64)
-        hipLaunchKernelGGL((k_cluster_tridiag<CPLX, 64>), dim3(grid), dim3(256), 0, s, a, a.expm_scratch, a.expm_slab);
+        hipLaunchKernelGGL((k_certify_tridiag<CPLX, 64>), dim3((unsigned)a.n), dim3(256), 0, s, a);
       else if (a.De == 128)
-        hipLaunchKernelGGL((k_cluster_tridiag<CPLX, 128>), dim3(grid), dim3(256), 0, s, a, a.expm_scratch, a.expm_slab);
+        hipLaunchKernelGGL((k_certify_tridiag<CPLX, 128>), dim3((unsigned)a.n), dim3(512), 0, s, a);
       else if (a.De == 256)
         hipLaunchKernelGGL((k_cluster_tridiag<CPLX, 256>), dim3(grid), dim3(256), 0, s, a, a.expm_scratch, a.expm_slab);
       else
