@@ -4028,12 +4028,20 @@ __global__ __launch_bounds__(DE * 4) void k_certify_tridiag(ClusterArgs<double> 
 // slab once (column t of the Hermitian theta_e gives row t of theta_e q, coalesced across t);
 // the right-looking blocked factorisation reads and writes the trailing lower triangle once per
 // panel.
+// At 256 dimensions (the 1017 clusters of a 1024-site chain, 56 to 72 Lanczos steps) the time goes to the
+// products, bound by what the caches deliver (13.5 us each, 4 MiB of L2 serving 32 matrices), then the
+// factorisation, and the barriers of both: 12.5 ms with every row in the slab, three barriers to a
+// panel column and to a sum, and divisions on 1024 points in ritz_min; 10.0 ms with rows in LDS, one
+// barrier each, and reciprocals on 256 points.
 
 // Smallest eigenvalue of the symmetric tridiagonal (al[0..k-1], off-diagonal be[0..k-2]) by
-// multisection on Sturm counts with every thread of the workgroup, from the bracket
-// [Gershgorin lower end, min_i al_i]; the midpoint of the final bracket.
+// multisection on Sturm counts from the bracket [Gershgorin lower end, min_i al_i]; the midpoint of
+// the final bracket.  One wave per SIMD counts: the chain of reciprocals is latency, and with 1024
+// points a round the instructions of four waves, divisions then, came one after another (67 us a call
+// at about 50 steps).
 __device__ double ritz_min(const double* al, const double* be, int k, double* red) {
-  const int tid = threadIdx.x, nth = blockDim.x;
+  const int tid = threadIdx.x;
+  constexpr int nth = 256;   // counting threads, of at least as many in the workgroup
   double lo = INFINITY, hi = INFINITY, emax = 0.0;
   for (int i = 0; i < k; ++i) {   // every thread, same order: identical values
     const double bl = i > 0 ? be[i - 1] : 0.0, br = i + 1 < k ? be[i] : 0.0;
@@ -4044,15 +4052,18 @@ __device__ double ritz_min(const double* al, const double* be, int k, double* re
   const double pivmin = DBL_MIN * fmax(1.0, emax);
   for (int round = 0; round < 12; ++round) {
     if (hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi))) break;
-    const double x = lo + (hi - lo) * (double)(tid + 1) / (double)(nth + 1);
     int cnt = 0;
-    double q = al[0] - x;
-    if (fabs(q) < pivmin) q = -pivmin;
-    cnt += q < 0.0;
-    for (int i = 1; i < k; ++i) {
-      q = (al[i] - x) - be[i - 1] * be[i - 1] / q;
+    if (tid < nth) {
+      const double x = lo + (hi - lo) * (double)(tid + 1) / (double)(nth + 1);
+      double q = al[0] - x;
       if (fabs(q) < pivmin) q = -pivmin;
       cnt += q < 0.0;
+#pragma unroll 4
+      for (int i = 1; i < k; ++i) {
+        q = fmin(fmax(fma(-be[i - 1] * be[i - 1], rcp_nr(q), al[i] - x), -1e300), 1e300);
+        if (fabs(q) < pivmin) q = -pivmin;
+        cnt += q < 0.0;
+      }
     }
     const int t = (int)block_min(cnt > 0 ? (double)tid : (double)nth, red);
     const double nlo = t == 0 ? lo : lo + (hi - lo) * (double)t / (double)(nth + 1);
@@ -4085,10 +4096,17 @@ __global__ __launch_bounds__(1024) void k_certify_lanczos(ClusterArgs<double> A,
   __shared__ double qr[DE], qi[CPLX ? DE : 1];
   __shared__ double yr[G][DE], yi[CPLX ? G : 1][CPLX ? DE : 1];
   __shared__ double al[KMAX], be[KMAX];
-  __shared__ double Pr[NB][DE], Pi[CPLX ? NB : 1][CPLX ? DE : 1];
+  // rows sh < NL of the half storage live in LDS, under the panel that is used after them: 28 of the
+  // 129 complex rows.  (As many again in registers spill more than they save; so do more than four
+  // slab loads in flight to a thread.)
+  constexpr int NC = CPLX ? 2 : 1;
+  constexpr int NL = DE == 256 ? 56 / NC : 0;
+  static_assert(NL % G == 0 && NL <= H, "whole groups of rows, the last one in the slab");
+  __shared__ double lds[(NL > NB ? NL : NB) * DE * NC];
+  double(*Pr)[DE] = (double(*)[DE])lds, (*Pi)[DE] = (double(*)[DE])(lds + (NC - 1) * NB * DE);
   __shared__ double rsum[DE];
   __shared__ double csum[NB];
-  __shared__ double red[NW];
+  __shared__ double red[NW], rsa[NW], rsb[NW];
   const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
   const int t = tid % DE, g = tid / DE;
   const double u = 0.5 * DBL_EPSILON;
@@ -4106,8 +4124,13 @@ __global__ __launch_bounds__(1024) void k_certify_lanczos(ClusterArgs<double> A,
       const int sh = idx / DE, tt = idx % DE;
       double vr_, vi_;
       theta_elem<double, CPLX>(A, c, DE, NBITS, ho, (tt + sh) & (DE - 1), tt, 0.0, vr_, vi_);
-      br[idx] = vr_;
-      if constexpr (CPLX) bi[idx] = vi_;
+      if (sh < NL) {
+        lds[sh * NC * DE + tt] = vr_;
+        if constexpr (CPLX) lds[(sh * NC + 1) * DE + tt] = vi_;
+      } else {
+        br[idx] = vr_;
+        if constexpr (CPLX) bi[idx] = vi_;
+      }
       // every off-diagonal pair once, except on the last shift-diagonal (twice there)
       const double w = (sh == 0 || sh == H) ? 1.0 : 2.0;
       my = fma(w * vr_, vr_, my);
@@ -4139,19 +4162,10 @@ __global__ __launch_bounds__(1024) void k_certify_lanczos(ClusterArgs<double> A,
         // shift-diagonal s are coalesced across t (the second is the first rotated by s).
         // Thread (g, t) takes the shift-diagonals s = g mod G.
         double sr = 0.0, si = 0.0;
-#pragma unroll 2
-        for (int sh = g; sh <= H; sh += G) {
-          const double* rr = br + (int64_t)sh * DE;
-          const int up = (t + sh) & (DE - 1), dn = (t - sh) & (DE - 1);
-          const bool two = sh > 0 && sh < H;
-          const double b_r = rr[t];
-          const double c_r = two ? rr[dn] : 0.0;
-          double b_i = 0.0, c_i = 0.0;
-          if constexpr (CPLX) {
-            const double* ri = bi + (int64_t)sh * DE;
-            b_i = ri[t];
-            c_i = two ? ri[dn] : 0.0;
-          }
+        int t1 = t;
+        asm volatile("" : "+v"(t1));   // else the addresses of all rows are kept over the steps, and spill
+        auto add = [&](int sh, double b_r, double b_i, double c_r, double c_i) {
+          const int up = (t1 + sh) & (DE - 1), dn = (t1 - sh) & (DE - 1);
           const double xr = qr[up], yr_ = qr[dn];
           sr = fma(b_r, xr, sr);
           sr = fma(c_r, yr_, sr);
@@ -4162,6 +4176,28 @@ __global__ __launch_bounds__(1024) void k_certify_lanczos(ClusterArgs<double> A,
             si = fma(b_r, xi, fma(-b_i, xr, si));
             si = fma(c_r, yi_, fma(c_i, yr_, si));
           }
+        };
+#pragma unroll 2
+        for (int sh = g; sh < NL; sh += G) {
+          const double* rr = lds + sh * NC * DE;
+          const int dn = (t1 - sh) & (DE - 1);
+          const double z = sh > 0 ? 1.0 : 0.0;   // the diagonal once
+          add(sh, rr[t1], CPLX ? rr[DE + t1] : 0.0, z * rr[dn], CPLX ? z * rr[DE + dn] : 0.0);
+        }
+#pragma unroll 2
+        for (int sh = NL + g; sh <= H; sh += G) {
+          const double* rr = br + (int64_t)sh * DE;
+          const int dn = (t1 - sh) & (DE - 1);
+          const bool two = sh > 0 && sh < H;
+          const double b_r = rr[t1];
+          const double c_r = two ? rr[dn] : 0.0;
+          double b_i = 0.0, c_i = 0.0;
+          if constexpr (CPLX) {
+            const double* ri = bi + (int64_t)sh * DE;
+            b_i = ri[t1];
+            c_i = two ? ri[dn] : 0.0;
+          }
+          add(sh, b_r, b_i, c_r, c_i);
         }
         yr[g][t] = sr;
         if constexpr (CPLX) yi[g][t] = si;
@@ -4181,7 +4217,20 @@ __global__ __launch_bounds__(1024) void k_certify_lanczos(ClusterArgs<double> A,
           ma = fma(qi[tid], wi, ma);
         }
       }
-      const double alpha = block_sum(ma, red);
+      // sums over the waves that hold the vector, one barrier each (a buffer of its own: it is read
+      // again only after the barrier of the next sum)
+      auto vec_sum = [&](double v, double* buf) {
+        if (tid < DE) {
+          v = wave_sum_dpp(v);
+          if (lane == 0) buf[wave] = v;
+        }
+        __syncthreads();
+        double z = 0.0;
+#pragma unroll
+        for (int h = 0; h < DE / 64; ++h) z += buf[h];
+        return z;
+      };
+      const double alpha = vec_sum(ma, rsa);
       double mb = 0.0;
       if (tid < DE) {
         wr = fma(-alpha, qr[tid], wr);
@@ -4191,7 +4240,7 @@ __global__ __launch_bounds__(1024) void k_certify_lanczos(ClusterArgs<double> A,
           mb = fma(wi, wi, mb);
         }
       }
-      const double beta = sqrt(block_sum(mb, red));
+      const double beta = sqrt(vec_sum(mb, rsb));
       const bool invariant = !(beta > 64.0 * u * nf);   // Krylov space invariant (or no progress)
       if (tid == 0) {
         al[k] = alpha;
@@ -4240,26 +4289,32 @@ __global__ __launch_bounds__(1024) void k_certify_lanczos(ClusterArgs<double> A,
         if constexpr (CPLX) Pi[q][r] = vi_;
       }
       __syncthreads();
+      // One barrier a column: column q is scaled to L where it is used, and stored scaled a column
+      // later, when no wave reads it any more
+      auto store_scaled = [&](int q, double il, double l) {
+        for (int r = q + tid; r < m; r += NT) {
+          Pr[q][r] = r == q ? l : Pr[q][r] * il;
+          if constexpr (CPLX) Pi[q][r] = r == q ? 0.0 : Pi[q][r] * il;
+        }
+      };
+      double l = 0.0, il = 0.0;
       for (int q = 0; q < NB; ++q) {
+        if (q > 0) store_scaled(q - 1, il, l);
         const double d = Pr[q][q];
         if (!(d > 0.0) || !isfinite(d)) {   // every thread reads the same value: uniform
           ok = false;
           break;
         }
-        const double l = sqrt(d), il = 1.0 / l;
-        __syncthreads();
-        for (int r = q + tid; r < m; r += NT) {
-          Pr[q][r] = r == q ? l : Pr[q][r] * il;
-          if constexpr (CPLX) Pi[q][r] = r == q ? 0.0 : Pi[q][r] * il;
-        }
-        __syncthreads();
+        l = sqrt(d);
+        il = 1.0 / l;
         // S[r][q2] -= L[r][q] conj(L[q2][q]) for the panel's later columns q2 <= r (wave per column)
         for (int q2 = q + 1 + wave; q2 < NB; q2 += NW) {
-          const double kr = Pr[q][q2], ki = CPLX ? Pi[q][q2] : 0.0;
+          const double kr = Pr[q][q2] * il, ki = CPLX ? Pi[q][q2] * il : 0.0;
+#pragma unroll 4
           for (int r = q2 + lane; r < m; r += 64) {
-            const double lr = Pr[q][r];
+            const double lr = Pr[q][r] * il;
             if constexpr (CPLX) {
-              const double li = Pi[q][r];
+              const double li = Pi[q][r] * il;
               Pr[q2][r] -= fma(lr, kr, li * ki);
               Pi[q2][r] -= fma(li, kr, -lr * ki);
             } else {
@@ -4269,6 +4324,8 @@ __global__ __launch_bounds__(1024) void k_certify_lanczos(ClusterArgs<double> A,
         }
         __syncthreads();
       }
+      if (ok) store_scaled(NB - 1, il, l);
+      __syncthreads();
       if (!ok) break;
       // sums of |L| along the panel's rows (this thread's rows) and columns (wave per column)
       for (int r = tid; r < m; r += NT) {
