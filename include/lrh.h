@@ -68,9 +68,9 @@ typedef enum {
 #define LRH_F32    0x1u   /* state buffers (nu, zeta, grad, marginals) are float, and the
                              iterations compute in FP32; certification stays FP64.  Gibbs
                              states of clusters with D_e >= 16 come from scaling and
-                             squaring: a degree-8 Taylor polynomial and the first four
-                             squarings in FP64, the later squarings in FP32 (FP64 messages:
-                             degree 12, every squaring in FP64); the result is within the
+                             squaring: a degree-12 polynomial and the first squarings (two
+                             in the W = 0 shape) in FP64, the later squarings in FP32
+                             (FP64 messages: everything in FP64); the result is within the
                              float rounding of the messages                                 */
 #define LRH_FUSED  0x2u   /* graph-replayed iterations: for 2-local problems one launch per
                              iteration (the message update of the previous step folded into
@@ -305,13 +305,16 @@ lrh_status lrh_set_certify_method(lrh_problem p, int32_t method);
 
 /* Launch shapes (the W of the calls below), per cluster bucket and precision:
  *   W = 1      register kernel, one lane per cluster (D_e <= 8), Jacobi
- *   W = 8..64  LDS kernel, W lanes per cluster, 64/W clusters per wave (8 <= D_e <= 64), Jacobi
+ *   W = 8..64  W lanes per cluster, 64/W clusters per wave (8 <= D_e <= 64), Jacobi, in registers
+ *              where FP64 and D_e <= 16, else in LDS.  D_e = 8 without a forced shape: 16 lanes up
+ *              to 2048 clusters, 8 up to 32768 (float iterations: 24576), then W = 1
+ *              where it is compiled (not complex FP64)
  *   W = 1024   one 1024-thread workgroup per cluster, matrix in a device slab (D_e = 128, 256),
  *              Jacobi; ground projector only once the exponential exists for the bucket
  *   W = 0      Gibbs state exp(-beta theta)/Z by scaling and squaring on the FP64 matrix cores,
  *              no eigenvectors, one wave per cluster, matrices in registers (D_e = 16, 32;
  *              Gibbs passes only, the default there)
- *   W = 4      the same on one 256-thread workgroup per cluster, matrices in a device slab
+ *   W = 4      the same on one workgroup of 3 to 12 waves per cluster, matrices in a device slab
  *              (D_e >= 32; the default for D_e >= 64)
  *   W = 5      clusters holding a spin-1 site (D_e not a power of two): the LDS Jacobi kernel
  *              driven by index tables (lift and partial-trace maps per cluster and child) on the

@@ -2075,24 +2075,21 @@ __global__ __launch_bounds__(1024) void k_cluster_big(ClusterArgs<T> A, T* scrat
 //
 // The smoothed dual needs rho_e = exp(-beta theta_e) / Z and F_beta = -(1/beta) log Z only
 // (Sec. 4.1.2); the eigenvectors are not needed for that.  With mu = Tr(theta)/D and
-// X = beta (theta - mu), the scaling s is the least s >= 0 with ||X|| / 2^s <= 1/2, where ||X||
-// is an upper bound of the spectral norm: the induced 1-norm (largest absolute row sum) in the
-// one-wave kernel, min(||X||_F, ||X||_1) in the workgroup kernel (both norms are
-// submultiplicative, so the Taylor remainder bound holds in either; the 1-norm is the tight one
-// for lifted local terms 1 (x) h, whose Frobenius norm carries a factor sqrt(D / D_h)), and
-//     E0 = T_m(-X / 2^s)                (Taylor polynomial, Paterson-Stockmeyer, p = 3; m = 12,
-//                                        or 8 for float messages)
+// X = beta (theta - mu), the scaling s is the least s >= 0 with r <= kMax 2^s, where r = sqrt(||X^2||_1)
+// bounds the spectral radius of X (X^2 is a matrix the polynomial needs anyway, and its 1-norm is
+// nearer to the radius than that of X), and
+//     E0 = p(-X / 2^s)                  (ExpPoly: degree 12, four products)
 //     Y0 = E0 / tau_0,  Y_j = Y_{j-1}^2 / tau_j    (j = 1..s)
 //     rho = Y_s / Tr Y_s,  log Z = 2^s log tau_0 + sum_j 2^(s-j) log tau_j + log Tr Y_s
 // for any positive rescalings tau_j (the one-wave kernel uses exact powers of two; the
 // workgroup kernel tau_0 = Tr E0, tau_j = (Tr Y_{j-1})^2).
-// The truncation error of T12 at norm 1/2 is below 2e-14 relative (in the norm that set s),
-// i.e. a backward error of about 7e-14 ||X|| in X, which exact squaring preserves (T8: 5.4e-9,
-// under the float rounding of the messages).  Rounding in the squarings adds a relative error of
-// order D u (spectral spread / gap) to rho: the part along the dominant eigenvector is removed
-// by the final trace normalisation, the rest is damped once the spectrum separates.  The
-// polynomial and the first four squarings run in FP64 on the matrix cores; with double messages
-// so do the rest, with float messages the later squarings run in FP32.
+// A relative error e of p acts like e 2^s on X, at most (e / kMax) times 2 r: 3e-15 r with double
+// messages, under the float rounding of the messages with float ones.  Rounding in the squarings adds a
+// relative error of order D u (spectral spread / gap) to rho: the part along the dominant eigenvector is
+// removed by the final trace normalisation, the rest is damped once the spectrum separates.  With double
+// messages everything runs in FP64.  With float messages the polynomial and the first squarings do
+// (two in the one-wave kernel; in the workgroup kernel all but the last n32 <= log2(||X|| / 4)), the
+// rest in FP32.
 //
 // One wavefront per cluster.  A matrix is NB x NB blocks of 16 x 16 held in the MFMA result
 // layout: lane l, register r of block (I, J) is element (16 I + 4 r + l/16, 16 J + l%16).
@@ -2975,15 +2972,6 @@ struct WgMfma<double> {
   }
   static __device__ __forceinline__ int row(int l, int r) { return 4 * r + (l >> 4); }
 };
-template <>
-struct WgMfma<float> {
-  typedef mfma_f32x4 acc;
-  static __device__ __forceinline__ acc mma(float a, float b, acc c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int l, int r) { return 4 * (l >> 4) + r; }
-};
-
 // Bank swizzles of a stage.  Row k: the four rows that one fragment read touches would start on the
 // same bank, so its blocks of 16 elements are permuted by block ^ wg_swizzle(k), which depends on the
 // low bits of k only (those of l / 16 for a reading lane).  Columns are staged as DE pieces of CC
@@ -2999,8 +2987,7 @@ __device__ __forceinline__ int wg_csw(int i) {
   return CC == 16 ? (i & 15) : CC == 8 ? ((i >> 1) & 7) : CC == 4 ? ((i >> 2) & 3) : ((i >> 3) & 1);
 }
 
-// Sizes of a stage: KS rows (complex: and columns) of X (and of Y unless SAME).  A float stage holds
-// twice the rows of a double one, two matrices' stage half of them.
+// Sizes of a stage: KS rows (complex: and columns) of X (and of Y unless SAME; then half as many).
 template <typename S, bool CPLX, int DE, bool SAME>
 struct WgStage {
   using P = WgPlan<DE>;

@@ -1,0 +1,116 @@
+"""Edges of the kernels' size ranges and of the rules that choose between them: scalings of the matrix
+exponential around its first squarings, tridiagonalisation of matrices with nothing to reflect, the
+switches of the D = 8 launch shape, the bound without its reverse sweep."""
+import numpy as np
+import pytest
+
+import lrh_workloads as W
+from oracle import lrh_oracle as O
+from test_gpu_parity import (EXPM_PROBLEMS, lrhmod, max_pair_err, need_gpu, oracle_marginals, say,  # noqa: F401
+                             sites_per_instance)
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("wg32", [False, True])
+@pytest.mark.parametrize("name", ["randchain_Y5_complex", "k5_complete_real", "heis_Y7_real", "gue_Y8_complex"])
+def test_gibbs_around_the_first_squarings(name, wg32):
+    """beta from no squaring at all through one, two and a few, every dimension 16 to 256.  Entry
+    tolerance as for larger beta: 1e-10 below beta = 10 and 2e-9 above; float messages 5e-5."""
+    lrh = lrhmod()
+    make, dims = EXPM_PROBLEMS[name]
+    if wg32 and 32 not in dims:
+        pytest.skip("no 32-dimensional clusters")
+    d = make()
+    P = lrh.Problem(d, 0)
+    R = O.Relaxation(d)
+    if wg32:
+        P.force_shape(32, 4)
+    nu_o = R.draw(71, 0.5)
+    nu = P.from_dense(R.to_pairs(nu_o))
+    nu32 = P.from_dense(R.to_pairs(nu_o), f32=True)
+    nu_r = R.from_pairs(P.to_dense(nu32))
+    n = sites_per_instance(d)
+    for beta in (1e-9, 0.02, 0.1, 0.25, 0.55, 1.3, 40.0):
+        say(f"[expm scale] {name} beta={beta} wg32={wg32}")
+        q, g, m = P.dual_eval(nu, beta, grad=True, marg=True)
+        q32, g32, _ = P.dual_eval(nu32, beta, grad=True)
+        torch.cuda.synchronize()
+        tol = 1e-10 if beta < 10 else 2e-9
+        q_o, g_o = R.grad_beta(nu_o, beta)
+        _, rho = R.gibbs(nu_o, beta)
+        # F = mu - log Z / beta: at small beta a rounding of log Z ~ log D counts 1 / beta
+        assert np.all(np.abs(q.cpu().numpy() - q_o) <= (1e-9 + 1e-13 / beta) * n)
+        assert max_pair_err(P.to_dense(g), R.to_pairs(g_o)) < tol
+        assert max_pair_err(P.marg_dense(m), oracle_marginals(R, rho)) < tol
+        _, g_o = R.grad_beta(nu_r, beta)
+        assert max_pair_err(P.to_dense(g32), R.to_pairs(g_o)) < 5e-5
+    assert P.check() == (0, 0)
+
+
+@pytest.mark.parametrize("k", [6, 7])
+@pytest.mark.parametrize("kind", ["zero", "identity", "diagonal", "one_row", "random"])
+@pytest.mark.parametrize("cplx", [False, True])
+def test_certify_matrices_with_nothing_to_reflect(k, kind, cplx):
+    """One cluster of 64 or 128 dimensions: lambda_min within the margin, 8 D eps ||theta||_F, of the
+    eigenvalues by LAPACK (whose own error is far below it)."""
+    lrh = lrhmod()
+    say(f"[tridiag] 2^{k} {kind} cplx={cplx}")
+    D = 2 ** k
+    rng = np.random.default_rng(5 + k)
+    z = rng.normal(size=(D, D)) + (1j * rng.normal(size=(D, D)) if cplx else 0.0)
+    h = np.diag(np.diag(z + z.conj().T)).astype(z.dtype)
+    if kind == "zero":
+        h = 0 * h
+    elif kind == "identity":
+        h = -1.25 * np.eye(D, dtype=z.dtype)
+    elif kind == "one_row":   # a column whose only element below the diagonal is the last
+        h[D - 1, 0] = z[D - 1, 0]
+        h[0, D - 1] = np.conj(z[D - 1, 0])
+    elif kind == "random":
+        h = z + z.conj().T
+    b = W._Builder("dense", k)
+    b.add_term(tuple(range(k)), h)
+    d = b.build(real=not cplx)
+    P = lrh.Problem(d, 0)
+    q, mg, _ = P.certify(P.zeros())
+    torch.cuda.synchronize()
+    want = np.linalg.eigvalsh(h)[0]
+    margin = 8 * D * np.finfo(np.float64).eps * np.linalg.norm(h)
+    assert abs(q.item() - want) <= margin + np.finfo(np.float64).tiny   # the bracket of a zero matrix
+    assert mg.item() >= margin * (1 - 1e-9)
+
+
+@pytest.mark.parametrize("n", [1, 5, 2048, 2049, 32769])
+@pytest.mark.parametrize("beta", [0.0, 2.0])
+def test_eight_dimensional_shape_switches(n, beta):
+    """A real chain with n three-site clusters in the default shape against one lane per cluster: both FP64
+    Jacobi, so to rounding (the dual value per site, the oracle's entry tolerance)."""
+    lrh = lrhmod()
+    say(f"[D=8 default] n={n} beta={beta}")
+    d = W.with_tops(W.heisenberg_chain(n + 2, field_x=0.4), [tuple(range(i, i + 3)) for i in range(n)])
+    P = lrh.Problem(d, 0)
+    g0 = torch.Generator(device="cpu").manual_seed(3)
+    nu = P.zeros()
+    nu.copy_(0.3 * torch.randn(nu.shape, generator=g0, dtype=torch.float64))
+    q, g, m = P.dual_eval(nu, beta, grad=True, marg=True)
+    P.force_shape(8, 1)
+    q1, g1, m1 = P.dual_eval(nu, beta, grad=True, marg=True)
+    torch.cuda.synchronize()
+    assert (q - q1).abs().max().item() <= 1e-12 * d.n_sites
+    assert g.numel() == 0 or (g - g1).abs().max().item() < 1e-10
+    assert (m - m1).abs().max().item() < 1e-10
+
+
+@pytest.mark.parametrize("T", [0, 1, 7])
+def test_bound_without_gradient_is_the_bound(T):
+    lrh = lrhmod()
+    say(f"[unrolled value] T={T}")
+    d = W.xxz_triangular(4, 0.5, seed=5)
+    P = lrh.Problem(d, 0)
+    b, _, _ = P.unrolled_bound_grad(4.0, T)
+    v = lrh.unrolled_bound(torch.tensor(d.params, dtype=torch.float64, device="cuda"), P, 4.0, T)
+    torch.cuda.synchronize()
+    assert (v - b).abs().max().item() <= 1e-12 * d.n_sites
