@@ -4019,7 +4019,7 @@ __global__ __launch_bounds__(DE * 4) void k_certify_tridiag(ClusterArgs<double> 
 // products, bound by what the caches deliver (13.5 us each, 4 MiB of L2 serving 32 matrices), then the
 // factorisation, and the barriers of both: 12.5 ms with every row in the slab, three barriers to a
 // panel column and to a sum, and divisions on 1024 points in ritz_min; 10.0 ms with rows in LDS, one
-// barrier each, and reciprocals on 256 points.
+// barrier each, and reciprocals on 256 points; 9.1 ms with the trailing update on the matrix cores.
 
 // Smallest eigenvalue of the symmetric tridiagonal (al[0..k-1], off-diagonal be[0..k-2]) by
 // multisection on Sturm counts from the bracket [Gershgorin lower end, min_i al_i]; the midpoint of
@@ -4331,26 +4331,35 @@ __global__ __launch_bounds__(1024) void k_certify_lanczos(ClusterArgs<double> A,
         cs = wave_sum(cs);
         if (lane == 0) csum[q] = cs;
       }
-      // trailing update S[i][j] -= sum_q L[i][q] conj(L[j][q]), i >= j >= p + NB: wave per row
-      const int mt = m - NB;
-      for (int r = wave; r < mt; r += NW) {
-        const int i = NB + r;
-        for (int cc = lane; cc <= r; cc += 64) {
-          const int j = NB + cc;
-          double sr = 0.0, si = 0.0;
-#pragma unroll 4
-          for (int q = 0; q < NB; ++q) {
-            const double ar_ = Pr[q][i], br_ = Pr[q][j];
-            sr = fma(ar_, br_, sr);
-            if constexpr (CPLX) {
-              const double ai_ = Pi[q][i], bi_ = Pi[q][j];
-              sr = fma(ai_, bi_, sr);
-              si = fma(ai_, br_, fma(-ar_, bi_, si));
-            }
+      // trailing update S[i][j] -= sum_q L[i][q] conj(L[j][q]), i, j >= p + NB, of the 16 x 16 blocks on
+      // and below the diagonal (what lies above it is not read), on the matrix cores: as vector code it
+      // was bound by the LDS reads of four operands per complex product
+      const int nb = (m - NB) / 16;
+      for (int blk = wave, I = 0, first = 0; blk < nb * (nb + 1) / 2; blk += NW) {
+        while (blk - first > I) first += ++I;   // block row I starts at block I (I + 1) / 2
+        const int lr = lane >> 4, i = NB + 16 * I + (lane & 15), j = NB + 16 * (blk - first) + (lane & 15);
+        const int64_t o = (int64_t)(p + NB + 16 * I + lr) * DE + p + j;
+        mfma_f64x4 sr, si;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          sr[r] = -ar[o + 4 * r * DE];
+          if constexpr (CPLX) si[r] = -ai[o + 4 * r * DE];
+        }
+#pragma unroll
+        for (int q0 = 0; q0 < NB; q0 += 4) {
+          const double xr = Pr[q0 + lr][i], yr_ = Pr[q0 + lr][j];
+          sr = __builtin_amdgcn_mfma_f64_16x16x4f64(xr, yr_, sr, 0, 0, 0);
+          if constexpr (CPLX) {
+            const double xi = Pi[q0 + lr][i], yi_ = Pi[q0 + lr][j];
+            sr = __builtin_amdgcn_mfma_f64_16x16x4f64(xi, yi_, sr, 0, 0, 0);
+            si = __builtin_amdgcn_mfma_f64_16x16x4f64(xi, yr_, si, 0, 0, 0);
+            si = __builtin_amdgcn_mfma_f64_16x16x4f64(-xr, yi_, si, 0, 0, 0);
           }
-          const int64_t o = (int64_t)(p + i) * DE + p + j;
-          ar[o] -= sr;
-          if constexpr (CPLX) ai[o] -= si;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          ar[o + 4 * r * DE] = -sr[r];
+          if constexpr (CPLX) ai[o + 4 * r * DE] = -si[r];
         }
       }
       __syncthreads();
