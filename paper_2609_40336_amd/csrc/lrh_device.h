@@ -4765,23 +4765,26 @@ __global__ __launch_bounds__(64) void k_cluster_tridiag_w(ClusterArgs<double> A)
 // nu_bar = B^* Y is then the message kernel's gradient stage (Y_f - Tr_{e\f} Y_e).  At beta = 0
 // the cotangent of Q is Y_e = qbar mu_e (the ground projector; gbar must be absent).
 // W lanes per cluster, 64/W clusters per single-wave block.
+template <typename T, bool CPLX, int DE, int W>
+struct VjpLds {
+  static constexpr int G = 64 / W, LD = DE + 1, SZ = G * DE * LD, SI = CPLX ? SZ : 1;
+  T ar[SZ], ur[SZ], xr[SZ], tr[SZ], ai[SI], ui[SI], xi[SI], ti[SI];
+  T p[G * DE], lam[G * DE];
+  ScratchFor<T, DE, true> J[G];
+};
+
 template <typename T, bool CPLX, int DE, int MODE, int W>
-__global__ __launch_bounds__(64) void k_cluster_vjp(ClusterArgs<T> A) {
+__device__ void cluster_vjp_body(const ClusterArgs<T>& A, int64_t block, int64_t blocks, VjpLds<T, CPLX, DE, W>& L) {
   constexpr int LD = DE + 1;
   constexpr int G = 64 / W;
   constexpr int SZ = DE * LD;
-  __shared__ T sar_[G * SZ], sur_[G * SZ], sxr_[G * SZ], str_[G * SZ];
-  __shared__ T sai_[CPLX ? G * SZ : 1], sui_[CPLX ? G * SZ : 1], sxi_[CPLX ? G * SZ : 1], sti_[CPLX ? G * SZ : 1];
-  __shared__ ScratchFor<T, DE, true> J_[G];
-  __shared__ T sp_[G * DE];
-  __shared__ T slam_[G * DE];
   const int g = threadIdx.x / W, tid = threadIdx.x % W;
-  const int64_t c = xcd_cluster(blockIdx.x, gridDim.x) * G + g;
+  const int64_t c = xcd_cluster(block, blocks) * G + g;
   const bool active = c < A.n;
-  T *sar = sar_ + g * SZ, *sur = sur_ + g * SZ, *sxr = sxr_ + g * SZ, *str = str_ + g * SZ;
-  T *sai = CPLX ? sai_ + g * SZ : sai_, *sui = CPLX ? sui_ + g * SZ : sui_, *sxi = CPLX ? sxi_ + g * SZ : sxi_,
-    *sti = CPLX ? sti_ + g * SZ : sti_;
-  T *sp = sp_ + g * DE, *slam = slam_ + g * DE;
+  T *sar = L.ar + g * SZ, *sur = L.ur + g * SZ, *sxr = L.xr + g * SZ, *str = L.tr + g * SZ;
+  T *sai = CPLX ? L.ai + g * SZ : L.ai, *sui = CPLX ? L.ui + g * SZ : L.ui, *sxi = CPLX ? L.xi + g * SZ : L.xi,
+    *sti = CPLX ? L.ti + g * SZ : L.ti;
+  T *sp = L.p + g * DE, *slam = L.lam + g * DE;
   const bool has_g = (A.gb_c != nullptr || A.gb_p != nullptr);
   T n2 = T(0);
   if (active) {
@@ -4792,7 +4795,7 @@ __global__ __launch_bounds__(64) void k_cluster_vjp(ClusterArgs<T> A) {
   const T nrm2 = seg_sum<W>(n2);
   init_vectors<T, CPLX, DE, true, W, true>(sur, sui, tid, active);
   __syncthreads();
-  const bool conv = cluster_jacobi<T, CPLX, DE, true, W, true>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
+  const bool conv = cluster_jacobi<T, CPLX, DE, true, W, true>(sar, sai, sur, sui, L.J[g], A.tol * A.tol * (double)nrm2,
                                                          A.max_sweeps, tid, active);
   if (active && !conv && tid == 0 && A.noconv) atomicAdd(A.noconv, 1ull);
   T lmin = T(INFINITY);
@@ -4913,6 +4916,30 @@ __global__ __launch_bounds__(64) void k_cluster_vjp(ClusterArgs<T> A) {
     __syncthreads();
     if (active) lds_outputs<T, CPLX, DE, W>(A, c, tid, gid, sxr, sxi);
   }
+}
+
+template <typename T, bool CPLX, int DE, int MODE, int W>
+__global__ __launch_bounds__(64) void k_cluster_vjp(ClusterArgs<T> A) {
+  __shared__ VjpLds<T, CPLX, DE, W> L;
+  cluster_vjp_body<T, CPLX, DE, MODE, W>(A, blockIdx.x, gridDim.x, L);
+}
+
+// Buckets of D = 8, 4 and 2 in one launch, n8, n4, n2 blocks of each, the longest first (LDS: the
+// largest of the three).  Each bucket reads the messages and writes its own outputs.
+template <bool CPLX>
+constexpr int vjp_group_lds() { return (int)sizeof(VjpLds<double, CPLX, 8, 8>); }
+template <bool CPLX, int MODE>
+__global__ __launch_bounds__(64) void k_cluster_vjp_group(ClusterArgs<double> A8, ClusterArgs<double> A4,
+                                                          ClusterArgs<double> A2, int n8, int n4, int n2) {
+  using L8 = VjpLds<double, CPLX, 8, 8>;
+  using L4 = VjpLds<double, CPLX, 4, 4>;
+  using L2 = VjpLds<double, CPLX, 2, 2>;
+  static_assert(sizeof(L4) <= sizeof(L8) && sizeof(L2) <= sizeof(L8), "the largest");
+  __shared__ __align__(16) unsigned char lds[sizeof(L8)];
+  const int b = blockIdx.x;
+  if (b < n8) cluster_vjp_body<double, CPLX, 8, MODE, 8>(A8, b, n8, *reinterpret_cast<L8*>(lds));
+  else if (b < n8 + n4) cluster_vjp_body<double, CPLX, 4, MODE, 4>(A4, b - n8, n4, *reinterpret_cast<L4*>(lds));
+  else cluster_vjp_body<double, CPLX, 2, MODE, 2>(A2, b - n8 - n4, n2, *reinterpret_cast<L2*>(lds));
 }
 
 // ------------------------------------------------------------------------------------------

@@ -156,6 +156,10 @@ hipError_t launch_copy(T* dst, const T* src, int64_t n, hipStream_t s);
 
 // ---- adjoint helpers ----
 hipError_t launch_cluster_vjp(const ClusterArgs<double>& a, bool cplx, int mode, hipStream_t s);
+// buckets of D = 8, 4 and 2 together (each may be empty)
+hipError_t launch_cluster_vjp_group(const ClusterArgs<double>& a8, const ClusterArgs<double>& a4,
+                                    const ClusterArgs<double>& a2, bool cplx, int mode, hipStream_t s);
+int64_t vjp_group_resident(bool cplx);
 // h_e = hfix_e + sum_t params[p_t] * dterm_t for the clusters listed in (pc_gid... CSR)
 hipError_t launch_set_params(double* h, const double* hfix, const int64_t* pc_hoff, const int64_t* pc_ptr,
                              const int32_t* pc_param, const int64_t* pc_doff, const double* dterm,

@@ -30,4 +30,26 @@ hipError_t launch_cluster_vjp(const ClusterArgs<double>& a, bool cplx, int mode,
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_cluster_vjp_group(const ClusterArgs<double>& a8, const ClusterArgs<double>& a4,
+                                    const ClusterArgs<double>& a2, bool cplx, int mode, hipStream_t s) {
+  const int n8 = (int)((a8.n + 7) / 8), n4 = (int)((a4.n + 15) / 16), n2 = (int)((a2.n + 31) / 32);
+  const dim3 g((unsigned)(n8 + n4 + n2)), b(64);
+#define VJP_GROUP(CPLX, MODE) \
+  hipLaunchKernelGGL((k_cluster_vjp_group<CPLX, MODE>), g, b, 0, s, a8, a4, a2, n8, n4, n2)
+  if (cplx) {
+    if (mode == MODE_GIBBS) VJP_GROUP(true, MODE_GIBBS);
+    else VJP_GROUP(true, MODE_GROUND);
+  } else {
+    if (mode == MODE_GIBBS) VJP_GROUP(false, MODE_GIBBS);
+    else VJP_GROUP(false, MODE_GROUND);
+  }
+#undef VJP_GROUP
+  return hipGetLastError();
+}
+
+// blocks of launch_cluster_vjp_group that the 256 CUs hold at once, by their 160 KiB of LDS
+int64_t vjp_group_resident(bool cplx) {
+  return 256 * (163840 / (cplx ? vjp_group_lds<true>() : vjp_group_lds<false>()));
+}
+
 }  // namespace lrh

@@ -114,3 +114,20 @@ def test_bound_without_gradient_is_the_bound(T):
     v = lrh.unrolled_bound(torch.tensor(d.params, dtype=torch.float64, device="cuda"), P, 4.0, T)
     torch.cuda.synchronize()
     assert (v - b).abs().max().item() <= 1e-12 * d.n_sites
+
+
+@pytest.mark.parametrize("L", [5, 64, 96])
+@pytest.mark.parametrize("beta", [0.0, 3.0])
+def test_adjoint_of_the_value_is_the_gradient(L, beta):
+    """Dimensions 8, 4 and 2 in one launch (L = 5, 64) and one by one (96): the adjoint of Q alone is
+    the gradient of the evaluation, two FP64 eigensolvers apart (the oracle's entry tolerance)."""
+    lrh = lrhmod()
+    say(f"[vjp group] L={L} beta={beta}")
+    P = lrh.Problem(W.xxz_triangular(L, 0.5, seed=5), 0)
+    nu = P.zeros()
+    nu.copy_(0.3 * torch.randn(nu.shape, generator=torch.Generator().manual_seed(8), dtype=torch.float64))
+    _, g, _ = P.dual_eval(nu, beta, grad=True)
+    nb, _ = P.dual_vjp(nu, beta, qbar=P.qbuf(1.0))
+    torch.cuda.synchronize()
+    # (cotangents of the Frobenius inner product, as the gradient is)
+    assert (nb - g).abs().max().item() < 1e-10
