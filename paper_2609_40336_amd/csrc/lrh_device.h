@@ -1448,7 +1448,7 @@ __device__ void lds_rebuild(const T* sur, const T* sui, const T* sp, T* yr, T* y
 
 // W lanes per cluster, 64/W clusters per single-wave block.
 template <typename T, bool CPLX, int DE, int MODE, int W>
-__global__ __launch_bounds__(64) void k_cluster_lds(ClusterArgs<T> A) {
+__device__ __forceinline__ void cluster_lds_body(const ClusterArgs<T>& A, int block) {
   constexpr int LD = DE + 1;
   constexpr int G = 64 / W;
   constexpr int SZ = DE * LD;
@@ -1461,7 +1461,7 @@ __global__ __launch_bounds__(64) void k_cluster_lds(ClusterArgs<T> A) {
   __shared__ ScratchFor<T, DE, REG> J_[G];
   __shared__ T sp_[G * DE];
   const int g = threadIdx.x / W, lt = threadIdx.x % W;
-  const int64_t c = (int64_t)blockIdx.x * G + g;
+  const int64_t c = (int64_t)block * G + g;
   const bool active = c < A.n;
   T* sar = sar_ + g * SZ;
   T* sai = CPLX ? sai_ + g * SZ : sai_;
@@ -1514,6 +1514,27 @@ __global__ __launch_bounds__(64) void k_cluster_lds(ClusterArgs<T> A) {
     __syncthreads();
     // ---- a5: outputs ----
     if (active) lds_outputs<T, CPLX, DE, W>(A, c, lt, gid, sar, sai);
+  }
+}
+template <typename T, bool CPLX, int DE, int MODE, int W>
+__global__ __launch_bounds__(64) void k_cluster_lds(ClusterArgs<T> A) {
+  cluster_lds_body<T, CPLX, DE, MODE, W>(A, blockIdx.x);
+}
+
+// 8 x 8 clusters (W lanes each), bonds and sites in one launch, in n8, nbe and nbs blocks of one wave.
+// All three are chains of rotations that leave the chip idle, and the first needs the most registers.
+template <typename T, bool CPLX, int MODE, int W>
+__global__ __launch_bounds__(64) void k_cluster_lds8_pair(ClusterArgs<T> A, ClusterArgs<T> E, ClusterArgs<T> S, int n8,
+                                                          int nbe) {
+  const int b = blockIdx.x;
+  if (b < n8) {
+    cluster_lds_body<T, CPLX, 8, MODE, W>(A, b);
+  } else if (b < n8 + nbe) {
+    const int64_t c = (int64_t)(b - n8) * 64 + threadIdx.x;
+    if (c < E.n) cluster_reg_body<T, CPLX, 4, 2, MODE>(E, c);
+  } else {
+    const int64_t c = (int64_t)(b - n8 - nbe) * 64 + threadIdx.x;
+    if (c < S.n) cluster_reg_body<T, CPLX, 2, 0, MODE>(S, c);
   }
 }
 
@@ -5120,6 +5141,17 @@ static hipError_t launch_cluster_m(const ClusterArgs<T>& a, int block, int W, hi
   return hipGetLastError();
 }
 
+// k_cluster_lds8_pair with W = 8 or 16 lanes per 8 x 8 cluster.
+template <typename T, bool CPLX, int MODE>
+hipError_t launch_lds8_pair(const ClusterArgs<T>& a, const ClusterArgs<T>& e, const ClusterArgs<T>& st, int W,
+                            hipStream_t s) {
+  const int n8 = (int)((a.n + 64 / W - 1) / (64 / W)), nbe = (int)((e.n + 63) / 64), nbs = (int)((st.n + 63) / 64);
+  const dim3 g((unsigned)(n8 + nbe + nbs)), b(64);
+  if (W == 8) hipLaunchKernelGGL((k_cluster_lds8_pair<T, CPLX, MODE, 8>), g, b, 0, s, a, e, st, n8, nbe);
+  else if (W == 16) hipLaunchKernelGGL((k_cluster_lds8_pair<T, CPLX, MODE, 16>), g, b, 0, s, a, e, st, n8, nbe);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
 
 // The float Gibbs pass of a 16-dimensional bucket (one wave per cluster) with a bond and a site bucket.
 template <typename T, bool CPLX>

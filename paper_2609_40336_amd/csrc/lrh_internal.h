@@ -147,6 +147,10 @@ hipError_t launch_widen(double* dst, const float* src, int64_t n, hipStream_t s)
 // float Gibbs pass of 16-dimensional clusters (one wave each), edges (De=4, Dc=2) and sites (De=2)
 hipError_t launch_plaquette_pass(const ClusterArgs<float>& a, const ClusterArgs<float>& e, const ClusterArgs<float>& st,
                                  bool cplx, hipStream_t s);
+// 8 x 8 clusters in the lanes kernel (W = 8, 16), bonds and sites in one launch; modes: Gibbs, double ground
+template <typename T>
+hipError_t launch_triangle_pass(const ClusterArgs<T>& a, const ClusterArgs<T>& e, const ClusterArgs<T>& st, bool cplx,
+                                int mode, int W, hipStream_t s);
 // two-bucket launch, fused (2-local problems) or plain: edges (De=4, Dc=2) and sites (De=2)
 template <typename T>
 hipError_t launch_cluster_pair(const ClusterArgs<T>& edges, const ClusterArgs<T>& sites, bool cplx,

@@ -8,4 +8,8 @@ template hipError_t launch_expm16_pair<float, false>(const ClusterArgs<float>&, 
                                                      const ClusterArgs<float>&, hipStream_t);
 template hipError_t launch_expm16_pair<float, true>(const ClusterArgs<float>&, const ClusterArgs<float>&,
                                                     const ClusterArgs<float>&, hipStream_t);
+template hipError_t launch_lds8_pair<float, false, MODE_GIBBS>(const ClusterArgs<float>&, const ClusterArgs<float>&,
+    const ClusterArgs<float>&, int, hipStream_t);
+template hipError_t launch_lds8_pair<float, true, MODE_GIBBS>(const ClusterArgs<float>&, const ClusterArgs<float>&,
+    const ClusterArgs<float>&, int, hipStream_t);
 }  // namespace lrh

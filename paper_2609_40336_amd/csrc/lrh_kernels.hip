@@ -352,6 +352,30 @@ hipError_t launch_plaquette_pass(const ClusterArgs<float>& a, const ClusterArgs<
   return cplx ? launch_expm16_pair<float, true>(a, e, st, s) : launch_expm16_pair<float, false>(a, e, st, s);
 }
 
+extern template hipError_t launch_lds8_pair<float, false, MODE_GIBBS>(const ClusterArgs<float>&, const ClusterArgs<float>&,
+    const ClusterArgs<float>&, int, hipStream_t);
+extern template hipError_t launch_lds8_pair<float, true, MODE_GIBBS>(const ClusterArgs<float>&, const ClusterArgs<float>&,
+    const ClusterArgs<float>&, int, hipStream_t);
+extern template hipError_t launch_lds8_pair<double, false, MODE_GIBBS>(const ClusterArgs<double>&, const ClusterArgs<double>&,
+    const ClusterArgs<double>&, int, hipStream_t);
+extern template hipError_t launch_lds8_pair<double, true, MODE_GIBBS>(const ClusterArgs<double>&, const ClusterArgs<double>&,
+    const ClusterArgs<double>&, int, hipStream_t);
+extern template hipError_t launch_lds8_pair<double, false, MODE_GROUND>(const ClusterArgs<double>&, const ClusterArgs<double>&,
+    const ClusterArgs<double>&, int, hipStream_t);
+extern template hipError_t launch_lds8_pair<double, true, MODE_GROUND>(const ClusterArgs<double>&, const ClusterArgs<double>&,
+    const ClusterArgs<double>&, int, hipStream_t);
+template <typename T>
+hipError_t launch_triangle_pass(const ClusterArgs<T>& a, const ClusterArgs<T>& e, const ClusterArgs<T>& st, bool cplx,
+                                int mode, int W, hipStream_t s) {
+  if (mode == MODE_GIBBS)
+    return cplx ? launch_lds8_pair<T, true, MODE_GIBBS>(a, e, st, W, s) : launch_lds8_pair<T, false, MODE_GIBBS>(a, e, st, W, s);
+  if constexpr (std::is_same<T, double>::value)
+    if (mode == MODE_GROUND)
+      return cplx ? launch_lds8_pair<T, true, MODE_GROUND>(a, e, st, W, s)
+                  : launch_lds8_pair<T, false, MODE_GROUND>(a, e, st, W, s);
+  return hipErrorInvalidValue;
+}
+
 template <typename T>
 hipError_t launch_msg(const MsgArgs<T>& a, int mode, int block, hipStream_t s) {
   if (a.M == 0 || a.comps == 0) return hipSuccess;
@@ -486,6 +510,10 @@ template hipError_t launch_cluster_pair<float>(const ClusterArgs<float>&, const 
                                                hipStream_t);
 template hipError_t launch_cluster_pair<double>(const ClusterArgs<double>&, const ClusterArgs<double>&, bool, int,
                                                 int, hipStream_t);
+template hipError_t launch_triangle_pass<float>(const ClusterArgs<float>&, const ClusterArgs<float>&,
+                                                const ClusterArgs<float>&, bool, int, int, hipStream_t);
+template hipError_t launch_triangle_pass<double>(const ClusterArgs<double>&, const ClusterArgs<double>&,
+                                                 const ClusterArgs<double>&, bool, int, int, hipStream_t);
 template hipError_t launch_copy<double>(double*, const double*, int64_t, hipStream_t);
 
 }  // namespace lrh
