@@ -264,7 +264,7 @@ def dominant_kernel_roofline(P, nus, beta, f32, torch, reps=3):
         sus = lrh.lrh_measure_fp64_mfma(0)
         extra = dict(sustained_fp64_mfma_tflops=sus, frac_of_sustained=ach / sus,
                      executed_tflops_note="the exponential executes (4 + s) products of 2 D^3 flops per "
-                                          "cluster with float messages, (5 + s) with double ones, s the "
+                                          "cluster, s the "
                                           "squarings (more than the 11 D^3 counted here)")
     return dict(bound=bound, achieved=ach, peak=peak, unit="TFLOP/s", frac=ach / peak, traffic=None, **extra,
                 kernel=f"{kind}, bucket D={D} (n={n}), beta={beta:g}",
