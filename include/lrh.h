@@ -219,7 +219,9 @@ lrh_status lrh_step_nesterov(lrh_problem p, void* nu, void* zeta, lrh_nesterov_s
  *     sweep cap);
  *   D_e = 16, 32 (Householder tridiagonalisation, Sturm bisection): m_e = 8 D_e eps_64
  *     ||theta_e||_F, the value being the lower end of the Sturm bracket;
- *   D_e = 64, 128: as D_e = 16, 32 (one workgroup per cluster, the matrix in a device slab);
+ *   D_e = 64, 128: as D_e = 16, 32 (one workgroup per cluster, the matrix in its registers).
+ *     Every tridiagonalisation works on theta_e over a power of two near its largest entry, so value
+ *     and margin scale exactly with theta_e; where an entry is not finite the value is NaN and counted;
  *   D_e = 256 (lambda_min only, Sec. 4.2: Lanczos for the Ritz value rho, then one
  *     Cholesky factorisation of theta_e - sigma I, sigma = rho - eta, that proves
  *     lambda_min >= sigma - g || |R| ||_1 || |R| ||_inf - 2 u max_i |theta_ii - sigma| - a_e,

@@ -905,6 +905,12 @@ __device__ __forceinline__ T seg_sum(T v) {
   return v;
 }
 template <int W, typename T>
+__device__ __forceinline__ T seg_max(T v) {
+#pragma unroll
+  for (int o = W / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+  return v;
+}
+template <int W, typename T>
 __device__ __forceinline__ T seg_min(T v) {
 #pragma unroll
   for (int o = W / 2; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
@@ -3622,13 +3628,69 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
 // symmetric tridiagonal (d, |e|).  lambda_min is then bracketed by multisection on Sturm counts
 // (number of eigenvalues below x from the signs of the LDL^T pivots), 256 points per round;
 // the lower end of the final bracket, below which no eigenvalue lies, is returned.
+//
+// Every tridiagonalisation here works on theta_e / 2^e, e the binary exponent of its largest component
+// (unit_exponent), and takes the bracket and the margin back by 2^e: powers of two are exact, no
+// square of an entry overflows, and a square that underflows belongs to an entry below 1e-140, where the
+// margin 8 De eps ||theta_e||_F is above 1e-14.
+
+// e with 2^(e-1) <= amax < 2^e; 0 for a matrix that is zero or holds an infinity (NaN entries are not
+// in the maximum: they show in the norm)
+__device__ __forceinline__ int unit_exponent(double amax) {
+  int e = 0;
+  if (amax > 0.0 && amax <= DBL_MAX) (void)frexp(amax, &e);
+  return e;
+}
+
+// Norm xn of a column x, |x_0| and tau = 2 / ||v||^2, v = x + (x_0 / |x_0|) ||x|| e_1, of a matrix scaled as
+// above.  A square below 1e-280 may have lost its digits (x_0 |x_0|^-1 would have another modulus than 1,
+// and the reflection not be one): such an x_0 counts as zero.  A column of norm below 1e-120 is not
+// reflected (tau = 0).  Either changes theta_e by less than 1e-118 of its largest entry.  (tau = 0
+// too where a NaN or infinity reached the column.)
+__device__ __forceinline__ void householder_scalars(double xn2, double x0r, double x0i, double& xn, double& a0,
+                                                    double& tau) {
+  const double a2 = fma(x0r, x0r, x0i * x0i);
+  xn = sqrt(xn2);
+  a0 = a2 > 1e-280 ? sqrt(a2) : 0.0;
+  const double vn2 = 2.0 * (xn2 + a0 * xn);
+  tau = xn2 > 1e-240 ? 2.0 / vn2 : 0.0;
+}
+
+// Value and margin of a cluster from the scaled bracket's lower end and the scaled squared norm.  Scaled
+// finite entries keep every quantity of the reduction finite, so the norm tells whether all were.
+__device__ __forceinline__ void store_tridiag_bound(const ClusterArgs<double>& A, int32_t gid, int De, double lo,
+                                                    double nrm2, int e) {
+  const double v = isfinite(nrm2) ? ldexp(lo, e) : nrm2 - nrm2;   // NaN: a bracket of some rows is no bound
+  A.scal[gid] = v;
+  A.scal2[gid] = ldexp(8.0 * De * DBL_EPSILON * sqrt(nrm2), e);
+  if (!isfinite(v) && A.nonfinite) atomicAdd(A.nonfinite, 1ull);
+}
+
+// theta_e is in the slab, each element written by the thread that scales it here.
 template <bool CPLX, int DE>
-__device__ void tridiag_lambda_min(const ClusterArgs<double>& A, int64_t c, double* ar, double* ai, double nrm2) {
+__device__ void tridiag_lambda_min(const ClusterArgs<double>& A, int64_t c, double* ar, double* ai) {
   __shared__ double vr[DE], vi[DE], pr[DE], pi[DE];
   __shared__ double qvr[DE], qvi[DE], qwr[DE], qwi[DE];
   __shared__ double dg[DE], e2[DE];
   __shared__ double red[16];
   const int tid = threadIdx.x, nth = blockDim.x;
+  double amax = 0.0, n2 = 0.0;
+  for (int idx = tid; idx < DE * DE; idx += nth) {
+    amax = fmax(amax, fabs(ar[idx]));
+    if constexpr (CPLX) amax = fmax(amax, fabs(ai[idx]));
+  }
+  const int ex = unit_exponent(block_max(amax, red));
+  for (int idx = tid; idx < DE * DE; idx += nth) {
+    const double xr = ldexp(ar[idx], -ex);
+    ar[idx] = xr;
+    n2 = fma(xr, xr, n2);
+    if constexpr (CPLX) {
+      const double xi = ldexp(ai[idx], -ex);
+      ai[idx] = xi;
+      n2 = fma(xi, xi, n2);
+    }
+  }
+  const double nrm2 = block_sum(n2, red);
   {
     // The rank-2 update of each reflection is applied during the next reflection's sweep over
     // the trailing matrix (pending vectors qv, qw): every trailing element is read and written
@@ -3661,21 +3723,19 @@ __device__ void tridiag_lambda_min(const ClusterArgs<double>& A, int64_t c, doub
         if constexpr (CPLX) xs = fma(xim, xim, xs);
       }
       const double xn2 = block_sum(xs, red);
-      const double xn = sqrt(xn2);
       const double x0r = vr[0], x0i = vi[0];
-      const double a0 = sqrt(fma(x0r, x0r, x0i * x0i));
+      double xn, a0, tau;
+      householder_scalars(xn2, x0r, x0i, xn, a0, tau);
       if (tid == 0) {
         double ur, ui;
         pend(k, k, ur, ui);
         dg[k] = ar[(int64_t)k * DE + k] - ur;
         e2[k] = xn2;
       }
-      const double vn2 = 2.0 * (xn2 + a0 * xn);
       // an already reduced column (block-uniform) reflects nothing (v = 0) but still flushes the
       // pending update into the trailing matrix
-      const bool act = vn2 > 0.0;
+      const bool act = tau > 0.0;
       const double ur0 = a0 > 0.0 ? x0r / a0 : 1.0, ui0 = a0 > 0.0 ? x0i / a0 : 0.0;
-      const double tau = act ? 2.0 / vn2 : 0.0;
       __syncthreads();
       if (act) {
         if (tid == 0) {   // v = x - alpha e1, alpha = -(x0/|x0|) ||x||
@@ -3774,12 +3834,7 @@ __device__ void tridiag_lambda_min(const ClusterArgs<double>& A, int64_t c, doub
       lo = nlo;
       hi = nhi;
     }
-    const int32_t gid = A.gid[c];
-    if (tid == 0) {
-      A.scal[gid] = lo;
-      A.scal2[gid] = 8.0 * DE * DBL_EPSILON * sqrt(nrm2);
-      if (!isfinite(lo) && A.nonfinite) atomicAdd(A.nonfinite, 1ull);
-    }
+    if (tid == 0) store_tridiag_bound(A, A.gid[c], DE, lo, nrm2, ex);
     __syncthreads();
   }
 }
@@ -3787,14 +3842,12 @@ __device__ void tridiag_lambda_min(const ClusterArgs<double>& A, int64_t c, doub
 template <bool CPLX, int DE>
 __global__ __launch_bounds__(256) void k_cluster_tridiag(ClusterArgs<double> A, double* scratch, int64_t slab) {
   constexpr int64_t DD = (int64_t)DE * DE;
-  __shared__ double red[8];
   const int tid = threadIdx.x, nth = blockDim.x;
   double* ar = scratch + (int64_t)blockIdx.x * slab;
   double* ai = CPLX ? ar + DD : nullptr;
   for (int64_t c = blockIdx.x; c < A.n; c += gridDim.x) {
-    const double my_n2 = big_assemble<double, double, CPLX, false>(A, c, DE, ar, ai, (double*)nullptr,
-                                                                    (double*)nullptr, 0.0, tid, nth);
-    tridiag_lambda_min<CPLX, DE>(A, c, ar, ai, block_sum(my_n2, red));
+    big_assemble<double, double, CPLX, false>(A, c, DE, ar, ai, (double*)nullptr, (double*)nullptr, 0.0, tid, nth);
+    tridiag_lambda_min<CPLX, DE>(A, c, ar, ai);
   }
 }
 
@@ -3818,21 +3871,33 @@ __global__ __launch_bounds__(DE * 4) void k_certify_tridiag(ClusterArgs<double> 
   const int g = __builtin_amdgcn_readfirstlane(tid / 64);
   const int64_t c = xcd_cluster(blockIdx.x, A.n);
   const int64_t ho = A.hoff[c];
-  double ar[NC][NE], ai[NC][NI], my = 0.0;
+  double ar[NC][NE], ai[NC][NI], amax = 0.0, my = 0.0;
 #pragma unroll 4   // in full it is 8000 instructions
   for (int e = 0; e < NE; ++e)
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
       double vr, vi;
       theta_elem<double, CPLX>(A, c, DE, log2i(DE), ho, G * e + g, l + 64 * q, 0.0, vr, vi);
-      my = fma(vr, vr, my);
-      if constexpr (CPLX) my = fma(vi, vi, my);
+      amax = fmax(amax, fabs(vr));
+      if constexpr (CPLX) amax = fmax(amax, fabs(vi));
 #pragma unroll
       for (int f = 0; f < NE; ++f)
         if (f == e) {
           ar[q][f] = vr;
           if constexpr (CPLX) ai[q][f] = vi;
         }
+    }
+  const int ex = __builtin_amdgcn_readfirstlane(unit_exponent(block_max(amax, red)));
+#pragma unroll
+  for (int e = 0; e < NE; ++e)
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      ar[q][e] = ldexp(ar[q][e], -ex);
+      my = fma(ar[q][e], ar[q][e], my);
+      if constexpr (CPLX) {
+        ai[q][e] = ldexp(ai[q][e], -ex);
+        my = fma(ai[q][e], ai[q][e], my);
+      }
     }
   const double nrm2 = block_sum(my, red);
   for (int k = 0; k < DE - 2; ++k) {
@@ -3861,14 +3926,13 @@ __global__ __launch_bounds__(DE * 4) void k_certify_tridiag(ClusterArgs<double> 
       xi[q] = x[l + 64 * q];
       xs = fma(xi[q].x, xi[q].x, fma(xi[q].y, xi[q].y, xs));
     }
-    const double xn2 = wave_sum_dpp(xs), xn = sqrt(xn2);
+    const double xn2 = wave_sum_dpp(xs);
     const double2 x0 = x[k + 1];
-    const double a0 = sqrt(fma(x0.x, x0.x, x0.y * x0.y));
-    const double vn2 = 2.0 * (xn2 + a0 * xn);
+    double xn, a0, tau;
+    householder_scalars(xn2, x0.x, x0.y, xn, a0, tau);
     // v = x - alpha e1, alpha = -(x0/|x0|) ||x||; x = 0: nothing to reflect
     const double ia = a0 > 0.0 ? xn / a0 : 0.0;
     const double2 v0 = a0 > 0.0 ? double2{fma(x0.x, ia, x0.x), fma(x0.y, ia, x0.y)} : double2{xn, 0.0};
-    const double tau = vn2 > 0.0 ? 2.0 / vn2 : 0.0;
     if (tid == 0) e2[k] = xn2;
     // (A v)_i = sum_j conj(A[j][i]) v_j over this wave's rows
     double sr[NC], si[NC];
@@ -4002,13 +4066,7 @@ __global__ __launch_bounds__(DE * 4) void k_certify_tridiag(ClusterArgs<double> 
     lo = nlo;
     hi = nhi;
   }
-  if (tid == 0) {
-    const int32_t gid = A.gid[c];
-    if (!isfinite(nrm2)) lo = nrm2;   // a NaN or infinite entry leaves no bracket
-    A.scal[gid] = lo;
-    A.scal2[gid] = 8.0 * DE * DBL_EPSILON * sqrt(nrm2);
-    if (!isfinite(lo) && A.nonfinite) atomicAdd(A.nonfinite, 1ull);
-  }
+  if (tid == 0) store_tridiag_bound(A, A.gid[c], DE, lo, nrm2, ex);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -4406,9 +4464,8 @@ __global__ __launch_bounds__(1024) void k_certify_lanczos(ClusterArgs<double> A,
       __syncthreads();
     } else {
       if (tid == 0 && A.cert_fallback) atomicAdd(A.cert_fallback, 1ull);
-      const double n2 = block_sum(big_assemble<double, double, CPLX, false>(A, c, DE, ar, ai, (double*)nullptr,
-                                                                            (double*)nullptr, 0.0, tid, NT), red);
-      tridiag_lambda_min<CPLX, DE>(A, c, ar, ai, n2);
+      big_assemble<double, double, CPLX, false>(A, c, DE, ar, ai, (double*)nullptr, (double*)nullptr, 0.0, tid, NT);
+      tridiag_lambda_min<CPLX, DE>(A, c, ar, ai);
     }
   }
 }
@@ -4493,8 +4550,9 @@ __device__ void rows_assemble(const ClusterArgs<double>& A, int64_t c, int i, bo
 // clusters per wave, lane i holding row i of theta_e in registers.  Column k below the diagonal
 // is then one register per lane, the vectors v and w of each reflection are exchanged through
 // LDS, and the reductions stay inside the lane group.  The tridiagonal (d, |e|^2) goes to a
-// workspace (structure of arrays: d_k of cluster c at ws[k n + c], |e_k|^2 at ws[(De + k) n + c])
-// for k_sturm_bisect, which brackets lambda_min with one lane per cluster.
+// workspace (structure of arrays: d_k of cluster c at ws[k n + c], |e_k|^2 at ws[(De + k) n + c], and in the
+// place of a |e_{De-1}|^2 the exponent of the scaling, or NaN where an entry is not finite) for
+// k_sturm_bisect, which brackets lambda_min with one lane per cluster.
 template <bool CPLX, int DE>
 __global__ __launch_bounds__(64) void k_certify_rows(ClusterArgs<double> A, double* ws) {
   constexpr int LD = DE + 1;
@@ -4509,13 +4567,23 @@ __global__ __launch_bounds__(64) void k_certify_rows(ClusterArgs<double> A, doub
   double* di = CPLX ? sai + g * DE * LD : sai;
   rows_assemble<CPLX, DE>(A, c, i, active, dr, di);
   double ar[DE], ai[CPLX ? DE : 1];
-  double n2 = 0.0;
+  double amax = 0.0, n2 = 0.0;
 #pragma unroll
   for (int j = 0; j < DE; ++j) {
     ar[j] = active ? dr[i * LD + j] : 0.0;
-    n2 = fma(ar[j], ar[j], n2);
+    amax = fmax(amax, fabs(ar[j]));
     if constexpr (CPLX) {
       ai[j] = active ? di[i * LD + j] : 0.0;
+      amax = fmax(amax, fabs(ai[j]));
+    }
+  }
+  const int ex = unit_exponent(seg_max<DE>(amax));
+#pragma unroll
+  for (int j = 0; j < DE; ++j) {
+    ar[j] = ldexp(ar[j], -ex);
+    n2 = fma(ar[j], ar[j], n2);
+    if constexpr (CPLX) {
+      ai[j] = ldexp(ai[j], -ex);
       n2 = fma(ai[j], ai[j], n2);
     }
   }
@@ -4531,10 +4599,8 @@ __global__ __launch_bounds__(64) void k_certify_rows(ClusterArgs<double> A, doub
     if (i == k) e2mine = xn2;
     // x0 = element k + 1, the first of x, broadcast from lane k + 1 of the group
     const double x0r = __shfl(xr, g * DE + k + 1, 64), x0i = CPLX ? __shfl(xi, g * DE + k + 1, 64) : 0.0;
-    const double xn = sqrt(xn2), a0 = sqrt(fma(x0r, x0r, x0i * x0i));
-    const double vn2 = 2.0 * (xn2 + a0 * xn);
-    const bool act = vn2 > 0.0;      // uniform in the group: nothing to reflect when x = 0
-    const double tau = act ? 2.0 / vn2 : 0.0;
+    double xn, a0, tau;   // uniform in the group
+    householder_scalars(xn2, x0r, x0i, xn, a0, tau);
     const double ur = a0 > 0.0 ? x0r / a0 : 1.0, ui = a0 > 0.0 ? x0i / a0 : 0.0;
     // v = x - alpha e_{k+1}, alpha = -(x0 / |x0|) ||x||
     double vr = xr, vi = xi;
@@ -4587,8 +4653,8 @@ __global__ __launch_bounds__(64) void k_certify_rows(ClusterArgs<double> A, doub
     if (j == i) dmine = ar[j];
   if (active) {
     ws[(int64_t)i * A.n + c] = dmine;
-    ws[(int64_t)(DE + i) * A.n + c] = (i < DE - 1) ? e2mine : 0.0;
-    if (i == 0) A.scal2[A.gid[c]] = 8.0 * DE * DBL_EPSILON * sqrt(nrm2);
+    ws[(int64_t)(DE + i) * A.n + c] = (i < DE - 1) ? e2mine : isfinite(nrm2) ? (double)ex : nrm2 - nrm2;
+    if (i == 0) A.scal2[A.gid[c]] = ldexp(8.0 * DE * DBL_EPSILON * sqrt(nrm2), ex);
   }
 }
 
@@ -4605,6 +4671,8 @@ __global__ __launch_bounds__(256) void k_sturm_bisect(ClusterArgs<double> A, con
     d[k] = ws[(int64_t)k * A.n + c];
     e2[k] = ws[(int64_t)(DE + k) * A.n + c];
   }
+  const double ex = e2[DE - 1];   // NaN: not finite
+  e2[DE - 1] = 0.0;
   double lo = INFINITY, hi = -INFINITY, emax = 0.0, re_prev = 0.0;
 #pragma unroll
   for (int k = 0; k < DE; ++k) {
@@ -4635,9 +4703,9 @@ __global__ __launch_bounds__(256) void k_sturm_bisect(ClusterArgs<double> A, con
     if (neg) hi = x;   // an eigenvalue below x
     else lo = x;
   }
-  const int32_t gid = A.gid[c];
-  A.scal[gid] = lo;
-  if (!isfinite(lo) && A.nonfinite) atomicAdd(A.nonfinite, 1ull);
+  const double v = ex == ex ? ldexp(lo, (int)ex) : ex;
+  A.scal[A.gid[c]] = v;
+  if (!isfinite(v) && A.nonfinite) atomicAdd(A.nonfinite, 1ull);
 }
 
 // One-wave variant for De = 16, 32: the matrix in LDS, the De rows of A22 v split over
@@ -4653,8 +4721,24 @@ __global__ __launch_bounds__(64) void k_cluster_tridiag_w(ClusterArgs<double> A)
   const int64_t c = xcd_cluster(blockIdx.x, A.n);
   const int l = threadIdx.x;
   const int li = l % DE, lg = l / DE;
-  const double nrm2 = wave_sum_dpp(
-      lds_assemble<double, CPLX, DE, 64>(A, c, l, A.nu_c, nullptr, A.nu_p, nullptr, 0.0, true, 1.0, ar, ai));
+  lds_assemble<double, CPLX, DE, 64>(A, c, l, A.nu_c, nullptr, A.nu_p, nullptr, 0.0, true, 1.0, ar, ai);
+  double amax = 0.0, n2 = 0.0;
+  for (int idx = l; idx < DE * DE; idx += 64) {   // the lane's own elements
+    const int o = idx / DE * LD + idx % DE;
+    amax = fmax(amax, fabs(ar[o]));
+    if constexpr (CPLX) amax = fmax(amax, fabs(ai[o]));
+  }
+  const int ex = __builtin_amdgcn_readfirstlane(unit_exponent(seg_max<64>(amax)));
+  for (int idx = l; idx < DE * DE; idx += 64) {
+    const int o = idx / DE * LD + idx % DE;
+    ar[o] = ldexp(ar[o], -ex);
+    n2 = fma(ar[o], ar[o], n2);
+    if constexpr (CPLX) {
+      ai[o] = ldexp(ai[o], -ex);
+      n2 = fma(ai[o], ai[o], n2);
+    }
+  }
+  const double nrm2 = wave_sum_dpp(n2);
   __syncthreads();
   for (int k = 0; k < DE - 2; ++k) {
     const int m = DE - k - 1;
@@ -4665,17 +4749,15 @@ __global__ __launch_bounds__(64) void k_cluster_tridiag_w(ClusterArgs<double> A)
       if constexpr (CPLX) xs = fma(ai[rk + l], ai[rk + l], xs);
     }
     const double xn2 = wave_sum_dpp(xs);
-    const double xn = sqrt(xn2);
     const double x0r = ar[rk], x0i = CPLX ? -ai[rk] : 0.0;
-    const double a0 = sqrt(fma(x0r, x0r, x0i * x0i));
+    double xn, a0, tau;
+    householder_scalars(xn2, x0r, x0i, xn, a0, tau);
     if (l == 0) {
       dg[k] = ar[k * LD + k];
       e2[k] = xn2;
     }
-    const double vn2 = 2.0 * (xn2 + a0 * xn);
-    if (!(vn2 > 0.0)) continue;   // wave-uniform
+    if (!(tau > 0.0)) continue;   // wave-uniform
     const double ur = a0 > 0.0 ? x0r / a0 : 1.0, ui = a0 > 0.0 ? x0i / a0 : 0.0;
-    const double tau = 2.0 / vn2;
     if (l < m) {
       double r = ar[rk + l], im = CPLX ? -ai[rk + l] : 0.0;
       if (l == 0) {
@@ -4763,12 +4845,7 @@ __global__ __launch_bounds__(64) void k_cluster_tridiag_w(ClusterArgs<double> A)
     lo = nlo;
     hi = nhi;
   }
-  const int32_t gid = A.gid[c];
-  if (l == 0) {
-    A.scal[gid] = lo;
-    A.scal2[gid] = 8.0 * DE * DBL_EPSILON * sqrt(nrm2);
-    if (!isfinite(lo) && A.nonfinite) atomicAdd(A.nonfinite, 1ull);
-  }
+  if (l == 0) store_tridiag_bound(A, A.gid[c], DE, lo, nrm2, ex);
 }
 
 // ------------------------------------------------------------------------------------------
