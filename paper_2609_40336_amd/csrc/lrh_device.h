@@ -267,6 +267,18 @@ __device__ __forceinline__ double rsq_nr(double x) {
   return fma(0.5 * y, fma(-x * y, y, 1.0), y);
 }
 
+// The Jacobi solvers (but the one-lane ones in float and at D = 8) work on the matrix over 2^e,
+// e = norm_exponent(||A||_F^2): its norm is then near one, and the elements whose squares underflow, which
+// are left as they are or rotated with a phase that is not quite of modulus one, are far under the
+// tolerance.  The scaling is exact.  (Unscaled, complex matrices of norm 1e-130, in float 1e-14, never met
+// it.)  0 where the squared norm is zero or not finite.
+template <typename T>
+__device__ __forceinline__ int norm_exponent(T nrm2) {
+  int e = 0;
+  if (nrm2 > T(0) && isfinite(nrm2)) (void)frexp(nrm2, &e);
+  return (e + 1) >> 1;
+}
+
 // A rotation that annihilates a_pq = r e^{i phi}: t, c and g = s e^{-i phi} (real: gi unused), from
 // the diagonal and a_pq, by Newton reciprocals.  An element below 1e-290 (or, complex, whose square
 // is) is left as it is: nz false, t = 0, c = 1, g = 0.
@@ -682,12 +694,20 @@ __device__ void cluster_reg_body(const ClusterArgs<T>& A, int64_t c) {
         if constexpr (CPLX) ui[i][j] = T(0);
       }
   }
-  const double tol2 = A.tol * A.tol * nrm2;
+  constexpr bool ROUNDS = std::is_same<T, double>::value && DE <= 4;
+  const int ex = ROUNDS ? norm_exponent(nrm2) : 0;
+  if constexpr (ROUNDS) {
+#pragma unroll
+    for (int i = 0; i < DE; ++i)
+#pragma unroll
+      for (int j = i; j < DE; ++j) H.set(i, j, ldexp(H.re(i, j), -ex), ldexp(H.im(i, j), -ex));
+  }
+  const double tol2 = A.tol * A.tol * (ROUNDS ? ldexp(nrm2, -2 * ex) : nrm2);
   bool conv = false;
   for (int sweep = 0; sweep <= A.max_sweeps; ++sweep) {
     if (offdiag2<T, CPLX, DE>(H) <= tol2) { conv = true; break; }
     if (sweep == A.max_sweeps) break;
-    if constexpr (std::is_same<T, double>::value && DE <= 4) {
+    if constexpr (ROUNDS) {
       jacobi_sweep_rounds<CPLX, DE, VEC>(H, ur, ui);
     } else {
       jacobi_sweep_reg<T, CPLX, DE, VEC>(H, ur, ui);
@@ -695,16 +715,21 @@ __device__ void cluster_reg_body(const ClusterArgs<T>& A, int64_t c) {
   }
   if (!conv && A.noconv) atomicAdd(A.noconv, 1ull);
   T lam[DE];
-  T lmin = H.r[0];
 #pragma unroll
-  for (int k = 0; k < DE; ++k) { lam[k] = H.r[tri_index(k, k, DE)]; lmin = fmin(lmin, lam[k]); }
+  for (int k = 0; k < DE; ++k) {
+    lam[k] = H.r[tri_index(k, k, DE)];
+    if constexpr (ROUNDS) lam[k] = ldexp(lam[k], ex);
+  }
+  T lmin = lam[0];
+#pragma unroll
+  for (int k = 0; k < DE; ++k) lmin = fmin(lmin, lam[k]);
   if (!isfinite((double)lmin) && A.nonfinite) atomicAdd(A.nonfinite, 1ull);
   if constexpr (MODE == MODE_CERTIFY) {
     // The rotated matrix differs from a diagonal one by its remaining off-diagonal part, so
     // lambda_min >= min diag - ||off||_2 >= min diag - ||off||_F (Weyl): the bound holds whether or
     // not the sweeps reached the tolerance.  The first term is the backward error of the rotations.
     A.scal[gid] = (double)lmin;
-    A.scal2[gid] = 8.0 * DE * DBL_EPSILON * sqrt((double)nrm2) + sqrt(offdiag2<T, CPLX, DE>(H));
+    A.scal2[gid] = 8.0 * DE * DBL_EPSILON * sqrt((double)nrm2) + ldexp(sqrt(offdiag2<T, CPLX, DE>(H)), ex);
     return;
   } else {
     // ---- a4: marginal weights ----
@@ -1179,18 +1204,20 @@ __device__ __forceinline__ T xor_lane(T v) {
 // convergence test are those of the register kernel; G = [[c, conj(g)], [-g, c]], g = s e^{-i phi}.
 // The matrix is read from LDS (sar, sai) and written back with U; lanes lt >= DE of a cluster's
 // group and inactive clusters take part with a zero matrix.  Returns true (lanes lt < DE) when the
-// off-diagonal norm fell below tol2 within max_sweeps sweeps.
+// off-diagonal norm fell below tol times the matrix's, nrm2 its square, within max_sweeps sweeps.
 template <typename T, bool CPLX, int DE, bool VEC>
-__device__ bool xor_jacobi(T* sar, T* sai, T* sur, T* sui, double tol2, int max_sweeps, int lt, bool active) {
+__device__ bool xor_jacobi(T* sar, T* sai, T* sur, T* sui, double tol, T nrm2, int max_sweeps, int lt, bool active) {
   constexpr int LD = DE + 1;
+  const int ex = norm_exponent(nrm2);
+  const double tol2 = tol * tol * ldexp((double)nrm2, -2 * ex);
   const bool mine = active && lt < DE;
   const int j = lt & (DE - 1);
   T ar[DE], ai[CPLX ? DE : 1], ur[VEC ? DE : 1], ui[VEC && CPLX ? DE : 1];
 #pragma unroll
   for (int k = 0; k < DE; ++k) {
     const int o = (j ^ k) * LD + j;
-    ar[k] = mine ? sar[o] : T(0);
-    if constexpr (CPLX) ai[k] = mine ? sai[o] : T(0);
+    ar[k] = mine ? ldexp(sar[o], -ex) : T(0);
+    if constexpr (CPLX) ai[k] = mine ? ldexp(sai[o], -ex) : T(0);
     if constexpr (VEC) ur[k] = k == 0 ? T(1) : T(0);
     if constexpr (VEC && CPLX) ui[k] = T(0);
   }
@@ -1318,8 +1345,8 @@ __device__ bool xor_jacobi(T* sar, T* sai, T* sur, T* sui, double tol2, int max_
 #pragma unroll
     for (int k = 0; k < DE; ++k) {
       const int o = (j ^ k) * LD + j;
-      sar[o] = ar[k];
-      if constexpr (CPLX) sai[o] = ai[k];
+      sar[o] = ldexp(ar[k], ex);
+      if constexpr (CPLX) sai[o] = ldexp(ai[k], ex);
       if constexpr (VEC) sur[o] = ur[k];
       if constexpr (VEC && CPLX) sui[o] = ui[k];
     }
@@ -1349,13 +1376,27 @@ __device__ __forceinline__ void init_vectors(T* sur, T* sui, int lt, bool active
 // init_vectors), W >= min(DE, 64) lanes per cluster: in registers up to DE = 16 (REG), else LDS.  Float passes that return values
 // keep the LDS order of rotations, whose rounding is part of the value.
 template <typename T, bool CPLX, int DE, bool VEC, int W, bool REG>
-__device__ __forceinline__ bool cluster_jacobi(T* sar, T* sai, T* sur, T* sui, ScratchFor<T, DE, REG>& J, double tol2,
-                                               int max_sweeps, int lt, bool active) {
+__device__ __forceinline__ bool cluster_jacobi(T* sar, T* sai, T* sur, T* sui, ScratchFor<T, DE, REG>& J, double tol,
+                                               T nrm2, int max_sweeps, int lt, bool active) {
   if constexpr (REG && DE <= 16) {
     static_assert(W >= DE, "one lane per column");
-    return xor_jacobi<T, CPLX, DE, VEC>(sar, sai, sur, sui, tol2, max_sweeps, lt, active);
+    return xor_jacobi<T, CPLX, DE, VEC>(sar, sai, sur, sui, tol, nrm2, max_sweeps, lt, active);
   } else {
-    return lds_jacobi<T, CPLX, DE, VEC, W>(sar, sai, sur, sui, J, tol2, max_sweeps, lt, active);
+    const int ex = norm_exponent(nrm2);
+    const auto scale = [&](int e) {
+      if (active)
+        for (int idx = lt; idx < DE * DE; idx += W) {
+          const int o = idx / DE * (DE + 1) + idx % DE;
+          sar[o] = ldexp(sar[o], e);
+          if constexpr (CPLX) sai[o] = ldexp(sai[o], e);
+        }
+      __syncthreads();
+    };
+    scale(-ex);
+    const bool conv = lds_jacobi<T, CPLX, DE, VEC, W>(sar, sai, sur, sui, J, tol * tol * ldexp((double)nrm2, -2 * ex),
+                                                      max_sweeps, lt, active);
+    scale(ex);
+    return conv;
   }
 }
 
@@ -1483,7 +1524,7 @@ __device__ __forceinline__ void cluster_lds_body(const ClusterArgs<T>& A, int bl
   init_vectors<T, CPLX, DE, VEC, W, REG>(sur, sui, lt, active);
   __syncthreads();
   // ---- a3: parallel cyclic Jacobi ----
-  const bool conv = cluster_jacobi<T, CPLX, DE, VEC, W, REG>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
+  const bool conv = cluster_jacobi<T, CPLX, DE, VEC, W, REG>(sar, sai, sur, sui, J_[g], A.tol, nrm2,
                                                         A.max_sweeps, lt, active);
   if (active && !conv && lt == 0 && A.noconv) atomicAdd(A.noconv, 1ull);
   T lmin = T(INFINITY);
@@ -1674,7 +1715,7 @@ __global__ __launch_bounds__(64) void k_cluster_gen(ClusterArgs<T> A) {
   init_vectors<T, CPLX, DEP, VEC, W, REG>(sur, sui, lt, active);
   __syncthreads();
   // ---- a3: parallel cyclic Jacobi over DEP (the padding stays decoupled) ----
-  const bool conv = cluster_jacobi<T, CPLX, DEP, VEC, W, REG>(sar, sai, sur, sui, J_[g], A.tol * A.tol * (double)nrm2,
+  const bool conv = cluster_jacobi<T, CPLX, DEP, VEC, W, REG>(sar, sai, sur, sui, J_[g], A.tol, nrm2,
                                                          A.max_sweeps, lt, active);
   if (active && !conv && lt == 0 && A.noconv) atomicAdd(A.noconv, 1ull);
   T lmin = T(INFINITY);
@@ -4893,7 +4934,7 @@ __device__ void cluster_vjp_body(const ClusterArgs<T>& A, int64_t block, int64_t
   const T nrm2 = seg_sum<W>(n2);
   init_vectors<T, CPLX, DE, true, W, true>(sur, sui, tid, active);
   __syncthreads();
-  const bool conv = cluster_jacobi<T, CPLX, DE, true, W, true>(sar, sai, sur, sui, L.J[g], A.tol * A.tol * (double)nrm2,
+  const bool conv = cluster_jacobi<T, CPLX, DE, true, W, true>(sar, sai, sur, sui, L.J[g], A.tol, nrm2,
                                                          A.max_sweeps, tid, active);
   if (active && !conv && tid == 0 && A.noconv) atomicAdd(A.noconv, 1ull);
   T lmin = T(INFINITY);

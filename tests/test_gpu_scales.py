@@ -1,10 +1,11 @@
 """Magnitudes far from one: certified values of matrices whose squares underflow or overflow, or that hold
-single entries of such a size, and of matrices that are not finite."""
+single entries of such a size, and of matrices that are not finite; states and iterations of Hamiltonians
+times a power of two."""
 import numpy as np
 import pytest
 
 import lrh_workloads as W
-from test_gpu_parity import lrhmod, need_gpu, say  # noqa: F401
+from test_gpu_parity import PROBLEMS, lrhmod, need_gpu, say  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -114,3 +115,59 @@ def test_certified_value_of_a_matrix_that_is_not_finite(k, cplx, bad):
     with pytest.raises(lrh.LrhError) as err:
         P.check()
     assert err.value.code == 6
+
+
+def scaled(name, e, f32, seed=3):
+    """Problem and messages of PROBLEMS[name] times 2^e."""
+    P = lrhmod().Problem(W.batch_scaled([PROBLEMS[name]()], [2.0 ** e]), 0)
+    x = 0.3 * torch.randn(P.nu_len, generator=torch.Generator().manual_seed(seed), dtype=torch.float64)
+    nu = P.zeros(f32)
+    nu.copy_(x.float().double() * 2.0 ** e)
+    return P, nu
+
+
+@pytest.mark.parametrize("name", ["c1_tfim16_complex", "randchain_Y3", "randchain_Y4", "randchain_T4_two_level",
+                                  "xxz_tri3", "spin1_Y3_complex", "gue_Y5"])
+@pytest.mark.parametrize("e", [-440, 400])
+def test_double_states_and_iterations_at_any_magnitude(name, e):
+    """H and messages times 2^e (1e-133: squares near the smallest normal number), beta over 2^e: the states,
+    iterates and cotangents are those of H to the entry tolerance of the parity tests, and no solve misses its
+    tolerance.  At beta = 0 every eigenvalue of the small one lies in the ground window, 1e-9 wide: mu = 1 / D."""
+    lrh = lrhmod()
+    out = []
+    for k in (0, e):
+        say(f"[scale] {name} 2^{k}")
+        P, nu = scaled(name, k, False)
+        sc = 2.0 ** k
+        q, g, m = P.dual_eval(nu, 0.7 / sc, grad=True, marg=True)
+        b, mg, lm = P.certify(nu, lmin=True)
+        x, z = nu.clone(), nu.clone()
+        P.step_nesterov(x, z, P.new_nesterov_state(4.0 / sc), 5)
+        r = [q / sc, g, m, lm / sc, mg / sc, x / sc, z / sc]
+        if not name.startswith("spin1"):
+            r.append(P.dual_vjp(nu, 3.0 / sc, qbar=P.qbuf(0.7))[0])
+        if k < 0:
+            assert P.dual_eval(nu, 0.0, grad=True)[1].abs().max().item() < 1e-10
+        torch.cuda.synchronize()
+        assert P.check() == (0, 0)
+        out.append(r)
+    n = P.desc.n_sites
+    for i, (a, b) in enumerate(zip(*out)):
+        assert (a - b).abs().max().item() <= (1e-9 * n if i == 0 else 1e-10)
+
+
+@pytest.mark.parametrize("W_", [8, 16])
+@pytest.mark.parametrize("e", [-43, -58, 40])
+def test_float_lanes_solver_at_any_magnitude(W_, e):
+    """Complex 8 x 8 clusters in lanes, float: as above, at the float tolerance."""
+    out = []
+    for k in (0, e):
+        say(f"[scale float] W={W_} 2^{k}")
+        P, nu = scaled("randchain_T4_two_level", k, True)
+        P.force_shape(8, W_, f32=True)
+        q, g, m = P.dual_eval(nu, 2.0 / 2.0 ** k, grad=True, marg=True)
+        torch.cuda.synchronize()
+        assert P.check() == (0, 0)
+        out.append((q / 2.0 ** k, g, m))
+    for a, b in zip(*out):
+        assert (a - b).abs().max().item() <= 5e-5
