@@ -4904,25 +4904,43 @@ __global__ __launch_bounds__(64) void k_cluster_tridiag_w(ClusterArgs<double> A)
 // nu_bar = B^* Y is then the message kernel's gradient stage (Y_f - Tr_{e\f} Y_e).  At beta = 0
 // the cotangent of Q is Y_e = qbar mu_e (the ground projector; gbar must be absent).
 // W lanes per cluster, 64/W clusters per single-wave block.
-template <typename T, bool CPLX, int DE, int W>
+template <typename T, bool CPLX, int DE, int MODE, int W>
 struct VjpLds {
   static constexpr int G = 64 / W, LD = DE + 1, SZ = G * DE * LD, SI = CPLX ? SZ : 1;
-  T ar[SZ], ur[SZ], xr[SZ], tr[SZ], ai[SI], ui[SI], xi[SI], ti[SI];
+  // A wave per cluster: the products' plane only where there are products; without it a third wave of complex
+  // 32 x 32 clusters fits a CU.  (Several clusters to a wave keep it: five waves on the four SIMDs of
+  // a CU cost more than they bring, 265 us for 8000 real 16 x 16 clusters against 221.)
+  static constexpr int ST = MODE == MODE_GIBBS || G > 1 ? SZ : 1, STI = CPLX ? ST : 1;
+  using Scratch = ScratchFor<T, DE, true>;
+  T ar[SZ], ur[SZ], xr[SZ], yr[ST], ai[SI], ui[SI], xi[SI], yi[STI];
   T p[G * DE], lam[G * DE];
-  ScratchFor<T, DE, true> J[G];
+  Scratch J[G];
 };
+// Where a body finds them: members of one VjpLds, or, a wave per cluster, arrays of their own, which the
+// compiler can tell apart (as members, a cluster of 32 or 64 dimensions takes 4 to 9 % longer).
+template <typename T, typename Scratch>
+struct VjpPlanes {
+  T *ar, *ur, *xr, *yr, *ai, *ui, *xi, *yi, *p, *lam;
+  Scratch* J;
+};
+template <typename T, typename L>
+__device__ __forceinline__ VjpPlanes<T, typename L::Scratch> vjp_planes(L& v) {
+  return {v.ar, v.ur, v.xr, v.yr, v.ai, v.ui, v.xi, v.yi, v.p, v.lam, v.J};
+}
 
 template <typename T, bool CPLX, int DE, int MODE, int W>
-__device__ void cluster_vjp_body(const ClusterArgs<T>& A, int64_t block, int64_t blocks, VjpLds<T, CPLX, DE, W>& L) {
+__device__ void cluster_vjp_body(const ClusterArgs<T>& A, int64_t block, int64_t blocks,
+                                 const VjpPlanes<T, ScratchFor<T, DE, true>>& L) {
   constexpr int LD = DE + 1;
   constexpr int G = 64 / W;
   constexpr int SZ = DE * LD;
-  const int g = threadIdx.x / W, tid = threadIdx.x % W;
+  // (one cluster per wave: constants, which are another 4 to 8 % at D = 32, 64)
+  const int g = G == 1 ? 0 : threadIdx.x / W, tid = G == 1 ? threadIdx.x : threadIdx.x % W;
   const int64_t c = xcd_cluster(block, blocks) * G + g;
-  const bool active = c < A.n;
-  T *sar = L.ar + g * SZ, *sur = L.ur + g * SZ, *sxr = L.xr + g * SZ, *str = L.tr + g * SZ;
+  const bool active = G == 1 || c < A.n;
+  T *sar = L.ar + g * SZ, *sur = L.ur + g * SZ, *sxr = L.xr + g * SZ, *str = L.yr + g * SZ;
   T *sai = CPLX ? L.ai + g * SZ : L.ai, *sui = CPLX ? L.ui + g * SZ : L.ui, *sxi = CPLX ? L.xi + g * SZ : L.xi,
-    *sti = CPLX ? L.ti + g * SZ : L.ti;
+    *sti = CPLX ? L.yi + g * SZ : L.yi;
   T *sp = L.p + g * DE, *slam = L.lam + g * DE;
   const bool has_g = (A.gb_c != nullptr || A.gb_p != nullptr);
   T n2 = T(0);
@@ -5059,26 +5077,36 @@ __device__ void cluster_vjp_body(const ClusterArgs<T>& A, int64_t block, int64_t
 
 template <typename T, bool CPLX, int DE, int MODE, int W>
 __global__ __launch_bounds__(64) void k_cluster_vjp(ClusterArgs<T> A) {
-  __shared__ VjpLds<T, CPLX, DE, W> L;
-  cluster_vjp_body<T, CPLX, DE, MODE, W>(A, blockIdx.x, gridDim.x, L);
+  using L = VjpLds<T, CPLX, DE, MODE, W>;
+  if constexpr (L::G > 1) {
+    __shared__ L lds;
+    cluster_vjp_body<T, CPLX, DE, MODE, W>(A, blockIdx.x, gridDim.x, vjp_planes<T>(lds));
+  } else {
+    // (arrays of one size lie in the order of their names: those of the solver within the reach, 64 KiB, of an
+    // LDS instruction's offset; with the products' plane second the adjoint at D = 64 took 5 % longer)
+    __shared__ T ar[L::SZ], ur[L::SZ], xr[L::SZ], yr[L::ST], ai[L::SI], ui[L::SI], xi[L::SI], yi[L::STI];
+    __shared__ T p[DE], lam[DE];
+    __shared__ typename L::Scratch J[1];
+    cluster_vjp_body<T, CPLX, DE, MODE, W>(A, blockIdx.x, gridDim.x, {ar, ur, xr, yr, ai, ui, xi, yi, p, lam, J});
+  }
 }
 
 // Buckets of D = 8, 4 and 2 in one launch, n8, n4, n2 blocks of each, the longest first (LDS: the
 // largest of the three).  Each bucket reads the messages and writes its own outputs.
 template <bool CPLX>
-constexpr int vjp_group_lds() { return (int)sizeof(VjpLds<double, CPLX, 8, 8>); }
+constexpr int vjp_group_lds() { return (int)sizeof(VjpLds<double, CPLX, 8, MODE_GIBBS, 8>); }
 template <bool CPLX, int MODE>
 __global__ __launch_bounds__(64) void k_cluster_vjp_group(ClusterArgs<double> A8, ClusterArgs<double> A4,
                                                           ClusterArgs<double> A2, int n8, int n4, int n2) {
-  using L8 = VjpLds<double, CPLX, 8, 8>;
-  using L4 = VjpLds<double, CPLX, 4, 4>;
-  using L2 = VjpLds<double, CPLX, 2, 2>;
+  using L8 = VjpLds<double, CPLX, 8, MODE, 8>;
+  using L4 = VjpLds<double, CPLX, 4, MODE, 4>;
+  using L2 = VjpLds<double, CPLX, 2, MODE, 2>;
   static_assert(sizeof(L4) <= sizeof(L8) && sizeof(L2) <= sizeof(L8), "the largest");
   __shared__ __align__(16) unsigned char lds[sizeof(L8)];
   const int b = blockIdx.x;
-  if (b < n8) cluster_vjp_body<double, CPLX, 8, MODE, 8>(A8, b, n8, *reinterpret_cast<L8*>(lds));
-  else if (b < n8 + n4) cluster_vjp_body<double, CPLX, 4, MODE, 4>(A4, b - n8, n4, *reinterpret_cast<L4*>(lds));
-  else cluster_vjp_body<double, CPLX, 2, MODE, 2>(A2, b - n8 - n4, n2, *reinterpret_cast<L2*>(lds));
+  if (b < n8) cluster_vjp_body<double, CPLX, 8, MODE, 8>(A8, b, n8, vjp_planes<double>(*reinterpret_cast<L8*>(lds)));
+  else if (b < n8 + n4) cluster_vjp_body<double, CPLX, 4, MODE, 4>(A4, b - n8, n4, vjp_planes<double>(*reinterpret_cast<L4*>(lds)));
+  else cluster_vjp_body<double, CPLX, 2, MODE, 2>(A2, b - n8 - n4, n2, vjp_planes<double>(*reinterpret_cast<L2*>(lds)));
 }
 
 // ------------------------------------------------------------------------------------------
