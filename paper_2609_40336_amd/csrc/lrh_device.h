@@ -4911,7 +4911,8 @@ struct VjpLds {
   // 32 x 32 clusters fits a CU.  (Several clusters to a wave keep it: five waves on the four SIMDs of
   // a CU cost more than they bring, 265 us for 8000 real 16 x 16 clusters against 221.)
   static constexpr int ST = MODE == MODE_GIBBS || G > 1 ? SZ : 1, STI = CPLX ? ST : 1;
-  using Scratch = ScratchFor<T, DE, true>;
+  static constexpr bool REG = W < 64;   // a wave per cluster: the solver in LDS, on all its lanes
+  using Scratch = ScratchFor<T, DE, REG>;
   T ar[SZ], ur[SZ], xr[SZ], yr[ST], ai[SI], ui[SI], xi[SI], yi[STI];
   T p[G * DE], lam[G * DE];
   Scratch J[G];
@@ -4930,7 +4931,8 @@ __device__ __forceinline__ VjpPlanes<T, typename L::Scratch> vjp_planes(L& v) {
 
 template <typename T, bool CPLX, int DE, int MODE, int W>
 __device__ void cluster_vjp_body(const ClusterArgs<T>& A, int64_t block, int64_t blocks,
-                                 const VjpPlanes<T, ScratchFor<T, DE, true>>& L) {
+                                 const VjpPlanes<T, typename VjpLds<T, CPLX, DE, MODE, W>::Scratch>& L) {
+  constexpr bool REG = VjpLds<T, CPLX, DE, MODE, W>::REG;
   constexpr int LD = DE + 1;
   constexpr int G = 64 / W;
   constexpr int SZ = DE * LD;
@@ -4950,9 +4952,9 @@ __device__ void cluster_vjp_body(const ClusterArgs<T>& A, int64_t block, int64_t
                                             (T)A.gb_offscale, sxr, sxi);
   }
   const T nrm2 = seg_sum<W>(n2);
-  init_vectors<T, CPLX, DE, true, W, true>(sur, sui, tid, active);
+  init_vectors<T, CPLX, DE, true, W, REG>(sur, sui, tid, active);
   __syncthreads();
-  const bool conv = cluster_jacobi<T, CPLX, DE, true, W, true>(sar, sai, sur, sui, L.J[g], A.tol, nrm2,
+  const bool conv = cluster_jacobi<T, CPLX, DE, true, W, REG>(sar, sai, sur, sui, L.J[g], A.tol, nrm2,
                                                          A.max_sweeps, tid, active);
   if (active && !conv && tid == 0 && A.noconv) atomicAdd(A.noconv, 1ull);
   T lmin = T(INFINITY);

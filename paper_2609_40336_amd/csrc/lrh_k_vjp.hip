@@ -22,6 +22,11 @@ hipError_t launch_cluster_vjp(const ClusterArgs<double>& a, bool cplx, int mode,
   VJP_CASE(2, 2)
   VJP_CASE(4, 4)
   VJP_CASE(8, 8)
+  // Complex, up to a wave per SIMD of the chip, a wave per cluster with the solver in LDS: its products are
+  // four times as wide, and the code of the solver in registers (15 000 instructions) does not fit the instruction
+  // cache.  A call on two-level windows of 4 sites, us, beta = 0 / 3: 100 clusters 185 / 200 (16 lanes 211 /
+  // 247), 1000 clusters 205 / 220 (237 / 272); 1400 clusters 287 / 301 (237 / 273).  Real, 16 lanes are the faster.
+  if (a.De == 16 && cplx && a.n <= 1024) VJP_LAUNCH(16, true, 64)
   VJP_CASE(16, 16)
   VJP_CASE(32, 64)
   if (a.De == 64 && !cplx) VJP_LAUNCH(64, false, 64)

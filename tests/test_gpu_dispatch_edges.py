@@ -131,3 +131,29 @@ def test_adjoint_of_the_value_is_the_gradient(L, beta):
     torch.cuda.synchronize()
     # (cotangents of the Frobenius inner product, as the gradient is)
     assert (nb - g).abs().max().item() < 1e-10
+
+
+@pytest.mark.parametrize("beta", [0.0, 3.0])
+def test_complex_sixteen_dimensional_adjoint_switch(beta):
+    """1024 complex 16 x 16 windows (a wave each) and 1025 (16 lanes each) of one chain: the same messages away from
+    the end, so the same cotangents there, two FP64 eigensolvers apart (the entry tolerance)."""
+    lrh = lrhmod()
+    say(f"[vjp D=16 switch] beta={beta}")
+    rng = np.random.default_rng(12)
+    draws = {}
+    out = []
+    for n in (1025, 1024):
+        P = lrh.Problem(W.random_chain(n + 3, seed=6, top_len=4, two_level=True), 0)
+        assert sum(s["n"] for s in P.shapes() if s["De"] == 16) == n
+        for k in P.message_keys():
+            if k not in draws:
+                z = rng.normal(size=(2, 8, 8)) + 1j * rng.normal(size=(2, 8, 8))
+                draws[k] = 0.2 * (z + np.conj(np.swapaxes(z, 1, 2)))
+        nu, gb = (P.from_dense({k: v[i] for k, v in draws.items()}) for i in (0, 1))
+        nb, _ = P.dual_vjp(nu, beta, qbar=P.qbuf(0.7), gbar=gb if beta > 0 else None)
+        torch.cuda.synchronize()
+        assert P.check() == (0, 0)
+        out.append(P.to_dense(nb))
+    keys = [k for k in out[1] if k[0][-1] < 1000]
+    assert len(keys) > 1900
+    assert max(np.abs(out[0][k] - out[1][k]).max() for k in keys) < 1e-10
