@@ -307,10 +307,13 @@ lrh_status lrh_set_certify_method(lrh_problem p, int32_t method);
 
 /* Launch shapes (the W of the calls below), per cluster bucket and precision:
  *   W = 1      register kernel, one lane per cluster (D_e <= 8), Jacobi
- *   W = 8..64  W lanes per cluster, 64/W clusters per wave (8 <= D_e <= 64), Jacobi, in registers
- *              where FP64 and D_e <= 16, else in LDS.  D_e = 8 without a forced shape: 16 lanes up
- *              to 2048 clusters, 8 up to 32768 (float iterations: 24576), then W = 1
- *              where it is compiled (not complex FP64)
+ *   W = 8..64  W lanes per cluster, 64/W clusters per wave (8 <= D_e <= 64), Jacobi: in registers
+ *              at D_e <= 16 (FP64, and float Gibbs states; not complex clusters at W = 64), else in
+ *              LDS.  D_e = 8 without a forced shape: 16 lanes up to 2048 clusters, 8 up to 32768
+ *              (float iterations: 13000 real, 24576 complex), then W = 1 where it is compiled (not
+ *              complex FP64); float evaluations that return values: W = 1.  Shapes agree to
+ *              rounding, so the last bits of a result depend on the size of its bucket: an instance alone
+ *              and the same in a batch may differ in them
  *   W = 1024   one 1024-thread workgroup per cluster, matrix in a device slab (D_e = 128, 256),
  *              Jacobi; ground projector only once the exponential exists for the bucket
  *   W = 0      Gibbs state exp(-beta theta)/Z by scaling and squaring on the FP64 matrix cores,

@@ -276,18 +276,20 @@ inline int comps_of(int D, bool cplx) { return cplx ? D * D : D * (D + 1) / 2; }
 // ------------------------------------------------------------------------------------------
 
 // Launch shape of a bucket until the autotuner or the caller picks one: the first compiled, except for
-// 8 x 8 clusters, where the lanes kernel (W = 8) is faster until one lane per cluster fills the chip.
-// Gibbs pass, us, W = 1 / 8 / 16 (complex double has no W = 1): real float 1022 clusters 37 / 17 / 15,
-// 8190 37 / 19 / 24, 32766 40 / 44 / 69; real double 1022 80 / 25 / 23, 8190 80 / 28 / 40, 32766 86 /
-// 78 / 130; complex float 1022 77 / 27 / 24, 16382 77 / 48 / 76; complex double 1022 - / 40 / 37,
-// 16382 - / 90 / 156.  Float evaluations that return a value keep W = 1: F_beta is the float
-// arithmetic's there, and another order of the rotations rounds it differently.
+// 8 x 8 clusters, where the lanes kernel (W = 8, 16) is faster until one lane per cluster fills the chip.
+// Gibbs pass alone, us, W = 1 / 8 / 16 (complex double has no W = 1): real double 1022 clusters 80 / 25 / 23,
+// 8190 80 / 28 / 40, 32766 86 / 78 / 130; complex double 1022 - / 40 / 37, 16382 - / 90 / 156.  Float iterations on a
+// chain, us for 64 with the smaller clusters, W = 1 / 8 / 16: real 2048 2747 / 1649 / 1484, 8192 2815 / 1789 /
+// 2530, 12288 2895 / 2370 / 3122, 14336 2904 / 2926 / 3659, 20480 3035 / 3567 / 4262 (W = 8 gains as long as the
+// merged launch takes the bonds and sites along: 13 000 clusters); complex 2048 6069 / 2375 / 2156, 16384 6259 /
+// 4734 / 6358, 24576 6774 / 6062 / 8370, 28672 6943 / 7025 / 9375.  Float evaluations that return a value
+// keep W = 1: F_beta is the float arithmetic's there, and another order of the rotations rounds it differently.
 int default_shape(int De, int Dc, int64_t n, bool dbl, bool cplx) {
   int shapes[8];
   const int k = cluster_shapes(De, Dc, dbl, cplx, MODE_GIBBS, shapes);
   if (k == 0) return 1;
   if (De == 8) {
-    const int want = n <= 2048 ? 16 : (n <= (dbl ? 32768 : 24576) ? 8 : 1);
+    const int want = n <= 2048 ? 16 : n <= (dbl ? 32768 : cplx ? 24576 : 13000) ? 8 : 1;
     for (int i = 0; i < k; ++i)
       if (shapes[i] == want) return want;
     if (want == 1) return 8;

@@ -157,3 +157,55 @@ def test_complex_sixteen_dimensional_adjoint_switch(beta):
     keys = [k for k in out[1] if k[0][-1] < 1000]
     assert len(keys) > 1900
     assert max(np.abs(out[0][k] - out[1][k]).max() for k in keys) < 1e-10
+
+
+@pytest.mark.parametrize("n,other", [(32768, 1), (32769, 8)])
+@pytest.mark.parametrize("beta", [0.0, 2.0])
+def test_eight_dimensional_double_shapes_on_both_sides_of_the_last_switch(n, other, beta):
+    """8 lanes per cluster up to 32768 real clusters, one above: against the shape of the other side, both FP64
+    Jacobi (the dual value per site, the oracle's entry tolerance)."""
+    lrh = lrhmod()
+    say(f"[D=8 double switch] n={n} beta={beta}")
+    d = W.with_tops(W.heisenberg_chain(n + 2, field_x=0.4), [tuple(range(i, i + 3)) for i in range(n)])
+    P = lrh.Problem(d, 0)
+    nu = P.zeros()
+    nu.copy_(0.3 * torch.randn(nu.shape, generator=torch.Generator().manual_seed(3), dtype=torch.float64))
+    q, g, m = P.dual_eval(nu, beta, grad=True, marg=True)
+    P.force_shape(8, other, f32=False)
+    q1, g1, m1 = P.dual_eval(nu, beta, grad=True, marg=True)
+    torch.cuda.synchronize()
+    assert not torch.equal(m, m1)   # (another order of rotations, so another shape did run)
+    assert (q - q1).abs().max().item() <= 1e-12 * d.n_sites
+    assert (g - g1).abs().max().item() < 1e-10
+    assert (m - m1).abs().max().item() < 1e-10
+
+
+@pytest.mark.parametrize("cplx,n,default,other", [(False, 2048, 16, 1), (False, 2049, 8, 1), (False, 13000, 8, 1),
+                                                  (False, 13001, 1, 8), (True, 2048, 16, 1), (True, 2049, 8, 1),
+                                                  (True, 24576, 8, 1), (True, 24577, 1, 8)])
+def test_eight_dimensional_float_iterations_at_the_switches(cplx, n, default, other):
+    """Float iterations on n three-site clusters with their bonds and sites (one launch with the 8 x 8 clusters while
+    their blocks are few, apart above) in the default shape, against another: float Jacobi solvers of the same
+    Gibbs states, three steps, at the float entry tolerance."""
+    lrh = lrhmod()
+    say(f"[D=8 float switch] cplx={cplx} n={n}")
+    d = (W.random_chain(n + 2, seed=7, top_len=3, subintervals=True) if cplx else
+         W.with_tops(W.heisenberg_chain(n + 2, field_x=0.4), [tuple(range(i, i + 3)) for i in range(n)],
+                     subintervals=True))
+    P = lrh.Problem(d, 0)
+    x = 0.3 * torch.randn(P.nu_len, generator=torch.Generator().manual_seed(3), dtype=torch.float64)
+    out = {}
+    for shape in (None, default, other):
+        if shape:
+            P.force_shape(8, shape, f32=True)
+        nu = P.zeros(True)
+        nu.copy_(x)
+        ze = nu.clone()
+        P.step_nesterov(nu, ze, P.new_nesterov_state(2.0), 3)
+        torch.cuda.synchronize()
+        assert P.check() == (0, 0)
+        out[shape] = (nu, ze)
+    for k in (0, 1):
+        assert torch.equal(out[None][k], out[default][k])
+        assert not torch.equal(out[None][k], out[other][k])
+        assert (out[None][k] - out[other][k]).abs().max().item() < 5e-5
