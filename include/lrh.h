@@ -342,22 +342,26 @@ lrh_status lrh_set_certify_method(lrh_problem p, int32_t method);
  * results agree to rounding. */
 lrh_status lrh_autotune(lrh_problem p, uint32_t flags, const char* cache_path, hipStream_t stream);
 
-/* Launch shapes in use, one entry per cluster bucket (at most `cap` written; *count = number
- * of buckets): dimensions, cluster count, block / lanes-per-cluster, measured microseconds
- * (0 when not measured).  Host arrays, any may be NULL except count. */
+/* Launch shapes in use by the float accelerated iterations, one entry per cluster bucket (at most
+ * `cap` written; *count = number of buckets): dimensions, cluster count, threads per block of the
+ * register kernel, W, measured microseconds (0 when not measured).  The block is the one launched
+ * with, which need not be the one set (see lrh_set_shape).  Host arrays, any may be NULL except count. */
 lrh_status lrh_get_shapes(lrh_problem p, int32_t cap, int32_t* De, int32_t* Dc, int64_t* n, int32_t* block,
                           int32_t* W, double* us, int32_t* count);
 
 /* Force the launch shape of every cluster bucket of dimension De for the precision of `flags`
  * (LRH_F32: FP32 iterations, else FP64): block = threads per block of the register kernel
- * (64, 128, 256), W one of the shapes listed above for the Gibbs pass.  Errors:
+ * (64, 128, 256), W one of the shapes listed above for the Gibbs pass.  A pass launches 4 x 4
+ * clusters with site children and the sites (W = 1) together, in the former's block, and where it
+ * takes 8 x 8 clusters in lanes, or float 16 x 16 ones at W = 0, along with them, in blocks of 64; a
+ * block set or tuned for these buckets has effect only where they are launched apart.  Errors:
  * LRH_E_INVALID (no such bucket, bad block), LRH_E_UNSUPPORTED (shape not compiled for that
  * bucket). */
 lrh_status lrh_set_shape(lrh_problem p, int32_t De, int32_t block, int32_t W, uint32_t flags);
 
 /* Per-bucket kernel timing for roofline accounting: runs reps + 1 launches of every cluster
- * bucket's kernel (Gibbs state at beta > 0, ground projector at beta = 0) at the messages nu
- * (device, precision of `flags`), in each bucket's current shape, on `stream`, and writes the
+ * bucket's kernel by itself (Gibbs state at beta > 0, ground projector at beta = 0) at the messages
+ * nu (device, precision of `flags`), in the shape of the iterations, on `stream`, and writes the
  * average duration of one launch in microseconds to us[b] (host array, one entry per bucket in
  * lrh_get_shapes order).  Overwrites the library's workspace; synchronises the stream.
  * Errors: LRH_E_INVALID (null pointer, reps < 1, beta < 0), LRH_E_DEVICE. */

@@ -1103,6 +1103,42 @@ PairOf pair_of(const lrh_problem_s* P, bool dbl, int mode, bool value) {
   return r.edges && r.sites ? r : PairOf{};
 }
 
+// Buckets that a plain pass takes in one launch with the bonds and sites.
+struct MergedPass {
+  PairOf pair;
+  const CBucket* plaq = nullptr;   // 16-dimensional clusters, float Gibbs
+  const CBucket* tri = nullptr;    // 8 x 8 clusters in tri_W lanes
+  int tri_W = 0;
+  // threads per block that the pass launches the bucket's register kernel with
+  int block(const CBucket& B) const {
+    const bool paired = &B == pair.edges || &B == pair.sites;
+    return !paired ? B.block : plaq || tri ? 64 : pair.edges->block;
+  }
+};
+MergedPass merged_pass(const lrh_problem_s* P, bool dbl, int mode, bool value) {
+  MergedPass m;
+  m.pair = pair_of(P, dbl, mode, value);
+  if (!m.pair.edges) return m;
+  // The bonds and sites are small launches bound by latency: one launch for both, in float together
+  // with 16-dimensional clusters (in double the pair's registers would halve that kernel's waves).
+  if (!dbl && mode == MODE_GIBBS)
+    for (const CBucket& B : P->cb)
+      if (B.De == 16 && !m.plaq && shape_for(P, B, dbl, mode, value) == 0) m.plaq = &B;
+  // Likewise with 8 x 8 clusters in 8 or 16 lanes each, up to the blocks that their registers let the chip
+  // hold at once (two waves per SIMD in real double; beyond, the bonds would wait for them at that
+  // occupancy): 8192 triangles, 12288 bonds and 4096 sites in real double 24 + 8 us, together 24.6.
+  if (!m.plaq && (mode == MODE_GIBBS || (dbl && mode == MODE_GROUND)))
+    for (const CBucket& B : P->cb) {
+      const int W = B.De == 8 ? shape_for(P, B, dbl, mode, value) : 0;
+      if (m.tri || (W != 8 && W != 16) || B.n == 0) continue;
+      if ((B.n * W + 63) / 64 + (m.pair.edges->n + m.pair.sites->n) / 64 + 2 <= 2048) {
+        m.tri = &B;
+        m.tri_W = W;
+      }
+    }
+  return m;
+}
+
 // One plain pass of the cluster kernels over every bucket at (nu, zeta, theta).
 template <typename T>
 ClusterArgs<T> pass_args(lrh_problem_s* P, const CBucket& B, const T* nu, const T* ze, double theta, double beta,
@@ -1133,27 +1169,9 @@ template <typename T>
 lrh_status cluster_pass(lrh_problem_s* P, const T* nu, const T* ze, double theta, int mode, double beta,
                         T* marg, hipStream_t s, const FusedParams* tab = nullptr, bool value = true) {
   const bool dbl = sizeof(T) == 8;
-  const PairOf pr = pair_of(P, dbl, mode, value);
-  // The bonds and sites are small launches bound by latency: one launch for both, in float together
-  // with 16-dimensional clusters (in double the pair's registers would halve that kernel's waves).
-  const CBucket* plaq = nullptr;
-  if (!dbl && pr.edges && mode == MODE_GIBBS)
-    for (const CBucket& B : P->cb)
-      if (B.De == 16 && !plaq && shape_for(P, B, dbl, mode, value) == 0) plaq = &B;
-  // Likewise with 8 x 8 clusters in 8 or 16 lanes each, up to the blocks that their registers let the chip
-  // hold at once (two waves per SIMD in real double; beyond, the bonds would wait for them at that
-  // occupancy): 8192 triangles, 12288 bonds and 4096 sites in real double 24 + 8 us, together 24.6.
-  const CBucket* tri = nullptr;
-  int trW = 0;
-  if (!plaq && pr.edges && (mode == MODE_GIBBS || (dbl && mode == MODE_GROUND)))
-    for (const CBucket& B : P->cb) {
-      const int W = B.De == 8 ? shape_for(P, B, dbl, mode, value) : 0;
-      if (tri || (W != 8 && W != 16) || B.n == 0) continue;
-      if ((B.n * W + 63) / 64 + (pr.edges->n + pr.sites->n) / 64 + 2 <= 2048) {
-        tri = &B;
-        trW = W;
-      }
-    }
+  const MergedPass mg = merged_pass(P, dbl, mode, value);
+  const PairOf& pr = mg.pair;
+  const CBucket *plaq = mg.plaq, *tri = mg.tri;
   for (const CBucket& B : P->cb) {
     if (&B == pr.sites || &B == plaq || &B == tri) continue;   // with the edges
     ClusterArgs<T> a = pass_args<T>(P, B, nu, ze, theta, beta, marg, tab);
@@ -1166,7 +1184,7 @@ lrh_status cluster_pass(lrh_problem_s* P, const T* nu, const T* ze, double theta
         }
       }
       if (tri)
-        HIP_TRY(launch_triangle_pass<T>(pass_args<T>(P, *tri, nu, ze, theta, beta, marg, tab), a, st, P->cplx, mode, trW, s));
+        HIP_TRY(launch_triangle_pass<T>(pass_args<T>(P, *tri, nu, ze, theta, beta, marg, tab), a, st, P->cplx, mode, mg.tri_W, s));
       else
         HIP_TRY(launch_cluster_pair<T>(a, st, P->cplx, mode, B.block, s));
       continue;
@@ -1189,7 +1207,7 @@ lrh_status time_buckets_t(lrh_problem_s* P, const T* nu, double beta, int reps, 
   for (size_t b = 0; b < P->cb.size(); ++b) {
     const CBucket& B = P->cb[b];
     ClusterArgs<T> a = pass_args<T>(P, B, nu, nullptr, 0.0, beta, nullptr, nullptr);
-    const int W = shape_for(P, B, sizeof(T) == 8, mode);
+    const int W = shape_for(P, B, sizeof(T) == 8, mode, false);   // the iterations' shape
     HIP_TRY(launch_cluster<T>(a, P->cplx, mode, B.block, W, s));
     HIP_TRY(hipEventRecord(e0, s));
     for (int r = 0; r < reps; ++r) HIP_TRY(launch_cluster<T>(a, P->cplx, mode, B.block, W, s));
@@ -2180,8 +2198,8 @@ lrh_status lrh_get_shapes(lrh_problem p, int32_t cap, int32_t* De, int32_t* Dc, 
     if (De) De[i] = B.De;
     if (Dc) Dc[i] = B.Dc;
     if (n) n[i] = B.n;
-    if (block) block[i] = B.block;
-    if (W) W[i] = B.W;  // FP32 iteration shape
+    if (block) block[i] = merged_pass(p, false, MODE_GIBBS, false).block(B);
+    if (W) W[i] = B.Wit != 0 ? B.Wit : B.W;   // FP32 iteration shape
     if (us) us[i] = B.tuned_us;
   }
   return LRH_OK;
