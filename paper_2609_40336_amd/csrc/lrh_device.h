@@ -63,8 +63,6 @@ template <typename T> __device__ __forceinline__ T dfma(T a, T b, T c);
 template <> __device__ __forceinline__ float dfma<float>(float a, float b, float c) { return fmaf(a, b, c); }
 template <> __device__ __forceinline__ double dfma<double>(double a, double b, double c) { return fma(a, b, c); }
 
-// Algorithm 2 extrapolation / averaging (1 - th) x + th y, with one explicit rounding
-// pattern so that every kernel computing it from the same inputs gets the same bits.
 // Cluster handled by workgroup i of a launch with one workgroup per cluster (n of them).  The
 // dispatcher hands consecutive workgroups to the 8 XCDs in turn, and each XCD has its own L2;
 // consecutive clusters read neighbouring messages (one cache line holds the same component of
@@ -76,6 +74,8 @@ __device__ __forceinline__ int64_t xcd_cluster(int64_t i, int64_t n) {
   return x * q + (x < r ? x : r) + j;
 }
 
+// Algorithm 2 extrapolation / averaging (1 - th) x + th y, with one explicit rounding
+// pattern so that every kernel computing it from the same inputs gets the same bits.
 template <typename T>
 __device__ __forceinline__ T extrap(T x, T y, T th) {
   return dfma<T>(T(1) - th, x, th * y);
@@ -250,9 +250,6 @@ __device__ __forceinline__ void ptrace_reg(const HMat<T, CPLX, DE>& Rh, HMat<T, 
     }
 }
 
-// One cyclic sweep of two-sided Jacobi rotations over all pairs (p < q), row-cyclic order.
-// Branch-free: a pair with a_pq == 0 gets the identity rotation (t = 0, c = 1, s = 0), so the
-// unrolled sweep is straight-line code.
 // 1 / x and 1 / sqrt(x) of a positive normal number: the hardware estimate and two Newton steps
 // (within about one unit in the last place), a third of the dependent instructions of the exact
 // division and root.
@@ -376,8 +373,10 @@ __device__ __forceinline__ void jacobi_sweep_rounds(HMat<double, CPLX, D>& A, do
   }
 }
 
-// A sweep in float, and at D = 8 in double (where the registers are full): pairs row by row.  (The dual
-// values of float evaluations carry this order's rounding, so it stays.)
+// One cyclic sweep of two-sided Jacobi rotations over all pairs (p < q), row by row: in float, and at D = 8
+// in double (where the registers are full).  Branch-free: a pair with a_pq == 0 gets the identity
+// rotation (t = 0, c = 1, s = 0), so the unrolled sweep is straight-line code.  (The dual values of
+// float evaluations carry this order's rounding, so it stays.)
 template <typename T, bool CPLX, int D, bool VEC>
 __device__ __forceinline__ void jacobi_sweep_reg(HMat<T, CPLX, D>& A, T (&ur)[D][D], T (&ui)[D][D]) {
 #pragma unroll
@@ -1372,9 +1371,10 @@ __device__ __forceinline__ void init_vectors(T* sur, T* sui, int lt, bool active
   }
 }
 
-// Eigenvalues onto the diagonal of (sar, sai), eigenvectors into (sur, sui) when VEC (see
-// init_vectors), W >= min(DE, 64) lanes per cluster: in registers up to DE = 16 (REG), else LDS.  Float passes that return values
-// keep the LDS order of rotations, whose rounding is part of the value.
+// Eigenvalues onto the diagonal of (sar, sai), eigenvectors into (sur, sui) when VEC (see init_vectors),
+// W >= min(DE, 64) lanes per cluster: in registers up to DE = 16 where the caller says so (REG), else in LDS.
+// In LDS stay float ground projectors and spin-1 clusters, for the rounding that their order of rotations
+// puts into the values they return, and complex clusters with a whole wave.
 template <typename T, bool CPLX, int DE, bool VEC, int W, bool REG>
 __device__ __forceinline__ bool cluster_jacobi(T* sar, T* sai, T* sur, T* sui, ScratchFor<T, DE, REG>& J, double tol,
                                                T nrm2, int max_sweeps, int lt, bool active) {
@@ -2153,8 +2153,8 @@ __global__ __launch_bounds__(1024) void k_cluster_big(ClusterArgs<T> A, T* scrat
 //     rho = Y_s / Tr Y_s,  log Z = 2^s log tau_0 + sum_j 2^(s-j) log tau_j + log Tr Y_s
 // for any positive rescalings tau_j (the one-wave kernel uses exact powers of two; the
 // workgroup kernel tau_0 = Tr E0, tau_j = (Tr Y_{j-1})^2).
-// A relative error e of p acts like e 2^s on X, at most (e / kMax) times 2 r: 3e-15 r with double
-// messages, under the float rounding of the messages with float ones.  Rounding in the squarings adds a
+// A relative error e of p acts like e 2^s on X, at most 2 e r / kMax: 4e-15 r with double messages,
+// under the float rounding of the messages with float ones.  Rounding in the squarings adds a
 // relative error of order D u (spectral spread / gap) to rho: the part along the dominant eigenvector is
 // removed by the final trace normalisation, the rest is damped once the spectrum separates.  With double
 // messages everything runs in FP64.  With float messages the polynomial and the first squarings do
@@ -2175,9 +2175,12 @@ constexpr int kF64Squarings = 2;   // float-message path: squarings kept in FP64
 // four products,
 //     a6 = (y3 + b2 y2 + b1 y)^2 + r3 y3 + r2 y2 + r1 y,   p = (a6 + s3 y3 + s2 y2 + s1 y + s0) a6
 //          + t2 y2 + t1 y + 1,    y2 = y y, y3 = y y2,
-// kappa chosen to make the leading coefficient one.  Double messages: error 1.2e-15 on |x| <= 0.75
-// (a degree-12 Taylor polynomial takes five products and has 2e-14 on |x| <= 1/2); float messages:
-// 3.5e-10 on |x| <= 2 (degree-8 Taylor: four products, 5.4e-9 on |x| <= 1/2).
+// kappa chosen to make the leading coefficient one.  (The form B1 + (B2 + A6) A6, A6 = B3 + B4^2, is that of
+// Bader, Blanes and Casas, Computing the matrix exponential with an optimized Taylor polynomial
+// approximation, 2019; there for Taylor coefficients.)  Double messages: error 1.4e-15 on
+// |x| <= 0.75 with the coefficients rounded to doubles, 1.2e-15 before (a degree-12 Taylor polynomial,
+// error 2e-14 on |x| <= 1/2, took five products by powers of X^3); float messages: 3.5e-10 on |x| <= 2
+// (degree-8 Taylor: four products, 5.4e-9 on |x| <= 1/2).
 template <typename T>
 struct ExpPoly;
 template <>
@@ -2735,10 +2738,11 @@ __device__ __forceinline__ void cluster_expm_body(const ClusterArgs<T>& A, int64
   }
   // Float messages: the squarings after the first kF64Squarings run on the FP32 matrix cores.  A
   // relative rounding error e in Y_j acts on rho like an error of about 2^(s-j) e in
-  // X = beta (theta - mu); ||X|| is between 1 and 2 (kMax) times 2^s, so after two squarings
-  // the float ones perturb X by at most about ||X|| u_32 / 4 times the product's error growth, the
-  // order of what the float rounding of the messages themselves puts on X (beta ||nu|| u_32).  The
-  // polynomial and the first squarings, where the error would be amplified most, stay in FP64.
+  // X = beta (theta - mu).  2^s is below r = sqrt(||X^2||_1), the bound that set it, so after two squarings
+  // the float ones perturb X by at most about r u_32 / 4 times the product's error growth.  r is at
+  // most D^(1/4) times ||X|| (2 at D = 16, 2.4 at 32; 1.6 seen at 32), so this is the order of what the float
+  // rounding of the messages themselves puts on X (beta ||nu|| u_32).  The polynomial and the first
+  // squarings, where the error would be amplified most, stay in FP64.
   int n64 = s;
   if constexpr (std::is_same<T, float>::value) n64 = s < kF64Squarings ? s : kF64Squarings;
   auto post = [&](XMat<NB, CPLX>& Y, int j) {

@@ -1585,7 +1585,11 @@ lrh_status vjp_pass(lrh_problem_s* P, const double* nu, double beta, const doubl
   const int mode = beta > 0 ? MODE_GIBBS : MODE_GROUND;
   // The first buckets of D = 8, 4 and 2 share a launch while about twice the blocks that are resident
   // at once cover them: each alone leaves the chip idle while its wave-long chains of rotations run
-  // (8192 triangles, 12288 bonds and 4096 sites: 30 + 16 + 8.5 us; together 34 us).
+  // (8192 triangles, 12288 bonds and 4096 sites: 30 + 16 + 8.5 us; together 34 us).  A call, us, beta = 3, apart /
+  // together: real, half the resident blocks 76 / 53, as many 79 / 58, 1.8 times 106 / 91, 2.1 times 128 /
+  // 99, 3.7 times 160 / 148, 9 times 330 / 311; complex, 0.4 times 86 / 61, 1.7 times 94 / 85, 4 times 202 /
+  // 182.  (So the line, which stands where the first size was measured, is not a crossing: together is
+  // still 6 to 23 % faster above it.)
   ClusterArgs<double> grp[3] = {};
   int64_t blocks = 0;
   int parts = 0;

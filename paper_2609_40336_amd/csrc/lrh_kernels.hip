@@ -88,11 +88,10 @@ __device__ __forceinline__ void wave_sum_comp(double& s, double& e) {
   for (int o = 32; o > 0; o >>= 1) add_comp(s, e, __shfl_xor(s, o, 64), __shfl_xor(e, o, 64));
 }
 
-// Per-instance sums over the contiguous library-cluster range of each instance, in a fixed
-// order (strided per-thread partial sums, then a fixed tree that carries its rounding errors, so that
-// the sum of tens of thousands of clusters is good to its last place): bitwise reproducible.  One workgroup
-// per instance; a thread keeps 8 loads in flight (one at a time, the 20 470 clusters of a single
-// chain took 21 us).
+// Per-instance sums over the contiguous library-cluster range of each instance, in a fixed order
+// (strided per-thread partial sums, 40 plain additions for the 20 470 clusters of a long chain, then a fixed tree
+// that carries its rounding errors): bitwise reproducible.  One workgroup per instance; a thread
+// keeps 8 loads in flight (one at a time, those 20 470 clusters took 21 us).
 constexpr int kReduceThreads = 512;
 template <bool TWO>
 __global__ __launch_bounds__(kReduceThreads) void k_reduce(const double* scal, const int64_t* ptr, double* out,
