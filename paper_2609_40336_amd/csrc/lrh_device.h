@@ -3036,16 +3036,10 @@ __device__ __forceinline__ int wg_block(int t, int k) {
 template <bool CPLX, int DE>
 constexpr int wg_stage_bytes() { return WgPlan<DE>::ks * DE * (CPLX ? 2 : 1) * (int)sizeof(double); }
 
-template <typename S>
-struct WgMfma;
-template <>
-struct WgMfma<double> {
-  typedef mfma_f64x4 acc;
-  static __device__ __forceinline__ acc mma(double a, double b, acc c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int l, int r) { return 4 * r + (l >> 4); }
-};
+__device__ __forceinline__ mfma_f64x4 wg_mma(double a, double b, mfma_f64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ int wg_row(int l, int r) { return 4 * r + (l >> 4); }   // row of result register r
 // Bank swizzles of a stage.  Row k: the four rows that one fragment read touches would start on the
 // same bank, so its blocks of 16 elements are permuted by block ^ wg_swizzle(k), which depends on the
 // low bits of k only (those of l / 16 for a reading lane).  Columns are staged as DE pieces of CC
@@ -3062,17 +3056,17 @@ __device__ __forceinline__ int wg_csw(int i) {
 }
 
 // Sizes of a stage: KS rows (complex: and columns) of X (and of Y unless SAME; then half as many).
-template <typename S, bool CPLX, int DE, bool SAME>
+template <bool CPLX, int DE, bool SAME>
 struct WgStage {
   using P = WgPlan<DE>;
   static constexpr int NPL = CPLX ? 2 : 1;
-  static constexpr int KS0 = P::ks * (int)(sizeof(double) / sizeof(S)) / (SAME ? 1 : 2);
+  static constexpr int KS0 = P::ks / (SAME ? 1 : 2);
   static constexpr int KS = KS0 < DE ? KS0 : DE;
   static constexpr int NK = DE / KS;
-  static constexpr int PB = KS * DE * (int)sizeof(S);    // bytes of a panel (rows or columns)
+  static constexpr int PB = KS * DE * (int)sizeof(double);   // bytes of a panel (rows or columns)
   static constexpr int NINS = PB / 1024;                 // wave loads per panel
-  static constexpr int CPR = DE * (int)sizeof(S) / 16;   // 16-byte chunks per row
-  static constexpr int CC = KS * (int)sizeof(S) / 16;    // and per column piece
+  static constexpr int CPR = DE / 2;   // 16-byte chunks per row
+  static constexpr int CC = KS / 2;    // and per column piece
   static constexpr int NPAN = NPL * (SAME ? 1 : 2);
   static_assert(NINS * 1024 == PB && KS % 4 == 0 && NK * KS == DE, "whole wave loads and stages");
   static_assert(NPAN * PB <= wg_stage_bytes<CPLX, DE>(), "stage fits its buffer");
@@ -3080,20 +3074,20 @@ struct WgStage {
 
 // Rows (and columns) k0 .. k0 + KS - 1 to the buffer, by LDS-direct loads spread over the waves:
 // panels X rows, X columns, Y rows, Y columns.
-template <typename S, bool CPLX, int DE, bool SAME>
-__device__ __forceinline__ void wg_fill(const S* X, const S* Y, int k0, unsigned char* buf, int wave, int l) {
-  using G = WgStage<S, CPLX, DE, SAME>;
-  constexpr int EPC = 16 / (int)sizeof(S);   // elements per chunk
+template <bool CPLX, int DE, bool SAME>
+__device__ __forceinline__ void wg_fill(const double* X, const double* Y, int k0, unsigned char* buf, int wave, int l) {
+  using G = WgStage<CPLX, DE, SAME>;
+  constexpr int EPC = 2;   // elements per chunk
 #pragma unroll
   for (int pan = 0; pan < G::NPAN; ++pan) {
-    const S* Z = pan < G::NPL ? X : Y;
+    const double* Z = pan < G::NPL ? X : Y;
 #pragma unroll 2
     for (int q = wave; q < G::NINS; q += G::P::waves) {
       const int ch = q * 64 + l;
       int64_t o;
       if (pan % G::NPL == 0) {
         const int k = ch / G::CPR, cp = ch % G::CPR;
-        o = (int64_t)(k0 + k) * DE + (cp ^ (wg_swizzle<S, DE>(k) * (int)sizeof(S))) * EPC;   // sizeof(S) chunks per block
+        o = (int64_t)(k0 + k) * DE + (cp ^ (wg_swizzle<double, DE>(k) * 8)) * EPC;   // 8 chunks per block
       } else {
         const int i = ch / G::CC, cp = ch % G::CC;
         o = (int64_t)i * DE + k0 + (cp ^ wg_csw<G::CC>(i)) * EPC;
@@ -3106,45 +3100,44 @@ __device__ __forceinline__ void wg_fill(const S* X, const S* Y, int k0, unsigned
 
 // Accumulators of a wave's blocks: real: s1 the block; complex: s1 of Z1 Z2, s4 of (Z1^T Z2^T), p2 of
 // -(2 N1)(2 N2)
-template <typename S, bool CPLX, int DE>
+template <bool CPLX, int DE>
 struct WgAcc {
   static constexpr int N = WgPlan<DE>::nblk;
-  typename WgMfma<S>::acc s1[N], s4[CPLX ? N : 1], p2[CPLX ? N : 1];
+  mfma_f64x4 s1[N], s4[CPLX ? N : 1], p2[CPLX ? N : 1];
 };
 
 // One stage: the next one's loads are issued into `nxt` (k0 >= 0), then the products of the rows in
 // `st` are accumulated.  The two are different buffers: `restrict` tells the compiler so, which
 // would otherwise wait for the loads before the first read.  oz, ow: byte offsets of a lane's row and
 // column elements at kk = 0 (A blocks, then B blocks).
-template <typename S, bool CPLX, int DE, bool SAME>
-__device__ __forceinline__ void wg_step(const unsigned char* __restrict__ st, unsigned char* __restrict__ nxt, const S* X,
-                                        const S* Y, int k0, int wave, int l,
+template <bool CPLX, int DE, bool SAME>
+__device__ __forceinline__ void wg_step(const unsigned char* __restrict__ st, unsigned char* __restrict__ nxt, const double* X,
+                                        const double* Y, int k0, int wave, int l,
                                         const int (&oz)[WgPlan<DE>::na + WgPlan<DE>::nb],
-                                        const int (&ow)[WgPlan<DE>::na + WgPlan<DE>::nb], WgAcc<S, CPLX, DE>& acc) {
+                                        const int (&ow)[WgPlan<DE>::na + WgPlan<DE>::nb], WgAcc<CPLX, DE>& acc) {
   using P = WgPlan<DE>;
-  using F = WgMfma<S>;
-  using G = WgStage<S, CPLX, DE, SAME>;
+  using G = WgStage<CPLX, DE, SAME>;
   constexpr int NF = P::na + P::nb;
-  if (k0 >= 0) wg_fill<S, CPLX, DE, SAME>(X, Y, k0, nxt, wave, l);
+  if (k0 >= 0) wg_fill<CPLX, DE, SAME>(X, Y, k0, nxt, wave, l);
 #pragma unroll 4
   for (int kk = 0; kk < G::KS / 4; ++kk) {
-    S z[NF], w[NF];
+    double z[NF], w[NF];
 #pragma unroll
     for (int q = 0; q < NF; ++q) {
-      z[q] = *reinterpret_cast<const S*>(st + oz[q] + kk * 4 * DE * (int)sizeof(S));
+      z[q] = *reinterpret_cast<const double*>(st + oz[q] + kk * 4 * DE * (int)sizeof(double));
       // chunk (4 kk + l / 16) / EPC of the piece, permuted: kk only toggles bits of the offset
-      if constexpr (CPLX) w[q] = *reinterpret_cast<const S*>(st + (ow[q] ^ (kk * 4 * (int)sizeof(S))));
+      if constexpr (CPLX) w[q] = *reinterpret_cast<const double*>(st + (ow[q] ^ (kk * 4 * (int)sizeof(double))));
     }
 #pragma unroll
     for (int b = 0; b < P::nblk; ++b) {
       const int ia = P::ab[b], ib = P::na + P::bb[b];
       if constexpr (CPLX) {
         // A operands are transposes of what the lanes hold
-        acc.s1[b] = F::mma(w[ia], z[ib], acc.s1[b]);
-        acc.s4[b] = F::mma(z[ia], w[ib], acc.s4[b]);
-        acc.p2[b] = F::mma(z[ia] - w[ia], z[ib] - w[ib], acc.p2[b]);
+        acc.s1[b] = wg_mma(w[ia], z[ib], acc.s1[b]);
+        acc.s4[b] = wg_mma(z[ia], w[ib], acc.s4[b]);
+        acc.p2[b] = wg_mma(z[ia] - w[ia], z[ib] - w[ib], acc.p2[b]);
       } else {
-        acc.s1[b] = F::mma(z[ia], z[ib], acc.s1[b]);
+        acc.s1[b] = wg_mma(z[ia], z[ib], acc.s1[b]);
       }
     }
   }
@@ -3154,18 +3147,17 @@ __device__ __forceinline__ void wg_step(const unsigned char* __restrict__ st, un
 // element (j, i), for every block I <= J.  X, Y: slab matrices.  s0, s1: buffers of
 // wg_stage_bytes().  All waves call it, after a barrier that follows the writes of X and Y; it ends
 // with one itself.
-template <typename S, bool CPLX, int DE, bool SAME, typename Epi>
-__device__ __forceinline__ void wg_product(const S* X, const S* Y, unsigned char* s0, unsigned char* s1, int tid,
+template <bool CPLX, int DE, bool SAME, typename Epi>
+__device__ __forceinline__ void wg_product(const double* X, const double* Y, unsigned char* s0, unsigned char* s1, int tid,
                                            Epi&& epi) {
   using P = WgPlan<DE>;
-  using F = WgMfma<S>;
-  using G = WgStage<S, CPLX, DE, SAME>;
+  using G = WgStage<CPLX, DE, SAME>;
   static_assert(G::NK % 2 == 0, "stages alternate between the buffers");
   constexpr int NF = P::na + P::nb;
-  constexpr int ES = (int)sizeof(S);
+  constexpr int ES = (int)sizeof(double);
   const int wave = __builtin_amdgcn_readfirstlane(tid / 64), l = tid % 64;
   const int lr = l >> 4, lc = l & 15;
-  wg_fill<S, CPLX, DE, SAME>(X, Y, 0, s0, wave, l);
+  wg_fill<CPLX, DE, SAME>(X, Y, 0, s0, wave, l);
 #pragma unroll 1
   for (int pass = 0; pass < P::passes; ++pass) {
     const int t = pass * P::waves + wave;
@@ -3174,31 +3166,31 @@ __device__ __forceinline__ void wg_product(const S* X, const S* Y, unsigned char
     for (int q = 0; q < NF; ++q) {
       blk[q] = wg_block<DE>(t, q);
       const int pan = q < P::na || SAME ? 0 : G::NPL * G::PB;   // X's panels, or Y's
-      oz[q] = pan + (lr * DE + 16 * (blk[q] ^ wg_swizzle<S, DE>(lr)) + lc) * ES;
+      oz[q] = pan + (lr * DE + 16 * (blk[q] ^ wg_swizzle<double, DE>(lr)) + lc) * ES;
       ow[q] = pan + G::PB + (16 * blk[q] + lc) * G::CC * 16 + (((lr * ES / 16) ^ wg_csw<G::CC>(lc)) * 16 | (lr * ES & 15));
     }
-    WgAcc<S, CPLX, DE> acc;
+    WgAcc<CPLX, DE> acc;
 #pragma unroll
     for (int b = 0; b < P::nblk; ++b) {
-      acc.s1[b] = typename F::acc{0, 0, 0, 0};
-      if constexpr (CPLX) acc.s4[b] = acc.p2[b] = typename F::acc{0, 0, 0, 0};
+      acc.s1[b] = mfma_f64x4{0, 0, 0, 0};
+      if constexpr (CPLX) acc.s4[b] = acc.p2[b] = mfma_f64x4{0, 0, 0, 0};
     }
 #pragma unroll 1
     for (int K = 0; K < G::NK; K += 2) {
       __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's loads of the stage have landed
       __syncthreads();                      // and every wave's; the other buffer is no longer read
-      wg_step<S, CPLX, DE, SAME>(s0, s1, X, Y, (K + 1) * G::KS, wave, l, oz, ow, acc);
+      wg_step<CPLX, DE, SAME>(s0, s1, X, Y, (K + 1) * G::KS, wave, l, oz, ow, acc);
       __builtin_amdgcn_s_waitcnt(0x0f70);
       __syncthreads();
       const int k0 = K + 2 < G::NK ? (K + 2) * G::KS : (pass + 1 < P::passes ? 0 : -1);
-      wg_step<S, CPLX, DE, SAME>(s1, s0, X, Y, k0, wave, l, oz, ow, acc);
+      wg_step<CPLX, DE, SAME>(s1, s0, X, Y, k0, wave, l, oz, ow, acc);
     }
 #pragma unroll
     for (int b = 0; b < P::nblk; ++b) {
       const int I = blk[P::ab[b]], J = blk[P::na + P::bb[b]];
       if (I > J) continue;   // a 2 x 2 tile on the diagonal also covers its block below it
       if constexpr (CPLX) {
-        const typename F::acc p = S(0.5) * acc.p2[b];
+        const mfma_f64x4 p = 0.5 * acc.p2[b];
         epi(I, J, acc.s1[b] + p, acc.s4[b] + p);
       } else {
         epi(I, J, acc.s1[b], acc.s1[b]);
@@ -3310,29 +3302,29 @@ __device__ __forceinline__ void wg_square32(const float* Y, unsigned char* s0, u
 }
 
 // Elements (i, j) of block (I, J), I <= J, to the slab matrix C: v, and u to (j, i).
-template <typename D, typename S, int DE>
-__device__ __forceinline__ void wg_store(D* C, int I, int J, int l, const S (&v)[4], const S (&u)[4]) {
+template <int DE>
+__device__ __forceinline__ void wg_store(double* C, int I, int J, int l, const double (&v)[4], const double (&u)[4]) {
   const int j = 16 * J + (l & 15);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int i = 16 * I + WgMfma<S>::row(l, r);
-    C[i * DE + j] = (D)v[r];
-    if (I != J) C[j * DE + i] = (D)u[r];
+    const int i = 16 * I + wg_row(l, r);
+    C[i * DE + j] = v[r];
+    if (I != J) C[j * DE + i] = u[r];
   }
 }
 // The result instead as planes R and N: of its upper triangle, as the outputs read it, or (FULL) whole.
-template <bool CPLX, typename D, typename S, int DE, bool FULL = false>
-__device__ __forceinline__ void wg_store_planes(D* C, int I, int J, int l, const S (&v)[4], const S (&u)[4]) {
+template <bool CPLX, typename D, int DE, bool FULL = false>
+__device__ __forceinline__ void wg_store_planes(D* C, int I, int J, int l, const double (&v)[4], const double (&u)[4]) {
   constexpr int64_t DD = (int64_t)DE * DE;
   const int j = 16 * J + (l & 15);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int i = 16 * I + WgMfma<S>::row(l, r);
-    const D re = CPLX ? (D)(S(0.5) * (v[r] + u[r])) : (D)v[r];
+    const int i = 16 * I + wg_row(l, r);
+    const D re = CPLX ? (D)(0.5 * (v[r] + u[r])) : (D)v[r];
     C[i * DE + j] = re;
     if (FULL && I != J) C[j * DE + i] = re;
     if constexpr (CPLX) {
-      const D im = (D)(S(0.5) * (v[r] - u[r]));
+      const D im = (D)(0.5 * (v[r] - u[r]));
       C[DD + i * DE + j] = im;
       if (FULL && I != J) C[DD + j * DE + i] = -im;
     }
@@ -3480,7 +3472,7 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
     __builtin_amdgcn_s_waitcnt(0x0f70);
     __syncthreads();
     // ---- X^2, its column sums (per block row, in the still unused Q) and the scale; see k_cluster_expm ----
-    wg_product<double, CPLX, DE, true>(X, X, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
+    wg_product<CPLX, DE, true>(X, X, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
       double v[4], u[4], m[4], cs = 0.0;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -3500,7 +3492,7 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
           if ((l & 15) == 0) Q[J * DE + 16 * I + 4 * r + (l >> 4)] = m[r];
         }
       }
-      wg_store<double, double, DE>(P2, I, J, l, v, u);
+      wg_store<DE>(P2, I, J, l, v, u);
     });
     double rmax = 0.0;
     for (int i = tid; i < DE; i += nth) {
@@ -3527,7 +3519,7 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
     // (offsets of register r: o of (i, j), ot of (j, i))
     const auto off = [&](int I, int J, int r) { return (16 * I + 4 * r + (l >> 4)) * DE + 16 * J + (l & 15); };
     const auto offt = [&](int I, int J, int r) { return (16 * J + (l & 15)) * DE + 16 * I + 4 * r + (l >> 4); };
-    wg_product<double, CPLX, DE, false>(X, P2, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
+    wg_product<CPLX, DE, false>(X, P2, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
       double v[4], u[4], wv[4], wu[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -3542,12 +3534,12 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
           wu[r] = fma(EP::b2 * f2, P2[ot], fma(EP::b1 * f1, X[ot], u[r]));
         }
       }
-      wg_store<double, double, DE>(P3, I, J, l, v, u);
-      wg_store<double, double, DE>(M, I, J, l, wv, wu);
+      wg_store<DE>(P3, I, J, l, v, u);
+      wg_store<DE>(M, I, J, l, wv, wu);
     });
     // Q = a6, and a6 + s3 y3 + s2 y2 + s1 y + s0 over P3 (off the diagonal blocks each element is read
     // only by the thread that replaces it; within a diagonal block the whole wave reads first)
-    wg_product<double, CPLX, DE, true>(M, M, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
+    wg_product<CPLX, DE, true>(M, M, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
       double v[4], u[4], wv[4], wu[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -3567,8 +3559,8 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
         }
         if (I == J && 4 * r + (l >> 4) == (l & 15)) wv[r] += EP::s0;
       }
-      wg_store<double, double, DE>(Q, I, J, l, v, u);
-      wg_store<double, double, DE>(P3, I, J, l, wv, wu);
+      wg_store<DE>(Q, I, J, l, v, u);
+      wg_store<DE>(P3, I, J, l, wv, wu);
     });
     // Float messages: the last n32 squarings in FP32, a relative rounding error e in the first of them
     // acting on X = beta (theta - mu) like 2^n32 e: 2^n32 stays below ||X|| / 4, ||X|| the smaller of X's
@@ -3577,7 +3569,7 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
     // longer needs by then; the double squaring before them writes these.  The last product of all
     // writes planes too.
     double trp = 0.0;   // this thread's share of the trace
-    wg_product<double, CPLX, DE, false>(P3, Q, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
+    wg_product<CPLX, DE, false>(P3, Q, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
       double v[4], u[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -3594,8 +3586,8 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
           trp += v[r];
         }
       }
-      if (s == 0) wg_store_planes<CPLX, double, double, DE>(M, I, J, l, v, u);
-      else wg_store<double, double, DE>(M, I, J, l, v, u);
+      if (s == 0) wg_store_planes<CPLX, double, DE>(M, I, J, l, v, u);
+      else wg_store<DE>(M, I, J, l, v, u);
     });
     // ---- normalise and square: Z_{j+1} = Z_j^2 / (Tr Z_j)^2 ----
     double t = block_sum(trp, red);
@@ -3604,7 +3596,7 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
       const double scale = 1.0 / (t * t);
       const bool last32 = kF32 && j + 1 == n64 && n64 < s;
       trp = 0.0;
-      wg_product<double, CPLX, DE, true>(M, M, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
+      wg_product<CPLX, DE, true>(M, M, stage0, stage1, tid, [&](int I, int J, mfma_f64x4 av, mfma_f64x4 au) {
         double v[4], u[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -3612,9 +3604,9 @@ __global__ __launch_bounds__(WgPlan<DE>::waves * 64) void k_cluster_expm_wg(Clus
           u[r] = scale * au[r];
           if (I == J && 4 * r + (l >> 4) == (l & 15)) trp += v[r];
         }
-        if (last32) wg_store_planes<CPLX, float, double, DE, true>(fa, I, J, l, v, u);
-        else if (j + 1 == s) wg_store_planes<CPLX, double, double, DE>(Q, I, J, l, v, u);
-        else wg_store<double, double, DE>(Q, I, J, l, v, u);
+        if (last32) wg_store_planes<CPLX, float, DE, true>(fa, I, J, l, v, u);
+        else if (j + 1 == s) wg_store_planes<CPLX, double, DE>(Q, I, J, l, v, u);
+        else wg_store<DE>(Q, I, J, l, v, u);
       });
       double* tp = M;
       M = Q;
