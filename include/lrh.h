@@ -308,7 +308,7 @@ lrh_status lrh_set_certify_method(lrh_problem p, int32_t method);
 /* Launch shapes (the W of the calls below), per cluster bucket and precision:
  *   W = 1      register kernel, one lane per cluster (D_e <= 8), Jacobi
  *   W = 8..64  W lanes per cluster, 64/W clusters per wave (8 <= D_e <= 64), Jacobi: in registers
- *              at D_e <= 16 (FP64, and float Gibbs states; not complex clusters at W = 64), else in
+ *              at D_e <= 16 (FP64, and float Gibbs states; at W = 64 only real D_e = 8), else in
  *              LDS.  D_e = 8 without a forced shape: 16 lanes up to 2048 clusters, 8 up to 32768
  *              (float iterations: 13000 real, 24576 complex), then W = 1 where it is compiled (not
  *              complex FP64); float evaluations that return values: W = 1.  Shapes agree to

@@ -1374,7 +1374,7 @@ __device__ __forceinline__ void init_vectors(T* sur, T* sui, int lt, bool active
 // Eigenvalues onto the diagonal of (sar, sai), eigenvectors into (sur, sui) when VEC (see init_vectors),
 // W >= min(DE, 64) lanes per cluster: in registers up to DE = 16 where the caller says so (REG), else in LDS.
 // In LDS stay float ground projectors and spin-1 clusters, for the rounding that their order of rotations
-// puts into the values they return, and complex clusters with a whole wave.
+// puts into the values they return, and complex or 16-dimensional clusters with a whole wave.
 template <typename T, bool CPLX, int DE, bool VEC, int W, bool REG>
 __device__ __forceinline__ bool cluster_jacobi(T* sar, T* sai, T* sur, T* sui, ScratchFor<T, DE, REG>& J, double tol,
                                                T nrm2, int max_sweeps, int lt, bool active) {
@@ -1504,9 +1504,10 @@ __device__ __forceinline__ void cluster_lds_body(const ClusterArgs<T>& A, int bl
   __shared__ T sai_[CPLX ? G * SZ : 1];
   __shared__ T sur_[VEC ? G * SZ : 1];
   __shared__ T sui_[(VEC && CPLX) ? G * SZ : 1];
-  // (float ground values keep the order of rotations of the solver in LDS; a complex cluster with a whole wave
-  // is solved there too, on all its lanes: 2000 16 x 16 clusters in double 297 us, in registers 440)
-  constexpr bool REG = (sizeof(T) == 8 || MODE == MODE_GIBBS) && !(CPLX && W == 64);
+  // (float ground values keep the order of rotations of the solver in LDS; a complex or 16-dimensional cluster
+  // with a whole wave is solved there too, on all its lanes: 16 x 16 clusters in double, us, registers /
+  // LDS: 2000 complex 440 / 297, 123 000 real 8000 / 5800)
+  constexpr bool REG = (sizeof(T) == 8 || MODE == MODE_GIBBS) && !(W == 64 && (CPLX || DE == 16));
   __shared__ ScratchFor<T, DE, REG> J_[G];
   __shared__ T sp_[G * DE];
   const int g = threadIdx.x / W, lt = threadIdx.x % W;
