@@ -262,10 +262,12 @@ def dominant_kernel_roofline(P, nus, beta, f32, torch, reps=3):
     if bound == "mfma":
         from paper_2609_40336_amd import lrh
         sus = lrh.lrh_measure_fp64_mfma(0)
-        extra = dict(sustained_fp64_mfma_tflops=sus, frac_of_sustained=ach / sus,
-                     executed_tflops_note="the exponential executes (4 + s) products of 2 D^3 flops per "
-                                          "cluster, s the "
-                                          "squarings (more than the 11 D^3 counted here)")
+        note = ("the exponential executes (4 + s) products of 2 D^3 flops per cluster, s the "
+                "squarings (more than the 11 D^3 counted here)" if W == 0 else
+                "the exponential executes (4 + s) products, s the squarings, of the blocks on and above the "
+                "diagonal only, three real products to a complex one (float squarings: four, at the FP32 "
+                "rate): fewer flops than counted here, so the fraction can exceed one")
+        extra = dict(sustained_fp64_mfma_tflops=sus, frac_of_sustained=ach / sus, executed_tflops_note=note)
     return dict(bound=bound, achieved=ach, peak=peak, unit="TFLOP/s", frac=ach / peak, traffic=None, **extra,
                 kernel=f"{kind}, bucket D={D} (n={n}), beta={beta:g}",
                 per_launch=dict(flops=F, seconds=t,
@@ -537,14 +539,15 @@ def cpu_oracle_legs(Ls, hs, beta, budget):
 
 def profile_traffic_run(P, torch, beta, passes=3):
     """Short run for hardware counters: `passes` Gibbs passes over every cluster bucket (FP32
-    messages, seeded noise of scale 0.3) at `beta` and one FP64 certification of the same
-    messages, then a 64 MiB device copy (a plain copy kernel of known size, to scale FETCH_SIZE /
-    WRITE_SIZE)."""
+    messages, seeded noise of scale 0.3) at `beta`, two launches of every bucket's kernel by itself
+    and one FP64 certification of the same messages, then a 64 MiB device copy (a plain copy kernel
+    of known size, to scale FETCH_SIZE / WRITE_SIZE)."""
     g = torch.Generator(device="cuda")
     g.manual_seed(1)
     nu = (0.3 * torch.randn(P.nu_len, generator=g, device="cuda", dtype=torch.float64)).float()
     for _ in range(passes):
         P.dual_eval(nu, beta, grad=True)
+    P.time_buckets(nu, beta, 1)
     P.certify(nu)
     src = torch.ones(16 * 2 ** 20, dtype=torch.float32, device="cuda")
     dst = torch.empty_like(src)

@@ -1119,15 +1119,11 @@ MergedPass merged_pass(const lrh_problem_s* P, bool dbl, int mode, bool value) {
   MergedPass m;
   m.pair = pair_of(P, dbl, mode, value);
   if (!m.pair.edges) return m;
-  // The bonds and sites are small launches bound by latency: one launch for both, in float together
-  // with 16-dimensional clusters (in double the pair's registers would halve that kernel's waves).
-  if (!dbl && mode == MODE_GIBBS)
-    for (const CBucket& B : P->cb)
-      if (B.De == 16 && !m.plaq && shape_for(P, B, dbl, mode, value) == 0) m.plaq = &B;
-  // Likewise with 8 x 8 clusters in 8 or 16 lanes each, up to the blocks that their registers let the chip
-  // hold at once (two waves per SIMD in real double; beyond, the bonds would wait for them at that
-  // occupancy): 8192 triangles, 12288 bonds and 4096 sites in real double 24 + 8 us, together 24.6.
-  if (!m.plaq && (mode == MODE_GIBBS || (dbl && mode == MODE_GROUND)))
+  // The bonds and sites are small launches bound by latency: one launch for both, together with 8 x 8 clusters
+  // in 8 or 16 lanes each up to the blocks that their registers let the chip hold at once (two waves
+  // per SIMD in real double; beyond, the bonds would wait for them at that occupancy): 8192 triangles,
+  // 12288 bonds and 4096 sites in real double 24 + 8 us, together 24.6.
+  if (mode == MODE_GIBBS || (dbl && mode == MODE_GROUND))
     for (const CBucket& B : P->cb) {
       const int W = B.De == 8 ? shape_for(P, B, dbl, mode, value) : 0;
       if (m.tri || (W != 8 && W != 16) || B.n == 0) continue;
@@ -1136,6 +1132,14 @@ MergedPass merged_pass(const lrh_problem_s* P, bool dbl, int mode, bool value) {
         m.tri_W = W;
       }
     }
+  // Else, in float, with 16-dimensional clusters (in double the pair's registers would halve that kernel's
+  // waves) up to 200 000 of them: an iteration of plaquettes, us, together / apart: 2401 20 / 28, 32 000 103 / 112,
+  // 91 000 269 / 277, 201 000 583 / 584, 429 000 1250 / 1229, 837 000 2440 / 2388 (the launches fill the chip and the
+  // registers of the larger kernel slow the bonds).  With the 8 x 8 clusters where both could be: complex
+  // 4-site intervals of 1000 sites 53.7 against 58.8, 6000 98.5 against 112.
+  if (!dbl && mode == MODE_GIBBS && !m.tri)
+    for (const CBucket& B : P->cb)
+      if (B.De == 16 && !m.plaq && B.n <= 200000 && shape_for(P, B, dbl, mode, value) == 0) m.plaq = &B;
   return m;
 }
 

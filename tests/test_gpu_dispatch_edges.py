@@ -209,3 +209,46 @@ def test_eight_dimensional_float_iterations_at_the_switches(cplx, n, default, ot
         assert torch.equal(out[None][k], out[default][k])
         assert not torch.equal(out[None][k], out[other][k])
         assert (out[None][k] - out[other][k]).abs().max().item() < 5e-5
+
+
+@pytest.mark.parametrize("f32", [True, False])
+def test_plaquettes_on_both_sides_of_the_merged_launch(f32):
+    """199 809 plaquettes (in float one launch with their bonds and sites) and 200 704 (apart): from zero messages every
+    periodic lattice iterates translation-invariantly, so both have one bound per site (to rounding of the sums)."""
+    lrh = lrhmod()
+    out = []
+    for L in (447, 448, 5):
+        say(f"[plaquette merge] L={L} f32={f32}")
+        P = lrh.Problem(W.tfim_plaquette_batch([L], [1.7]), 0)
+        nu, ze = P.zeros(f32), P.zeros(f32)
+        P.step_nesterov(nu, ze, P.new_nesterov_state(3.0), 4)
+        q, _, _ = P.certify(nu)
+        torch.cuda.synchronize()
+        assert P.check() == (0, 0)
+        out.append(q.item() / L ** 2)
+    assert abs(out[0] - out[1]) <= 1e-9 and abs(out[0] - out[2]) <= (1e-5 if f32 else 1e-9)
+
+
+@pytest.mark.parametrize("n", [6, 900, 9400])
+def test_float_iterations_of_triples_and_quadruples_in_one_pass(n):
+    """8 x 8 clusters in lanes share the bonds' launch, 16 x 16 ones go apart (up to some 9000 complex triples; the other
+    way round above): against one lane per 8 x 8 cluster, at the float entry tolerance."""
+    lrh = lrhmod()
+    say(f"[triples and quadruples] n={n}")
+    P = lrh.Problem(W.random_chain(n, seed=11, top_len=4, subintervals=True), 0)
+    x = 0.3 * torch.randn(P.nu_len, generator=torch.Generator().manual_seed(3), dtype=torch.float64)
+    out = []
+    for shape in (None, 1):
+        if shape:
+            P.force_shape(8, shape, f32=True)
+        for fused in (False, True):
+            nu = P.zeros(True)
+            nu.copy_(x)
+            ze = nu.clone()
+            P.step_nesterov(nu, ze, P.new_nesterov_state(2.0), 3, fused=fused)
+            torch.cuda.synchronize()
+            out.append((nu, ze))
+    assert P.check() == (0, 0)
+    for k in (0, 1):
+        assert torch.equal(out[0][k], out[1][k]) and torch.equal(out[2][k], out[3][k])
+        assert (out[0][k] - out[2][k]).abs().max().item() < 5e-5
